@@ -132,7 +132,7 @@ typedef struct lpht_config {
 
 /* Launch parameters of the kernels; see lpht_set_tuning. */
 typedef struct lpht_tuning {
-  uint32_t block_threads; /* workgroup size, a multiple of 64 in 64..1024 */
+  uint32_t block_threads; /* workgroup size, a multiple of 64 in 64..1024 (width 1: at most 256 of it) */
   uint32_t group_width;   /* lanes that probe one operation together: 1, 2, 4, 8 or 16 */
   uint32_t blocks_per_cu; /* resident workgroups per compute unit the grid is sized for, 1..32 */
   uint32_t migrate_block; /* old cells per migration workgroup, power of two 256..8192 */

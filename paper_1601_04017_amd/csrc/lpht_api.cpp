@@ -543,7 +543,9 @@ int run_bulk(lpht_table *t, OpKind op, const void *keys, const void *vals, uint6
     p.flags = flags ? flags + done : nullptr;
     p.n = len;
     LaunchCfg cfg = t->launch;
-    cfg.group_width = pick_group_width(t, op, inserting ? used0 + done + len : t->known_used + t->pending);
+    const uint64_t used1 = inserting ? used0 + done + len : t->known_used + t->pending;
+    cfg.group_width = pick_group_width(t, op, used1);
+    cfg.dense = used1 > c / 2;
     const hipError_t e = launch_bulk(op, p, cfg, s);
     if (e != hipSuccess) return from_hip(e);
     done += len;

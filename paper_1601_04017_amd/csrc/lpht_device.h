@@ -1,7 +1,6 @@
 // Device helpers of liblpht shared by its kernel sources: the hash (CRC-32C
 // pair, Sec. 8.3) and the position map (Sec. 5.3.1), device atomics, count
-// reductions and cell access.  Included by lpht_kernels.hip and
-// lpht_shrink.hip only.
+// reductions and cell access.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -49,6 +48,51 @@ __device__ __forceinline__ uint32_t crc0_u64(const uint32_t (*T)[256], u64 x) {
 // CRC(0, x) over the 4 little-endian bytes of a 32-bit key.
 __device__ __forceinline__ uint32_t crc0_u32(const uint32_t (*T)[256], uint32_t x) {
   return T[3][x & 0xFF] ^ T[2][(x >> 8) & 0xFF] ^ T[1][(x >> 16) & 0xFF] ^ T[0][x >> 24];
+}
+
+// CRC(0, x) without tables: over GF(2) the register is a 32 x 64 bit matrix
+// times the key, so output bit i is the parity of the key under row i.  With
+// the rows as literals a bit is and, and-xor, popcount and a shift-in, about
+// 130 VALU instructions per key with no LDS, no set-up and no barrier.  The
+// one-operation-per-lane kernels hash one key per lane and use this; kernels
+// that hash many keys per workgroup amortise the 8 KiB tables above.
+struct CrcRows {
+  u64 row[32];
+};
+
+constexpr CrcRows crc_rows(int nbytes) {
+  CrcRows m{};
+  for (int j = 0; j < 8 * nbytes; ++j) {
+    // the register after the message whose only set bit is bit j
+    uint32_t r = 0;
+    for (int i = 0; i < nbytes; ++i) {
+      if (i == j / 8) r ^= 1u << (j % 8);
+      for (int k = 0; k < 8; ++k) r = (r >> 1) ^ (kPolyRefl & (0u - (r & 1u)));
+    }
+    for (int i = 0; i < 32; ++i) m.row[i] |= (u64)((r >> i) & 1u) << j;
+  }
+  return m;
+}
+
+template <int NBYTES, int I = 0>
+__device__ __forceinline__ uint32_t crc0_bits(uint32_t lo, uint32_t hi, uint32_t acc = 0) {
+  if constexpr (I == 32) {
+    return acc;
+  } else {
+    constexpr u64 row = crc_rows(NBYTES).row[I];
+    const uint32_t bits = (lo & (uint32_t)row) ^ (hi & (uint32_t)(row >> 32));
+    // shift the parity in from the top: after 32 steps bit I holds row I
+    return crc0_bits<NBYTES, I + 1>(lo, hi, __builtin_amdgcn_alignbit((uint32_t)__builtin_popcount(bits), acc, 1));
+  }
+}
+
+// The table's 64-bit hash of a key (as hash_of below), without tables.
+template <int LAYOUT>
+__device__ __forceinline__ u64 hash_direct(u64 key, uint32_t crc_hi, uint32_t crc_lo, u64 mul) {
+  if (mul) return key * mul;
+  const uint32_t c = LAYOUT == 0 ? crc0_bits<4>((uint32_t)key, 0u)
+                                 : crc0_bits<8>((uint32_t)key, (uint32_t)(key >> 32));
+  return ((u64)(c ^ crc_hi) << 32) | (u64)(c ^ crc_lo);
 }
 
 // The table's 64-bit hash of a key.  mul == 0: the CRC-32C pair

@@ -64,6 +64,7 @@ struct LaunchCfg {
   uint32_t num_cus;
   uint32_t migrate_block;
   uint32_t aggregate;
+  uint32_t dense;        // the table may be more than half full after the call
 };
 
 // A launch wrapper reports its launches through hipGetLastError.  HIP keeps

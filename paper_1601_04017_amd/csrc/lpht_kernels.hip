@@ -6,8 +6,9 @@
 //
 // Execution model
 // ---------------
-// A "group" of G lanes (G = 1, 2, 4, 8, 16; all in one wavefront) works on one
-// operation at a time.  The group scans the table in windows of G consecutive
+// A "group" of G lanes (G = 2, 4, 8, 16; all in one wavefront) works on one
+// operation at a time (G = 1, the default, has kernels of its own in
+// lpht_lane.hip; here it remains for the resident serving kernel).  The group scans the table in windows of G consecutive
 // cells aligned to G, so that for G = 8 (16-byte cells) or G = 16 (8-byte
 // cells) one window is one 128-byte line read by one coalesced load.  The
 // first window starts at the operation's home cell; lanes before it are
@@ -41,6 +42,7 @@
 #include <stdint.h>
 
 #include "lpht_device.h"
+#include "lpht_lane.h"
 #include "lpht_migrate.h"
 #include "lpht_internal.h"
 
@@ -254,69 +256,6 @@ __device__ __forceinline__ void bulk_round(const BulkArgs &A, const uint32_t (*T
     start();
   };
 
-  // Single-table finds one lane per operation: a lane probes both of its
-  // operations of the round together, so two random loads are in flight per
-  // lane instead of one after the other.
-  constexpr bool kPairFind = OP == OP_FIND && G == 1 && !RESIDENT;
-  const bool pair = kPairFind && shome && !A.kinds;
-  if (pair) {
-    static_assert(ROUND == 128, "two operations per lane");
-    u64 key[2], pos[2], val[2] = {0, 0}, steps[2] = {0, 0};
-    bool act[2];
-    uint8_t fl[2] = {0, 0};
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const uint32_t loc = lane + 64 * q;
-      act[q] = loc < cnt;
-      key[q] = act[q] ? skeys[loc] : 0;
-      pos[q] = act[q] ? shome[loc] : 0;
-      if (act[q] && (key[q] == kEmpty || key[q] == kTomb)) {
-        err |= kErrReserved;
-        fl[q] = 0xFE;
-        act[q] = false;
-      }
-    }
-    while (act[0] || act[1]) {
-      u64 ck[2], cv[2];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        ck[q] = kEmpty;
-        cv[q] = 0;
-        if (act[q]) {
-          if (LAYOUT == 0) {
-            const u64 w = Cells<0>::word<false>(A.cells, pos[q]);
-            ck[q] = Cells<0>::key_of(w);
-            cv[q] = Cells<0>::val_of(w);
-          } else {
-            const u64x2 c = Cells<1>::cell<false>(A.cells, pos[q]);
-            ck[q] = c.x;
-            cv[q] = c.y;
-          }
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        if (!act[q]) continue;
-        if (ck[q] == key[q]) {
-          fl[q] = 1;
-          val[q] = cv[q];
-          act[q] = false;
-        } else if (ck[q] == kEmpty || ++steps[q] > mask) {
-          act[q] = false;  // absent (or every cell probed)
-        } else {
-          pos[q] = (pos[q] + 1) & mask;
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const uint32_t loc = lane + 64 * q;
-      if (loc < cnt) {
-        wflag[loc] = fl[q];
-        wout[loc] = val[q];
-      }
-    }
-  } else {
   start();
   while (__any(active)) {
     if (active) {
@@ -484,7 +423,6 @@ __device__ __forceinline__ void bulk_round(const BulkArgs &A, const uint32_t (*T
         }
       }
     }
-  }
   }
   // write the round's results as whole lines
   wave_sync();
@@ -1622,7 +1560,6 @@ template <int LAYOUT, int OP, int UP>
 static hipError_t launch_mlo(const BulkArgs *d, const u64 *rs, uint32_t nd, u64 total,
                              const LaunchCfg &cfg, hipStream_t s) {
   switch (cfg.group_width) {
-    case 1: return launch_mg<LAYOUT, OP, UP, 1>(d, rs, nd, total, cfg, s);
     case 2: return launch_mg<LAYOUT, OP, UP, 2>(d, rs, nd, total, cfg, s);
     case 4: return launch_mg<LAYOUT, OP, UP, 4>(d, rs, nd, total, cfg, s);
     case 8: return launch_mg<LAYOUT, OP, UP, 8>(d, rs, nd, total, cfg, s);
@@ -1652,6 +1589,7 @@ hipError_t launch_bulk_multi(OpKind op, uint32_t up, uint32_t layout, const Bulk
                              const uint64_t *round_start, uint32_t ndesc, uint64_t total_rounds,
                              const LaunchCfg &cfg, hipStream_t s) {
   if (ndesc == 0 || total_rounds == 0) return hipSuccess;
+  if (cfg.group_width == 1) return launch_lane_multi(op, up, layout, descs, round_start, ndesc, total_rounds, s);
   const u64 *rs = (const u64 *)round_start;
   return layout == 0 ? launch_mlayout<0>(op, up, descs, rs, ndesc, (u64)total_rounds, cfg, s)
                      : launch_mlayout<1>(op, up, descs, rs, ndesc, (u64)total_rounds, cfg, s);
@@ -1660,7 +1598,6 @@ hipError_t launch_bulk_multi(OpKind op, uint32_t up, uint32_t layout, const Bulk
 template <int LAYOUT, int OP, int UP>
 static hipError_t launch_lo(const BulkArgs &a, const LaunchCfg &cfg, hipStream_t s) {
   switch (cfg.group_width) {
-    case 1: return launch_g<LAYOUT, OP, UP, 1>(a, cfg, s);
     case 2: return launch_g<LAYOUT, OP, UP, 2>(a, cfg, s);
     case 4: return launch_g<LAYOUT, OP, UP, 4>(a, cfg, s);
     case 8: return launch_g<LAYOUT, OP, UP, 8>(a, cfg, s);
@@ -1696,6 +1633,7 @@ hipError_t launch_bulk(OpKind op, const BulkArgs &a, const LaunchCfg &cfg, hipSt
       hipLaunchKernelGGL(k_upsert_add_agg<1>, dim3((uint32_t)grid), dim3(AGG_BLOCK), 0, s, a);
     return hipGetLastError();
   }
+  if (cfg.group_width == 1) return launch_lane(op, a, cfg.block_threads, cfg.dense != 0, s);
   return a.layout == 0 ? launch_layout<0>(op, a, cfg, s) : launch_layout<1>(op, a, cfg, s);
 }
 

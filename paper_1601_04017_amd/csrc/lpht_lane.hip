@@ -1,0 +1,331 @@
+// Bulk operations with one lane per operation (group width 1): the default
+// form of every single-table call and of the batch API's multi-table calls.
+//
+// What bounds it: random lines for finds (51 G lines/s measured on this
+// card), random compare-and-swap for insertions (17.9 G/s), launch and memory
+// latency for small calls.  So a lane carries exactly one operation from its
+// key to its result: no staging in LDS, no hash tables to build, no barrier
+// before the first probe, and the hardware's own dispatch of workgroups in
+// place of a persistent grid.  A lane looks at its home cell alone (below
+// fill 1/2 two in three operations end there, and a wavefront's 64 scattered
+// loads cost the address path 64 lines whatever their width), and from then
+// on at W cells an iteration, whose loads are in flight together: the wave
+// waits for its longest probe run, and W divides the number of waits.
+//
+// Measured against the staged form (128-operation rounds per wavefront, LDS
+// hash tables), KV64 finds: 1500 in 2^12 cells 13.5 -> 7.0 us, 300 007 in 2^24
+// 16.5 -> 9.8 us, 2^20 in 2^24 33.3 -> 26.6 us, 10^8 in 2^28 2.95 -> 2.74 ms
+// (the same kernel stopping after one cell: 2.66 ms); inserts: 24.5 -> 9.1 us,
+// 38 -> 25 us, 83 -> 81 us, 6.1 -> 5.8 ms.
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "lpht_device.h"
+#include "lpht_lane.h"
+
+namespace lpht {
+
+namespace {
+
+template <int LAYOUT>
+__device__ __forceinline__ u64 word_in(const void *a, u64 i) {
+  return LAYOUT == 0 ? (u64)((const uint32_t *)a)[i] : ((const u64 *)a)[i];
+}
+
+// What a probe looks at: the whole word (PACKED32) or the key, and for finds
+// the value too (KV64).
+struct Seen {
+  u64 w, v;
+};
+
+template <int LAYOUT, int OP>
+__device__ __forceinline__ Seen look(const void *cells, u64 p) {
+  if (LAYOUT == 0) return {Cells<0>::word(cells, p), 0};
+  if (OP == OP_FIND) {
+    const u64x2 c = Cells<1>::cell(cells, p);
+    return {c.x, c.y};
+  }
+  return {Cells<1>::key(cells, p), 0};
+}
+
+template <int LAYOUT>
+__device__ __forceinline__ u64 seen_key(u64 w) {
+  return LAYOUT == 0 ? (w & 0xFFFFFFFFull) : w;
+}
+
+// value := up(value, d) of the present key in cell p
+template <int LAYOUT, int UP>
+__device__ __forceinline__ void apply_up(void *cells, u64 p, u64 d) {
+  if (LAYOUT == 0) {
+    if (UP == 1)
+      add64((u64 *)cells + p, d << 32);
+    else
+      ((uint32_t *)cells)[2 * p + 1] = (uint32_t)d;
+  } else {
+    u64 *v = (u64 *)cells + 2 * p + 1;
+    if (UP == 1)
+      add64(v, d);
+    else
+      *v = d;
+  }
+}
+
+// Ends the operation at cell p, last seen as `s` (its key is k or empty), or
+// finds that another operation gave the cell to another key: then false, and
+// the probe goes on after p.  A failed compare-and-swap returns the current
+// word, which is looked at in place of the cell (the "revisit" of Algorithm 1).
+template <int LAYOUT, int OP, int UP>
+__device__ __forceinline__ bool settle(void *cells, u64 p, Seen s, u64 k, u64 d, uint8_t &flag, u64 &out) {
+  while (true) {
+    const u64 ck = seen_key<LAYOUT>(s.w);
+    if (ck == k) {
+      if (OP == OP_FIND) {
+        out = LAYOUT == 0 ? Cells<0>::val_of(s.w) : s.v;
+        flag = 1;
+      } else if (OP == OP_INSERT) {
+        flag = 0;
+      } else if (OP == OP_UPSERT || OP == OP_UPDATE) {
+        apply_up<LAYOUT, UP>(cells, p, d);
+        flag = OP == OP_UPDATE ? 1 : 0;
+      } else {
+        // the key becomes the tombstone, the value stays
+        u64 *w = (u64 *)cells + (LAYOUT == 0 ? p : 2 * p);
+        const u64 old = cas64(w, s.w, LAYOUT == 0 ? (s.w & ~0xFFFFFFFFull) | kTomb : kTomb);
+        if (old != s.w) {
+          s.w = old;
+          continue;
+        }
+        flag = 1;
+      }
+      return true;
+    }
+    if (ck != kEmpty) return false;
+    if (OP == OP_FIND || OP == OP_UPDATE || OP == OP_ERASE) {
+      flag = 0;
+      return true;
+    }
+    u64 *w = (u64 *)cells + (LAYOUT == 0 ? p : 2 * p);
+    const u64 old = cas64(w, s.w, LAYOUT == 0 ? (d << 32) | k : k);
+    if (old == s.w) {
+      // KV64: the claimed cell's value, 0 until now; concurrent insert-or-adds
+      // of the same key add to it
+      if (LAYOUT == 1) {
+        if (OP == OP_UPSERT && UP == 1)
+          add64(w + 1, d);
+        else
+          w[1] = d;
+      }
+      flag = 1;
+      return true;
+    }
+    s.w = old;
+  }
+}
+
+// One operation on a non-reserved key.  Returns the flag; finds leave the
+// value in `out`.
+template <int LAYOUT, int OP, int UP, int W>
+__device__ __forceinline__ uint8_t lane_op(const BulkArgs &A, u64 k, u64 d, u64 &out) {
+  const u64 mask = (1ull << A.log2c) - 1;
+  u64 p = hash_direct<LAYOUT>(k, A.crc_hi, A.crc_lo, A.mul) >> (64 - A.log2c);
+  uint8_t flag = 0;
+  Seen s = look<LAYOUT, OP>(A.cells, p);
+  u64 seen = 1;  // cells passed; more than the mask: every cell holds another key
+  bool event = seen_key<LAYOUT>(s.w) == k || seen_key<LAYOUT>(s.w) == kEmpty;
+  while (true) {
+    if (event && settle<LAYOUT, OP, UP>(A.cells, p, s, k, d, flag, out)) return flag;
+    if (seen > mask) break;
+    // the next W cells; the first of them that ends the run is looked at
+    Seen c[W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) c[j] = look<LAYOUT, OP>(A.cells, (p + 1 + j) & mask);
+    event = false;
+    uint32_t at = W - 1;
+    s = c[W - 1];
+#pragma unroll
+    for (int j = W - 1; j >= 0; --j) {
+      const u64 ck = seen_key<LAYOUT>(c[j].w);
+      if (ck == k || ck == kEmpty) {
+        event = true;
+        at = j;
+        s = c[j];
+      }
+    }
+    // a second look at cells already passed (at the end of a full table)
+    // changes nothing: they hold other keys
+    p = (p + 1 + at) & mask;
+    seen += 1 + at;
+  }
+  return OP == OP_INSERT || OP == OP_UPSERT ? 0xFF : 0;
+}
+
+// Adds the wavefront's changes to the counts: insertions (both counts) or
+// erasures (live), one atomic per workgroup and count.
+template <int OP>
+__device__ __forceinline__ void lane_counts(DevStatus *st, uint32_t slot, uint32_t wave_hits, uint32_t *s_hits) {
+  if (OP == OP_FIND || OP == OP_UPDATE) return;
+  const uint32_t wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) s_hits[wave] = wave_hits;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    u64 t = 0;
+    for (uint32_t w = 0; w < (blockDim.x >> 6); ++w) t += s_hits[w];
+    CountSlot *cs = &st->slot[slot % kCountSlots];
+    if (t) {
+      if (OP == OP_ERASE) {
+        add64(&cs->live, 0 - t);
+      } else {
+        add64(&cs->used, t);
+        add64(&cs->live, t);
+      }
+    }
+  }
+}
+
+__device__ __forceinline__ void lane_errors(DevStatus *st, uint32_t err) {
+  const u64 any = __ballot(err != 0);
+  if (any) {
+    const uint32_t e = (__ballot(err & kErrFull) ? kErrFull : 0) | (__ballot(err & kErrReserved) ? kErrReserved : 0);
+    if ((threadIdx.x & 63) == 0) atomicOr(&st->err, e);
+  }
+}
+
+// Operation i of A; returns its flag (0xFD: an operation of another phase).
+template <int LAYOUT, int OP, int UP, int W>
+__device__ __forceinline__ uint8_t lane_at(const BulkArgs &A, u64 i, uint32_t &err) {
+  u64 out = 0;
+  uint8_t flag = 0xFD;
+  if (!A.kinds || A.kinds[i] == A.kind_sel) {
+    const u64 k = word_in<LAYOUT>(A.keys, i);
+    if (k == kEmpty || k == kTomb) {
+      flag = 0xFE;
+      err |= kErrReserved;
+    } else {
+      const u64 d = OP != OP_FIND && OP != OP_ERASE && A.vals ? word_in<LAYOUT>(A.vals, i) : 1;
+      flag = lane_op<LAYOUT, OP, UP, W>(A, k, d, out);
+      if (flag == 0xFF) err |= kErrFull;
+    }
+    if (A.flags) A.flags[i] = flag;
+  }
+  if (OP == OP_FIND && A.vals_out) {
+    if (LAYOUT == 0)
+      ((uint32_t *)A.vals_out)[i] = (uint32_t)out;
+    else
+      ((u64 *)A.vals_out)[i] = out;
+  }
+  return flag;
+}
+
+// Threads per workgroup at most, whatever the tuning asks of the wider group
+// kernels: a workgroup's slots free up only when its longest probe run ends
+// (10^8 finds in 2^28 KV64 cells: 2.74 / 2.99 ms with 64 to 256 threads,
+// 2.84 / 3.18 ms with 512, 2.97 / 3.39 ms with 1024).
+constexpr uint32_t kMostThreads = 256;
+
+// One call on one table.
+template <int LAYOUT, int OP, int UP, int W>
+__global__ void __launch_bounds__(kMostThreads) k_lane(BulkArgs A) {
+  __shared__ uint32_t s_hits[kMostThreads / 64];
+  uint32_t err = 0, hits = 0;
+  const u64 stride = (u64)gridDim.x * blockDim.x;
+  for (u64 base = (u64)blockIdx.x * blockDim.x; base < A.n; base += stride) {
+    const u64 i = base + threadIdx.x;
+    uint8_t flag = 0;
+    if (i < A.n) flag = lane_at<LAYOUT, OP, UP, W>(A, i, err);
+    hits += (uint32_t)__popcll(__ballot(flag == 1));
+  }
+  lane_errors(A.status, err);
+  lane_counts<OP>(A.status, blockIdx.x, hits, s_hits);
+}
+
+// Descriptor j covers rounds [round_start[j], round_start[j + 1]) of kRound
+// operations; a workgroup of kRound threads takes a round.
+template <int LAYOUT, int OP, int UP, int W>
+__global__ void __launch_bounds__(kRound) k_lane_multi(const BulkArgs *descs, const u64 *round_start,
+                                                       uint32_t ndesc) {
+  __shared__ uint32_t s_hits[kRound / 64];
+  const u64 total = round_start[ndesc];
+  for (u64 r = blockIdx.x; r < total; r += gridDim.x) {
+    uint32_t lo = 0, hi = ndesc;  // last j with round_start[j] <= r
+    while (hi - lo > 1) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (round_start[mid] <= r) lo = mid; else hi = mid;
+    }
+    const BulkArgs A = descs[lo];
+    const u64 i = (r - round_start[lo]) * kRound + threadIdx.x;
+    uint32_t err = 0;
+    uint8_t flag = 0;
+    if (i < A.n) flag = lane_at<LAYOUT, OP, UP, W>(A, i, err);
+    const uint32_t hits = (uint32_t)__popcll(__ballot(flag == 1));
+    lane_errors(A.status, err);
+    lane_counts<OP>(A.status, (uint32_t)r, hits, s_hits);
+    __syncthreads();  // s_hits is written again by the next round
+  }
+}
+
+// Workgroups of a launch: HIP bounds the threads of a grid by 2^32.
+constexpr u64 kMaxThreads = 1ull << 31;
+
+// Lookahead: 2 cells up to fill 1/2, 4 above.  KV64, 10^8 finds in 2^28 cells
+// at fill 0.37 (hits / misses): W = 2 2.74 / 3.00 ms, W = 4 2.85 / 3.20 ms
+// (fetched cells that most lanes do not need); 1.6 * 10^6 in 2^21 at fill 0.75:
+// 69.5 / 127.6 us and 56.5 / 92.7 us (long runs, half the waits).
+template <int LAYOUT, int OP, int UP>
+void lane_launch(const BulkArgs &a, uint32_t threads, bool dense, hipStream_t s) {
+  threads = std::min(threads, kMostThreads);
+  const u64 blocks = std::min<u64>((a.n + threads - 1) / threads, kMaxThreads / threads);
+  if (dense)
+    hipLaunchKernelGGL((k_lane<LAYOUT, OP, UP, 4>), dim3((uint32_t)blocks), dim3(threads), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_lane<LAYOUT, OP, UP, 2>), dim3((uint32_t)blocks), dim3(threads), 0, s, a);
+}
+
+// The host does not know every table's fill here: W = 4, which costs small
+// calls nothing.
+template <int LAYOUT, int OP, int UP>
+void lane_launch_multi(const BulkArgs *d, const u64 *rs, uint32_t nd, u64 total, hipStream_t s) {
+  const u64 blocks = std::min<u64>(total, kMaxThreads / kRound);
+  hipLaunchKernelGGL((k_lane_multi<LAYOUT, OP, UP, 4>), dim3((uint32_t)blocks), dim3(kRound), 0, s, d, rs, nd);
+}
+
+}  // namespace
+
+#define LPHT_LANE_OPS(CALL, op, up)                        \
+  switch (op) {                                            \
+    case OP_FIND: CALL(OP_FIND, 0); break;                 \
+    case OP_INSERT: CALL(OP_INSERT, 0); break;             \
+    case OP_UPSERT:                                        \
+      if (up) CALL(OP_UPSERT, 1); else CALL(OP_UPSERT, 0); \
+      break;                                               \
+    case OP_UPDATE:                                        \
+      if (up) CALL(OP_UPDATE, 1); else CALL(OP_UPDATE, 0); \
+      break;                                               \
+    case OP_ERASE: CALL(OP_ERASE, 0); break;               \
+    default: return hipErrorInvalidValue;                  \
+  }
+
+hipError_t launch_lane(OpKind op, const BulkArgs &a, uint32_t threads, bool dense, hipStream_t s) {
+  drop_stale_error();
+#define LPHT_CALL(OP, UP) \
+  (a.layout == 0 ? lane_launch<0, OP, UP>(a, threads, dense, s) : lane_launch<1, OP, UP>(a, threads, dense, s))
+  LPHT_LANE_OPS(LPHT_CALL, op, a.up)
+#undef LPHT_CALL
+  return hipGetLastError();
+}
+
+hipError_t launch_lane_multi(OpKind op, uint32_t up, uint32_t layout, const BulkArgs *descs,
+                             const uint64_t *round_start, uint32_t ndesc, uint64_t total_rounds, hipStream_t s) {
+  drop_stale_error();
+  const u64 *rs = (const u64 *)round_start;
+  const u64 total = (u64)total_rounds;
+#define LPHT_CALL(OP, UP)                                              \
+  (layout == 0 ? lane_launch_multi<0, OP, UP>(descs, rs, ndesc, total, s) \
+               : lane_launch_multi<1, OP, UP>(descs, rs, ndesc, total, s))
+  LPHT_LANE_OPS(LPHT_CALL, op, up)
+#undef LPHT_CALL
+  return hipGetLastError();
+}
+
+}  // namespace lpht
