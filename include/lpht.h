@@ -34,8 +34,8 @@
  *   left for an inserting operation (sticky error LPHT_ERR_FULL).
  * - The table's cells and its status block are owned by the library and
  *   allocated through the configured allocator (default: the library's own
- *   stream-ordered memory pool on the table's device, which keeps freed
- *   memory for reuse until the process ends).
+ *   stream-ordered cache of blocks on the table's device, which keeps freed
+ *   memory for reuse, up to a quarter of the device's).
  */
 #ifndef LPHT_H
 #define LPHT_H
@@ -95,8 +95,8 @@ extern "C" {
 
 /* Allocator hook: returns device memory of `bytes` bytes (256-byte aligned)
  * usable in stream order on `stream`, or NULL.  `free` releases it in stream
- * order.  Both NULL selects the library's pool (hipMallocFromPoolAsync /
- * hipFreeAsync on a per-device pool that never releases memory). */
+ * order.  Both NULL selects the library's pool: blocks kept for reuse in stream
+ * order, up to a quarter of the device's memory, until lpht_release_pools. */
 typedef void *(*lpht_alloc_fn)(size_t bytes, void *stream, void *ctx);
 typedef void (*lpht_free_fn)(void *ptr, size_t bytes, void *stream, void *ctx);
 

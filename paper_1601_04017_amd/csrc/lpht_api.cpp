@@ -7,8 +7,6 @@
 
 #include <algorithm>
 
-#include <atomic>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -52,183 +50,6 @@ int from_hip(hipError_t e) {
 }
 
 uint64_t cell_bytes(uint32_t layout) { return layout == LPHT_PACKED32 ? 8u : 16u; }
-
-// The library's own stream-ordered memory pool per device.  It keeps freed
-// memory mapped (release threshold: never), so that the repeated growth of
-// a table reuses pages instead of mapping new ones; the paper uses a
-// user-space memory pool for the same reason (Sec. 7).
-constexpr int kMaxDevices = 64;
-std::mutex g_pool_mu;
-hipMemPool_t g_pools[kMaxDevices];
-// blocks handed out by pool_alloc and not yet given back to pool_free
-std::atomic<long long> g_pool_blocks{0};
-
-// Frees the pool has not been told of yet.  A block freed on stream s is
-// often still to be read by work queued on s (the old table of a migration
-// just enqueued); handed to another stream's allocation at once, it was seen
-// overwritten before that work ran, although the stream-ordered allocator
-// should have kept it back.  So pool_free records an event on s and returns
-// the block to the pool only once the event has completed; allocations and
-// frees reap the completed ones.
-struct PendingFree {
-  void *p;
-  hipEvent_t ev;
-  int device;
-};
-std::mutex g_pending_mu;
-std::vector<PendingFree> g_pending;
-std::vector<hipEvent_t> g_spare_events;
-// blocks whose event cannot be waited on: returned when the pools are released
-std::vector<PendingFree> g_stuck;
-
-// Returns to the pool every pending block of `device` whose event has
-// completed (all of them, waiting, when `wait`), ordered on stream s.
-void reap_pending(int device, hipStream_t s, bool wait) {
-  std::lock_guard<std::mutex> lk(g_pending_mu);
-  size_t k = 0;
-  for (size_t i = 0; i < g_pending.size(); ++i) {
-    PendingFree &f = g_pending[i];
-    hipError_t q = hipErrorNotReady;
-    if (f.device == device) q = wait ? hipEventSynchronize(f.ev) : hipEventQuery(f.ev);
-    const bool done = q == hipSuccess;
-    if (q != hipSuccess && q != hipErrorNotReady) {
-      // The event cannot be waited on (HIP has reported events recorded into
-      // a stream capture this way): the error is the pool's, not the
-      // caller's, and the block stays out of the pool until the pools are
-      // released after a device synchronisation.
-      (void)hipGetLastError();
-      g_stuck.push_back(f);
-      continue;
-    }
-    if (done) {
-      // a failed free leaves the block to the pool; its error is not the
-      // caller's to read
-      if (hipFreeAsync(f.p, s) != hipSuccess) (void)hipGetLastError();
-      g_spare_events.push_back(f.ev);
-    } else {
-      g_pending[k++] = f;
-    }
-  }
-  g_pending.resize(k);
-}
-
-hipMemPool_t device_pool(int dev) {
-  if (dev < 0 || dev >= kMaxDevices) return nullptr;
-  std::lock_guard<std::mutex> lk(g_pool_mu);
-  if (!g_pools[dev]) {
-    hipMemPoolProps props{};
-    props.allocType = hipMemAllocationTypePinned;
-    props.handleTypes = hipMemHandleTypeNone;
-    props.location.type = hipMemLocationTypeDevice;
-    props.location.id = dev;
-    hipMemPool_t pool = nullptr;
-    if (hipMemPoolCreate(&pool, &props) != hipSuccess) return nullptr;
-    uint64_t keep = ~0ull;
-    (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
-    g_pools[dev] = pool;
-  }
-  return g_pools[dev];
-}
-
-void *pool_alloc(int device, size_t bytes, hipStream_t s) {
-  hipMemPool_t pool = device_pool(device);
-  if (!pool) return nullptr;
-  reap_pending(device, s, false);
-  void *p = nullptr;
-  if (hipMallocFromPoolAsync(&p, bytes, pool, s) != hipSuccess) return nullptr;
-  g_pool_blocks.fetch_add(1);
-  return p;
-}
-
-void pool_free(void *p, hipStream_t s) {
-  if (!p) return;
-  int device = 0;
-  hipEvent_t ev = nullptr;
-  bool queued = false;
-  if (hipGetDevice(&device) == hipSuccess) {
-    {
-      std::lock_guard<std::mutex> lk(g_pending_mu);
-      if (!g_spare_events.empty()) {
-        ev = g_spare_events.back();
-        g_spare_events.pop_back();
-      }
-    }
-    if (ev || hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) {
-      if (hipEventRecord(ev, s) == hipSuccess) {
-        std::lock_guard<std::mutex> lk(g_pending_mu);
-        g_pending.push_back({p, ev, device});
-        queued = true;
-      } else {
-        (void)hipGetLastError();  // handled below: the free waits for the stream instead
-        (void)hipEventDestroy(ev);
-      }
-    }
-  }
-  if (!queued) {
-    // no event: wait for the stream, then free
-    if (hipStreamSynchronize(s) != hipSuccess) (void)hipGetLastError();
-    if (hipFreeAsync(p, s) != hipSuccess) (void)hipGetLastError();
-  }
-  g_pool_blocks.fetch_sub(1);
-  reap_pending(device, s, false);
-}
-
-int release_pools() {
-  std::lock_guard<std::mutex> lk(g_pool_mu);
-  if (g_pool_blocks.load() != 0) return LPHT_ERR_INVALID;
-  int cur = 0;
-  bool have_cur = false;
-  int rc = LPHT_OK;
-  for (int d = 0; d < kMaxDevices; ++d) {
-    if (!g_pools[d]) continue;
-    if (!have_cur) {
-      if (hipGetDevice(&cur) != hipSuccess) return LPHT_ERR_DEVICE;
-      have_cur = true;
-    }
-    // the frees of destroyed tables complete in stream order: wait for them
-    if (hipSetDevice(d) == hipSuccess) {
-      reap_pending(d, nullptr, true);
-      if (hipDeviceSynchronize() == hipSuccess) {
-        std::lock_guard<std::mutex> lk(g_pending_mu);
-        size_t k = 0;
-        for (const PendingFree &f : g_stuck) {
-          if (f.device == d) {
-            if (hipFreeAsync(f.p, nullptr) != hipSuccess) (void)hipGetLastError();
-            if (hipEventDestroy(f.ev) != hipSuccess) (void)hipGetLastError();
-          } else {
-            g_stuck[k++] = f;
-          }
-        }
-        g_stuck.resize(k);
-      }
-    }
-    if (hipSetDevice(d) != hipSuccess || hipDeviceSynchronize() != hipSuccess ||
-        hipMemPoolTrimTo(g_pools[d], 0) != hipSuccess || hipMemPoolDestroy(g_pools[d]) != hipSuccess)
-      rc = LPHT_ERR_DEVICE;
-    g_pools[d] = nullptr;
-  }
-  {
-    std::lock_guard<std::mutex> lk(g_pending_mu);
-    for (hipEvent_t ev : g_spare_events) (void)hipEventDestroy(ev);
-    g_spare_events.clear();
-  }
-  if (have_cur) (void)hipSetDevice(cur);
-  return rc;
-}
-
-void *dev_alloc(lpht_table *t, size_t bytes, hipStream_t s) {
-  if (t->cfg.alloc) return t->cfg.alloc(bytes, (void *)s, t->cfg.alloc_ctx);
-  return pool_alloc(t->device, bytes, s);
-}
-
-void dev_free(lpht_table *t, void *p, size_t bytes, hipStream_t s) {
-  if (!p) return;
-  if (t->cfg.free) {
-    t->cfg.free(p, bytes, (void *)s, t->cfg.alloc_ctx);
-    return;
-  }
-  pool_free(p, s);
-}
 
 void fill_launch(lpht_table *t) {
   t->launch.block_threads = t->tuning.block_threads;

@@ -59,12 +59,15 @@ namespace host {
 
 int from_hip(hipError_t e);
 uint64_t cell_bytes(uint32_t layout);
-// stream-ordered allocation from the library's per-device pool (or the
-// table's allocator hook)
-void *dev_alloc(lpht_table *t, size_t bytes, hipStream_t s);
+// Device memory from the library's cache of blocks (or the table's allocator
+// hook), usable in stream order on s; freed in stream order on s.  in_order
+// false: the first use is not ordered on s (a kernel already running is given
+// the block), so no block is taken whose last use has not completed.
+void *dev_alloc(lpht_table *t, size_t bytes, hipStream_t s, bool in_order = true);
 void dev_free(lpht_table *t, void *p, size_t bytes, hipStream_t s);
-void *pool_alloc(int device, size_t bytes, hipStream_t s);
+void *pool_alloc(int device, size_t bytes, hipStream_t s, bool in_order = true);
 void pool_free(void *p, hipStream_t s);
+int release_pools();
 void fill_launch(lpht_table *t);
 bool tuning_ok(const lpht_tuning *u);
 bool within_fill(const lpht_table *t, uint64_t x, uint64_t c);

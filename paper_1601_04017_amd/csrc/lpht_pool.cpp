@@ -1,0 +1,388 @@
+// The library's device memory: blocks of every table's cells, status and
+// scratch, kept for reuse after they are freed (the paper's user-space memory
+// pool, Sec. 7).
+//
+// Why not the runtime's stream-ordered pool: a block freed by an object of
+// one pass and asked for by the next went through page mapping again, and the
+// next kernel launch waited for it.  Growing a table from 4096 cells with
+// 2 * 10^7 keys took 57 ms a pass of which the kernels are 3.5, an insertion of
+// 10^7 Zipf keys growing inside the kernel 30 ms of 6; with this cache 3.4 and
+// 6.1 ms.
+//
+// Blocks come from hipMalloc in size classes.  A freed block carries an event
+// recorded on the stream it was freed on, since work queued there may still
+// use it (the old table of a migration just enqueued):
+//   - an allocation ordered on the same stream takes it at once, behind a
+//     stream wait on that event (free of charge in stream order, and right
+//     even if the handle has come to name another stream since);
+//   - any other allocation takes it only once the event has completed.
+// What is cached is bounded by a quarter of the device's memory; beyond that,
+// and when an allocation fails, the blocks freed longest ago go back to HIP.
+// All of it goes back in release_pools.
+//
+// While a stream is being captured no block of the cache is handed out, since
+// a replay would use it at any later time: allocations of a capturing stream
+// come from a hipMemPool, and their frees wait for release_pools unless their
+// events can be queried.
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <atomic>
+#include <cstdint>
+#include <mutex>
+#include <new>
+#include <unordered_map>
+#include <vector>
+
+#include "lpht_host.h"
+
+namespace lpht {
+namespace host {
+
+namespace {
+
+constexpr int kMaxDevices = 64;
+
+struct Free {
+  void *p;
+  hipEvent_t ev;      // null: never used since hipMalloc
+  hipStream_t s;      // the stream it was freed on
+  uint64_t seq;       // order of the frees
+};
+
+struct Block {
+  uint32_t cls;       // size class, or kGraphBlock
+  int device;
+  bool slab;          // part of a slab: never given back by itself
+};
+constexpr uint32_t kGraphBlock = ~0u;
+
+struct Device {
+  std::unordered_map<uint32_t, std::vector<Free>> free;  // by class, oldest first
+  std::vector<void *> slabs;
+  uint64_t cached = 0, limit = 0;
+  hipMemPool_t graph_pool = nullptr;
+  // blocks whose event cannot be waited on: given back by release_pools
+  std::vector<Free> stuck;
+};
+
+std::mutex g_mu;
+Device g_dev[kMaxDevices];
+std::unordered_map<void *, Block> g_blocks;  // every block the library holds
+std::vector<hipEvent_t> g_events;            // spare
+uint64_t g_seq = 0;
+// blocks handed out by pool_alloc and not yet given back to pool_free
+std::atomic<long long> g_out{0};
+
+// Classes: powers of two up to 64 KiB, above that eight steps per power of
+// two (at most an eighth is lost).  A class is its size's exponent and eighth.
+constexpr uint32_t kSmallLog2 = 16;
+constexpr size_t kSlabBytes = 1 << 20;
+
+uint32_t class_of(size_t bytes) {
+  uint32_t lg = 9;
+  while (lg < kSmallLog2 && ((size_t)1 << lg) < bytes) ++lg;
+  if (((size_t)1 << lg) >= bytes) return lg << 3;
+  lg = 63 - (uint32_t)__builtin_clzll((unsigned long long)bytes);
+  const uint64_t step = 1ull << (lg - 3);
+  const uint64_t eighths = (bytes - (1ull << lg) + step - 1) / step;  // 0..8
+  return (lg << 3) + (uint32_t)eighths;  // 8 eighths: the next power of two
+}
+
+size_t class_bytes(uint32_t cls) {
+  const uint32_t lg = cls >> 3;
+  return ((size_t)1 << lg) + (size_t)(cls & 7) * (((size_t)1 << lg) >> 3);
+}
+
+// A device selected for the calls that go to the current one.
+struct OnDevice {
+  int before = -1;
+  bool ok;
+  explicit OnDevice(int device) {
+    int cur = -1;
+    ok = hipGetDevice(&cur) == hipSuccess;
+    if (ok && cur != device) {
+      ok = hipSetDevice(device) == hipSuccess;
+      if (ok) before = cur;
+    }
+  }
+  ~OnDevice() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+};
+
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    // the legacy stream while another one is captured: nothing is captured here
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+void spare(hipEvent_t ev) {
+  if (ev) g_events.push_back(ev);
+}
+
+// Takes a free block of the class out of the cache, or null.  `in_order`: the
+// block's first use is ordered on s, so one freed on s needs no completion.
+void *take(Device &D, uint32_t cls, hipStream_t s, bool in_order) {
+  auto it = D.free.find(cls);
+  if (it == D.free.end()) return nullptr;
+  std::vector<Free> &v = it->second;
+  for (int pass = 0; pass < 2; ++pass) {
+    for (size_t k = v.size(); k-- > 0;) {
+      Free f = v[k];
+      const bool same = in_order && f.ev && f.s == s;
+      // first pass: blocks that need no query, the last freed first
+      if (pass == 0 ? !(same || !f.ev) : (same || !f.ev)) continue;
+      hipError_t e = hipSuccess;
+      if (f.ev) e = same ? hipStreamWaitEvent(s, f.ev, 0) : hipEventQuery(f.ev);
+      if (e == hipErrorNotReady) {
+        (void)hipGetLastError();
+        continue;
+      }
+      v.erase(v.begin() + (long)k);
+      if (e != hipSuccess) {
+        // an event that cannot be waited on (HIP has reported events recorded
+        // into a capture this way): the error is the pool's, not the caller's
+        (void)hipGetLastError();
+        D.stuck.push_back(f);
+        D.cached -= class_bytes(cls);
+        continue;
+      }
+      D.cached -= class_bytes(cls);
+      spare(f.ev);
+      return f.p;
+    }
+  }
+  return nullptr;
+}
+
+// Gives cached blocks back to HIP, the one freed longest ago first, until
+// `keep` bytes are left.  `wait`: those still in use are waited for.
+void trim(Device &D, uint64_t keep, bool wait) {
+  struct Ref {
+    uint64_t seq;
+    uint32_t cls;
+  };
+  std::vector<Ref> order;
+  for (auto &kv : D.free)
+    for (const Free &f : kv.second) {
+      const auto b = g_blocks.find(f.p);
+      if (b != g_blocks.end() && !b->second.slab) order.push_back({f.seq, kv.first});
+    }
+  std::sort(order.begin(), order.end(), [](const Ref &a, const Ref &b) { return a.seq < b.seq; });
+  for (const Ref &r : order) {
+    if (D.cached <= keep) break;
+    std::vector<Free> &v = D.free[r.cls];
+    for (size_t k = 0; k < v.size(); ++k) {
+      if (v[k].seq != r.seq) continue;
+      const Free f = v[k];
+      if (f.ev) {
+        const hipError_t e = wait ? hipEventSynchronize(f.ev) : hipEventQuery(f.ev);
+        if (e != hipSuccess) {
+          (void)hipGetLastError();
+          break;
+        }
+      }
+      if (hipFree(f.p) != hipSuccess) (void)hipGetLastError();
+      g_blocks.erase(f.p);
+      spare(f.ev);
+      D.cached -= class_bytes(r.cls);
+      v.erase(v.begin() + (long)k);
+      break;
+    }
+  }
+}
+
+hipMemPool_t graph_pool(int dev) {
+  Device &D = g_dev[dev];
+  if (!D.graph_pool) {
+    hipMemPoolProps props{};
+    props.allocType = hipMemAllocationTypePinned;
+    props.handleTypes = hipMemHandleTypeNone;
+    props.location.type = hipMemLocationTypeDevice;
+    props.location.id = dev;
+    hipMemPool_t pool = nullptr;
+    if (hipMemPoolCreate(&pool, &props) != hipSuccess) return nullptr;
+    uint64_t keep = ~0ull;
+    (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
+    D.graph_pool = pool;
+  }
+  return D.graph_pool;
+}
+
+void *graph_alloc(int device, size_t bytes, hipStream_t s) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  hipMemPool_t pool = graph_pool(device);
+  void *p = nullptr;
+  if (!pool || hipMallocFromPoolAsync(&p, bytes, pool, s) != hipSuccess) return nullptr;
+  g_blocks[p] = {kGraphBlock, device, true};
+  return p;
+}
+
+// A new block (with the lock held by `lk`, given up around hipMalloc).
+void *fresh(int device, uint32_t cls, std::unique_lock<std::mutex> &lk) {
+  Device &D = g_dev[device];
+  const size_t cb = class_bytes(cls);
+  const bool slab = cb <= ((size_t)1 << kSmallLog2);
+  const size_t nb = slab ? kSlabBytes : cb;
+  void *p = nullptr;
+  lk.unlock();
+  hipError_t e = hipMalloc(&p, nb);
+  lk.lock();
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    trim(D, 0, true);
+    if ((e = hipMalloc(&p, nb)) != hipSuccess) return nullptr;
+  }
+  if (!slab) {
+    g_blocks[p] = {cls, device, false};
+    return p;
+  }
+  // small classes are cut from slabs: one hipMalloc for many status blocks
+  D.slabs.push_back(p);
+  for (size_t at = 0; at + cb <= nb; at += cb) {
+    void *q = (unsigned char *)p + at;
+    g_blocks[q] = {cls, device, true};
+    if (at) {
+      D.free[cls].push_back({q, nullptr, nullptr, ++g_seq});
+      D.cached += cb;
+    }
+  }
+  return p;
+}
+
+}  // namespace
+
+void *pool_alloc(int device, size_t bytes, hipStream_t s, bool in_order) try {
+  if (device < 0 || device >= kMaxDevices) return nullptr;
+  OnDevice on(device);
+  if (!on.ok) return nullptr;
+  void *p = nullptr;
+  if (capturing(s)) {
+    p = graph_alloc(device, bytes, s);
+  } else {
+    const uint32_t cls = class_of(bytes);
+    std::unique_lock<std::mutex> lk(g_mu);
+    p = take(g_dev[device], cls, s, in_order);
+    if (!p) p = fresh(device, cls, lk);
+  }
+  if (p) g_out.fetch_add(1);
+  return p;
+} catch (const std::bad_alloc &) {
+  return nullptr;  // host memory for the bookkeeping
+}
+
+void pool_free(void *p, hipStream_t s) try {
+  if (!p) return;
+  std::lock_guard<std::mutex> lk(g_mu);
+  const auto it = g_blocks.find(p);
+  if (it == g_blocks.end()) return;  // not of this pool
+  const Block b = it->second;
+  Device &D = g_dev[b.device];
+  OnDevice on(b.device);
+  g_out.fetch_sub(1);
+  hipEvent_t ev = nullptr;
+  if (!g_events.empty()) {
+    ev = g_events.back();
+    g_events.pop_back();
+  } else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
+    ev = nullptr;
+  }
+  const bool captured = capturing(s);
+  if (ev && hipEventRecord(ev, s) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipEventDestroy(ev);
+    ev = nullptr;
+  }
+  if (captured || (!ev && hipStreamSynchronize(s) != hipSuccess)) {
+    // freed inside a capture, or nothing to wait for: out of use until the
+    // pools are released after a device synchronisation
+    (void)hipGetLastError();
+    D.stuck.push_back({p, ev, s, ++g_seq});
+    return;
+  }
+  if (b.cls == kGraphBlock) {
+    // freed outside the capture it was allocated in
+    D.stuck.push_back({p, ev, s, ++g_seq});
+    return;
+  }
+  D.free[b.cls].push_back({p, ev, s, ++g_seq});
+  D.cached += class_bytes(b.cls);
+  if (!D.limit) {
+    size_t total = 0;
+    if (hipDeviceTotalMem(&total, b.device) != hipSuccess) (void)hipGetLastError();
+    D.limit = std::max<uint64_t>(1ull << 30, total / 4);
+  }
+  if (D.cached > D.limit) trim(D, D.limit, false);
+} catch (const std::bad_alloc &) {
+  // no host memory for the bookkeeping: the block is lost to the process
+}
+
+int release_pools() try {
+  std::lock_guard<std::mutex> lk(g_mu);
+  if (g_out.load() != 0) return LPHT_ERR_INVALID;
+  int rc = LPHT_OK;
+  for (int d = 0; d < kMaxDevices; ++d) {
+    Device &D = g_dev[d];
+    bool any = D.graph_pool || !D.slabs.empty() || !D.stuck.empty();
+    for (const auto &kv : D.free) any = any || !kv.second.empty();
+    if (!any) continue;
+    OnDevice on(d);
+    if (!on.ok || hipDeviceSynchronize() != hipSuccess) {
+      rc = LPHT_ERR_DEVICE;
+      continue;
+    }
+    std::vector<Free> all = std::move(D.stuck);
+    D.stuck.clear();
+    for (auto &kv : D.free) all.insert(all.end(), kv.second.begin(), kv.second.end());
+    D.free.clear();
+    for (const Free &f : all) {
+      const Block b = g_blocks[f.p];
+      if (b.cls == kGraphBlock) {
+        if (hipFreeAsync(f.p, nullptr) != hipSuccess) (void)hipGetLastError();
+      } else if (!b.slab && hipFree(f.p) != hipSuccess) {
+        rc = LPHT_ERR_DEVICE;
+      }
+      g_blocks.erase(f.p);
+      if (f.ev && hipEventDestroy(f.ev) != hipSuccess) (void)hipGetLastError();
+    }
+    for (void *p : D.slabs)
+      if (hipFree(p) != hipSuccess) rc = LPHT_ERR_DEVICE;
+    D.slabs.clear();
+    D.cached = 0;
+    if (D.graph_pool) {
+      if (hipDeviceSynchronize() != hipSuccess || hipMemPoolTrimTo(D.graph_pool, 0) != hipSuccess ||
+          hipMemPoolDestroy(D.graph_pool) != hipSuccess)
+        rc = LPHT_ERR_DEVICE;
+      D.graph_pool = nullptr;
+    }
+  }
+  for (hipEvent_t ev : g_events) (void)hipEventDestroy(ev);
+  g_events.clear();
+  return rc;
+} catch (const std::bad_alloc &) {
+  return LPHT_ERR_OOM;
+}
+
+void *dev_alloc(lpht_table *t, size_t bytes, hipStream_t s, bool in_order) {
+  if (t->cfg.alloc) return t->cfg.alloc(bytes, (void *)s, t->cfg.alloc_ctx);
+  return pool_alloc(t->device, bytes, s, in_order);
+}
+
+void dev_free(lpht_table *t, void *p, size_t bytes, hipStream_t s) {
+  if (!p) return;
+  if (t->cfg.free) {
+    t->cfg.free(p, bytes, (void *)s, t->cfg.alloc_ctx);
+    return;
+  }
+  pool_free(p, s);
+}
+
+}  // namespace host
+}  // namespace lpht

@@ -487,7 +487,8 @@ constexpr uint32_t kPersistMigMinLog2 = 10;
 bool persist_post_migration(lpht_server *S, uint32_t ti, Req *q) {
   lpht_table *t = S->tables[ti];
   const size_t nb = (size_t)cell_bytes(t->cfg.layout) << (t->log2c + 1);
-  void *nc = dev_alloc(t, nb, S->streams[0]);
+  // the kernel that will use the cells is already running
+  void *nc = dev_alloc(t, nb, S->streams[0], false);
   if (!nc) return false;
   Req *m = new (std::nothrow) Req();
   if (!m) {
