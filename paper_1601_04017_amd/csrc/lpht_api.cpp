@@ -13,6 +13,7 @@
 #include "lpht_host.h"
 #include "lpht_async.h"
 #include "lpht_bulk.h"
+#include "lpht_lane.h"
 #include "lpht_part.h"
 #include "lpht_shrink.h"
 #include "lpht_special.h"
@@ -397,10 +398,12 @@ void batch_free(lpht_batch *b) {
   delete b;
 }
 
-// Uploads one group's descriptors and round offsets through a ring slot and
-// launches it.
+// Launches one group: few descriptors of width 1 as kernel arguments,
+// otherwise through a ring slot that uploads them with their round offsets
+// (a copy of 4 us in front of every group's kernel).
 int batch_launch(lpht_batch *b, OpKind op, uint32_t up, uint32_t layout, const BulkArgs *args,
                  uint32_t nd, const LaunchCfg &cfg, hipStream_t s) {
+  if (cfg.group_width == 1 && nd <= kLaneDescs) return from_hip(launch_lane_few(op, up, layout, args, nd, s));
   const int slot = b->next;
   b->next = (b->next + 1) % lpht_batch::kSlots;
   if (b->used[slot] && hipEventSynchronize(b->ev[slot]) != hipSuccess) return LPHT_ERR_DEVICE;

@@ -14,6 +14,14 @@ namespace lpht {
 // half full.
 hipError_t launch_lane(OpKind op, const BulkArgs &a, uint32_t threads, bool dense, hipStream_t s);
 
+// Descriptors of a multi-table launch that fit its kernel arguments.
+constexpr uint32_t kLaneDescs = 28;
+
+// As launch_lane_multi, from up to kLaneDescs descriptors in host memory: they
+// travel as kernel arguments, so nothing has to be uploaded before the launch.
+hipError_t launch_lane_few(OpKind op, uint32_t up, uint32_t layout, const BulkArgs *descs, uint32_t ndesc,
+                           hipStream_t s);
+
 // As launch_bulk_multi, with group width 1.
 hipError_t launch_lane_multi(OpKind op, uint32_t up, uint32_t layout, const BulkArgs *descs,
                              const uint64_t *round_start, uint32_t ndesc, uint64_t total_rounds, hipStream_t s);

@@ -240,6 +240,18 @@ __global__ void __launch_bounds__(kMostThreads) k_lane(BulkArgs A) {
   lane_counts<OP>(A.status, blockIdx.x, hits, s_hits);
 }
 
+// One round of kRound operations by a workgroup of kRound threads.
+template <int LAYOUT, int OP, int UP, int W>
+__device__ __forceinline__ void lane_round(const BulkArgs &A, u64 round, uint32_t slot, uint32_t *s_hits) {
+  const u64 i = round * kRound + threadIdx.x;
+  uint32_t err = 0;
+  uint8_t flag = 0;
+  if (i < A.n) flag = lane_at<LAYOUT, OP, UP, W>(A, i, err);
+  const uint32_t hits = (uint32_t)__popcll(__ballot(flag == 1));
+  lane_errors(A.status, err);
+  lane_counts<OP>(A.status, slot, hits, s_hits);
+}
+
 // Descriptor j covers rounds [round_start[j], round_start[j + 1]) of kRound
 // operations; a workgroup of kRound threads takes a round.
 template <int LAYOUT, int OP, int UP, int W>
@@ -254,14 +266,57 @@ __global__ void __launch_bounds__(kRound) k_lane_multi(const BulkArgs *descs, co
       if (round_start[mid] <= r) lo = mid; else hi = mid;
     }
     const BulkArgs A = descs[lo];
-    const u64 i = (r - round_start[lo]) * kRound + threadIdx.x;
-    uint32_t err = 0;
-    uint8_t flag = 0;
-    if (i < A.n) flag = lane_at<LAYOUT, OP, UP, W>(A, i, err);
-    const uint32_t hits = (uint32_t)__popcll(__ballot(flag == 1));
-    lane_errors(A.status, err);
-    lane_counts<OP>(A.status, (uint32_t)r, hits, s_hits);
+    lane_round<LAYOUT, OP, UP, W>(A, r - round_start[lo], (uint32_t)r, s_hits);
     __syncthreads();  // s_hits is written again by the next round
+  }
+}
+
+// The same from kernel arguments: few descriptors, each of its first round's
+// number and the fields a lane needs.
+struct LaneDesc {
+  void *cells;
+  DevStatus *status;
+  const void *keys, *vals;
+  void *vals_out;
+  uint8_t *flags;
+  const uint8_t *kinds;
+  u64 n, mul;
+  u64 first;
+  uint32_t log2c, crc_hi, crc_lo, kind_sel;
+};
+struct LaneFew {
+  LaneDesc d[kLaneDescs];
+  u64 rounds;
+  uint32_t n, pad;
+};
+static_assert(sizeof(LaneFew) <= 4096, "kernel arguments");
+
+template <int LAYOUT, int OP, int UP, int W>
+__global__ void __launch_bounds__(kRound) k_lane_few(LaneFew F) {
+  __shared__ uint32_t s_hits[kRound / 64];
+  for (u64 r = blockIdx.x; r < F.rounds; r += gridDim.x) {
+    uint32_t lo = 0, hi = F.n;
+    while (hi - lo > 1) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (F.d[mid].first <= r) lo = mid; else hi = mid;
+    }
+    const LaneDesc &D = F.d[lo];
+    BulkArgs A{};
+    A.cells = D.cells;
+    A.log2c = D.log2c;
+    A.crc_hi = D.crc_hi;
+    A.crc_lo = D.crc_lo;
+    A.status = D.status;
+    A.keys = D.keys;
+    A.vals = D.vals;
+    A.n = D.n;
+    A.vals_out = D.vals_out;
+    A.flags = D.flags;
+    A.kinds = D.kinds;
+    A.kind_sel = D.kind_sel;
+    A.mul = D.mul;
+    lane_round<LAYOUT, OP, UP, W>(A, r - D.first, (uint32_t)r, s_hits);
+    __syncthreads();
   }
 }
 
@@ -290,6 +345,12 @@ void lane_launch_multi(const BulkArgs *d, const u64 *rs, uint32_t nd, u64 total,
   hipLaunchKernelGGL((k_lane_multi<LAYOUT, OP, UP, 4>), dim3((uint32_t)blocks), dim3(kRound), 0, s, d, rs, nd);
 }
 
+template <int LAYOUT, int OP, int UP>
+void lane_launch_few(const LaneFew &f, hipStream_t s) {
+  const u64 blocks = std::min<u64>(f.rounds, kMaxThreads / kRound);
+  hipLaunchKernelGGL((k_lane_few<LAYOUT, OP, UP, 4>), dim3((uint32_t)blocks), dim3(kRound), 0, s, f);
+}
+
 }  // namespace
 
 #define LPHT_LANE_OPS(CALL, op, up)                        \
@@ -311,6 +372,25 @@ hipError_t launch_lane(OpKind op, const BulkArgs &a, uint32_t threads, bool dens
 #define LPHT_CALL(OP, UP) \
   (a.layout == 0 ? lane_launch<0, OP, UP>(a, threads, dense, s) : lane_launch<1, OP, UP>(a, threads, dense, s))
   LPHT_LANE_OPS(LPHT_CALL, op, a.up)
+#undef LPHT_CALL
+  return hipGetLastError();
+}
+
+hipError_t launch_lane_few(OpKind op, uint32_t up, uint32_t layout, const BulkArgs *descs, uint32_t ndesc,
+                           hipStream_t s) {
+  drop_stale_error();
+  if (ndesc > kLaneDescs) return hipErrorInvalidValue;
+  LaneFew f{};
+  for (uint32_t j = 0; j < ndesc; ++j) {
+    const BulkArgs &a = descs[j];
+    f.d[j] = {a.cells, a.status, a.keys,   a.vals,  a.vals_out, a.flags,  a.kinds,
+              a.n,     a.mul,    f.rounds, a.log2c, a.crc_hi,   a.crc_lo, a.kind_sel};
+    f.rounds += (a.n + kRound - 1) / kRound;
+  }
+  f.n = ndesc;
+  if (f.rounds == 0) return hipSuccess;
+#define LPHT_CALL(OP, UP) (layout == 0 ? lane_launch_few<0, OP, UP>(f, s) : lane_launch_few<1, OP, UP>(f, s))
+  LPHT_LANE_OPS(LPHT_CALL, op, up)
 #undef LPHT_CALL
   return hipGetLastError();
 }

@@ -5,7 +5,8 @@
 // (request slots, one request per table at a time in submission order, HBM
 // budget), launches them (as one multi-table wave per admission round, or one
 // request at a time), and retires launch groups whose completion event has
-// fired.  After each group a one-wave kernel writes every touched table's
+// fired.  A group's requests are copied in by one kernel and out by another
+// (pageable arrays by HIP's copies), which also writes every touched table's
 // exact counts into pinned host memory, so the growth rule that runs before
 // the next request on that table decides on exact counts with no stream
 // synchronisation.
@@ -25,6 +26,7 @@
 #include <vector>
 
 #include "lpht_host.h"
+#include "lpht_serve.h"
 
 using namespace lpht;
 using namespace lpht::host;
@@ -40,8 +42,9 @@ double now_us() {
 size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // True when the first and the last byte of [p, p + bytes) lie in pinned host
-// memory or in device memory (memory a kernel can address).
-bool gpu_accessible(const void *p, size_t bytes) {
+// memory or in device memory (memory a kernel can address); `at_p`: and the
+// device's address of it is p.
+bool gpu_accessible(const void *p, size_t bytes, bool at_p = false) {
   for (const void *x : {p, (const void *)((const char *)p + bytes - 1)}) {
     hipPointerAttribute_t at{};
     if (hipPointerGetAttributes(&at, x) != hipSuccess) {
@@ -49,8 +52,18 @@ bool gpu_accessible(const void *p, size_t bytes) {
       return false;
     }
     if (at.type != hipMemoryTypeHost && at.type != hipMemoryTypeDevice) return false;
+    if (at_p && at.devicePointer != x) return false;
   }
   return true;
+}
+
+// One array of a request, in or out: by the group's copy kernel where the
+// device can address it, else by a copy of its own.
+void stage(std::vector<ServeSeg> &segs, void *dst, const void *src, uint64_t bytes, bool in, hipStream_t s) {
+  if (gpu_accessible(in ? src : dst, bytes, true))
+    segs.push_back({dst, src, bytes, in ? 1u : 0u, 0});
+  else
+    (void)hipMemcpyAsync(dst, src, bytes, in ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost, s);
 }
 
 struct Req {
@@ -82,11 +95,10 @@ struct lpht_server {
   int device = 0;
   uint32_t kb = 8;
   std::vector<lpht_table *> tables;
-  // count readback areas, one per stream (a stream's groups copy its whole
-  // area; a table's entry is only read back after the group that wrote it):
+  // count areas, one per stream, written by the groups' copy kernels (a
+  // table's entry is read after the group that wrote it has completed):
   // [stream][table][used, live, err, pad]
   uint64_t *totals = nullptr;    // pinned
-  uint64_t *d_totals = nullptr;  // device, written by the count kernel
   std::vector<uint8_t> busy;
   std::vector<std::deque<Req *>> fifo;
   std::deque<Req *> incoming;
@@ -233,6 +245,8 @@ void launch_group(lpht_server *S, std::vector<Req *> &group) {
   g.ev = get_event(S);
   std::vector<lpht_batch_op> ops;
   ops.reserve(3 * group.size());
+  std::vector<ServeSeg> segs;
+  segs.reserve(2 * group.size());
   const double t_admit = now_us();
   for (Req *q : group) {
     q->c.admit_us = t_admit;
@@ -246,8 +260,8 @@ void launch_group(lpht_server *S, std::vector<Req *> &group) {
     lpht_table *t = S->tables[q->r.table];
     g.tables.push_back(q->r.table);
     g.reqs.push_back(q);
-    (void)hipMemcpyAsync(dkeys, q->r.keys, n * S->kb, hipMemcpyHostToDevice, s);
-    (void)hipMemcpyAsync(dkinds, q->r.kinds, n, hipMemcpyHostToDevice, s);
+    stage(segs, dkeys, q->r.keys, n * S->kb, true, s);
+    stage(segs, dkinds, q->r.kinds, n, true, s);
     const uint32_t kind_op[3] = {LPHT_OP_FIND, LPHT_OP_UPSERT, LPHT_OP_ERASE};
     for (uint32_t k = 0; k < 3; ++k) {
       if (q->count[k] == 0) continue;
@@ -266,6 +280,8 @@ void launch_group(lpht_server *S, std::vector<Req *> &group) {
       ops.push_back(o);
     }
   }
+  if (launch_serve_copy(segs, {}, s) != hipSuccess)
+    for (Req *q : group) q->c.status = LPHT_ERR_DEVICE;
   std::vector<uint64_t> before(group.size());
   for (size_t i = 0; i < group.size(); ++i) before[i] = table_bytes_of(S->tables[group[i]->r.table]);
   if (!ops.empty()) {
@@ -277,21 +293,19 @@ void launch_group(lpht_server *S, std::vector<Req *> &group) {
   }
   for (size_t i = 0; i < group.size(); ++i) growth_done(S, group[i], before[i]);
   const size_t area = 4 * S->tables.size();
-  for (uint32_t ti : g.tables)
-    (void)launch_count_totals(S->tables[ti]->status, S->d_totals + si * area + 4 * ti, s);
-  (void)hipMemcpyAsync(S->totals + si * area, S->d_totals + si * area, sizeof(uint64_t) * area,
-                       hipMemcpyDeviceToHost, s);
+  std::vector<ServeCount> counts;
+  counts.reserve(g.tables.size());
+  for (uint32_t ti : g.tables) counts.push_back({S->tables[ti]->status, S->totals + si * area + 4 * ti});
   g.stream = si;
+  segs.clear();
   for (Req *q : group) {
     const size_t n = q->r.n;
     unsigned char *base = S->arena + q->arena_off;
-    if (q->r.vals_out && q->count[0])
-      (void)hipMemcpyAsync(q->r.vals_out, base + round256(n * S->kb), n * S->kb,
-                           hipMemcpyDeviceToHost, s);
-    if (q->r.flags)
-      (void)hipMemcpyAsync(q->r.flags, base + 2 * round256(n * S->kb) + round256(n), n,
-                           hipMemcpyDeviceToHost, s);
+    if (q->r.vals_out && q->count[0]) stage(segs, q->r.vals_out, base + round256(n * S->kb), n * S->kb, false, s);
+    if (q->r.flags) stage(segs, q->r.flags, base + 2 * round256(n * S->kb) + round256(n), n, false, s);
   }
+  if (launch_serve_copy(segs, counts, s) != hipSuccess)
+    for (Req *q : group) q->c.status = LPHT_ERR_DEVICE;
   (void)hipEventRecord(g.ev, s);
   if (S->inflight.empty()) S->busy_since = now_us();
   S->inflight_reqs += (uint32_t)group.size();
@@ -763,7 +777,6 @@ void destroy_all(lpht_server *S) {
   }
   for (auto e : S->spare_events) (void)hipEventDestroy(e);
   if (S->totals) (void)hipHostFree(S->totals);
-  if (S->d_totals) (void)hipFree(S->d_totals);
   if (S->pctl) (void)hipHostFree(S->pctl);
   if (S->pring) (void)hipHostFree(S->pring);
   if (S->pdone) (void)hipHostFree(S->pdone);
@@ -820,11 +833,6 @@ int lpht_server_create(const lpht_server_config *cfg, lpht_server **out) {
     return LPHT_ERR_OOM;
   }
   std::memset(S->totals, 0, tot_bytes);
-  if (hipMalloc((void **)&S->d_totals, tot_bytes) != hipSuccess ||
-      hipMemset(S->d_totals, 0, tot_bytes) != hipSuccess) {
-    destroy_all(S);
-    return LPHT_ERR_OOM;
-  }
   for (uint32_t i = 0; i < cfg->ntables; ++i) {
     lpht_config tc;
     lpht_config_default(&tc);
@@ -913,15 +921,21 @@ int lpht_server_submit(lpht_server *S, const lpht_request *req, uint64_t *ticket
   Req *q = new (std::nothrow) Req();
   if (!q) return LPHT_ERR_OOM;
   q->r = *req;
-  q->count[0] = q->count[1] = q->count[2] = 0;
+  // (three independent sums of comparisons vectorise; a counter per kind
+  // took two nanoseconds per operation)
+  uint32_t n0 = 0, n1 = 0, n2 = 0;
   for (uint64_t i = 0; i < req->n; ++i) {
-    const uint8_t k = req->kinds[i];
-    if (k > 2) {
-      delete q;
-      return LPHT_ERR_INVALID;
-    }
-    q->count[k]++;
+    n0 += req->kinds[i] == 0;
+    n1 += req->kinds[i] == 1;
+    n2 += req->kinds[i] == 2;
   }
+  if ((uint64_t)n0 + n1 + n2 != req->n) {
+    delete q;
+    return LPHT_ERR_INVALID;
+  }
+  q->count[0] = n0;
+  q->count[1] = n1;
+  q->count[2] = n2;
   q->c = lpht_completion{};
   q->c.submit_us = now_us();
   {
