@@ -793,27 +793,10 @@ __global__ void __launch_bounds__(256) k_migrate_simple(const void *old_cells, u
 }
 
 // LDS-staged block migration with owner writes (Sec. 5.3.1), one wavefront
-// per block.  Wavefront w owns old block [d, d+B) and writes new cells
-// [g*d, g*(d+B)) exactly once, empty cells included, so the new table needs no
-// separate initialisation.  By Lemma 1 only clusters that overlap the block
-// send elements into that range: the one that may start before d (up to
-// MIG_HALO cells back) and the ones starting inside the block (the last may
-// run up to MIG_HALO cells past it).  The wavefront
-//   - loads the window of old cells [d - H, d + B + H) (Q cells per lane,
-//     lane-consecutive, all loads in flight together) into its LDS region,
-//     hashing every live key on the way (all lanes at once) to its new home;
-//   - finds the empty cells with ballots, hence the window range [lo, hi) of
-//     the clusters that overlap the block and their starts;
-//   - re-inserts each such cluster in old-array order (one lane per cluster;
-//     Lemma 1 makes their target ranges disjoint) into an image of the new
-//     range that holds 16-bit indices into the window;
-//   - streams the owned part of the image out as whole cells.
-// Elements of the last cluster that land past the owned range are written by
-// the next block's wavefront, which sees that cluster as its incoming one; the
-// first block's incoming cluster is the one that wraps around the table end.
-// Positions are kept unwrapped (old cell x may be negative for block 0).  A
-// cluster longer than the halo (or a table without empty cells) sets the
-// overflow flag; the guarded simple migration then redoes the whole move.
+// per block (mig_block in lpht_migrate.h): wavefront w owns old block [d, d+B)
+// and writes new cells [g*d, g*(d+B)) exactly once, empty cells included, so
+// the new table needs no separate initialisation.  On overflow the guarded
+// simple migration redoes the whole move.
 // Q = window cells per lane; the block is B = 64 Q - 2 MIG_HALO old cells.
 // A workgroup is 1..4 wavefronts, each with its own LDS region.
 template <int LAYOUT, int Q>
@@ -1701,8 +1684,7 @@ hipError_t launch_migrate(const void *old_cells, uint32_t log2_old, void *new_ce
   const size_t per_wave = g <= 1 ? mig_wave_lds(mb, layout, 1u << g) : ~(size_t)0 / 8;
   const size_t fixed = 8192 + 64;
   // wavefronts per workgroup (up to 4, within the 64 KiB a workgroup may
-  // allocate) that put the most wavefronts on a compute unit's 160 KiB: the
-  // migration is bound by the latency of each block's cluster walk
+  // allocate) that put the most wavefronts on a compute unit's 160 KiB
   uint32_t wpb = 0;
   {
     size_t best = 0;
@@ -1717,7 +1699,9 @@ hipError_t launch_migrate(const void *old_cells, uint32_t log2_old, void *new_ce
   }
   const bool lds_path = !old_is_full && g <= 1 && (mb == 256 || mb == 512 || mb == 1024) && cap >= mb &&
                         wpb >= 1;
-  const uint32_t sgrid = grid_for(cap, LaunchCfg{256, 1, cfg.blocks_per_cu, cfg.num_cus, mb, 0});
+  uint32_t sgrid = grid_for(cap, LaunchCfg{256, 1, cfg.blocks_per_cu, cfg.num_cus, mb, 0, 0});
+  // as a fallback it nearly always only reads the flag: a small grid then
+  if (lds_path) sgrid = std::min(2 * cfg.num_cus, sgrid);
   if (lds_path) {
     const size_t lds = wpb * per_wave;
     const u64 nwaves = cap / mb;
@@ -1740,8 +1724,8 @@ hipError_t launch_migrate(const void *old_cells, uint32_t log2_old, void *new_ce
     if (e != hipSuccess) return e;
     // fallback, a no-op unless a wavefront reported overflow
     const u64 n16 = new_bytes / 16;
-    hipLaunchKernelGGL(k_fill_zero_if, dim3(grid_for(n16, cfg)), dim3(cfg.block_threads), 0, s,
-                       (u64x2 *)new_cells, n16, st);
+    hipLaunchKernelGGL(k_fill_zero_if, dim3(std::min(2 * cfg.num_cus, grid_for(n16, cfg))), dim3(cfg.block_threads),
+                       0, s, (u64x2 *)new_cells, n16, st);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   } else {

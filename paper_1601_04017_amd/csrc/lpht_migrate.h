@@ -7,18 +7,11 @@
 // (g = gamma, 1 or 2).  It loads the window [d - H, d + B + H) of old cells
 // (H = MIG_HALO) lane-consecutively into registers (the caller prefetches the
 // next block's window before working on the current one) and then
-//   - stores each window cell's key and value and the image slot of its new
-//     home (or empty / tombstone) in LDS;
+//   - stores the window's cells in LDS;
 //   - finds the empty cells with ballots, hence the window range [lo, hi) of
-//     the clusters that overlap the block and their starts;
-//   - re-inserts each such cluster in old-array order (one lane per cluster;
-//     Lemma 1 makes their target ranges disjoint) into an image of the new
-//     range that holds 16-bit indices into the window.  The target range of
-//     a cluster starting at window cell s begins at image slot g s, and the
-//     lane keeps the first 64 of its cells in a register mask, so the first
-//     free cell from an element's home is found with one bit scan; only
-//     beyond those 64 cells does it probe the image in LDS.  The cells'
-//     states are loaded four at a time, ahead of their placement;
+//     the clusters that overlap the block, and hashes the keys in it;
+//   - places all their elements at once into an image of the new range that
+//     holds indices into the window (below);
 //   - streams the owned part of the image out as whole cells.
 // Elements of the last cluster that land past the owned range are written by
 // the next block's wavefront, which sees that cluster as its incoming one; the
@@ -26,34 +19,45 @@
 // Positions are kept unwrapped (old cell x may be negative for block 0).  A
 // cluster longer than the halo (or a table without empty cells) sets
 // `overflow`; the caller then redoes the whole move another way.
+//
+// Placement.  Re-inserting a cluster in old-array order gives every element
+// the first cell from its home on that no earlier element has.  That is the
+// one matching in which every cell prefers the earliest of the elements that
+// reach it, and deferred acceptance finds it with the elements proposing in any
+// order: an element asks for its home, a cell keeps the smaller index
+// (atomic minimum on the image), and whoever is turned away or pushed out asks
+// the next cell.  So all lanes place their elements side by side, about 1.3
+// LDS atomics each, where one lane per cluster walked it in order (the longest
+// of 64 clusters of a block held the wavefront, and with 8 to 10 wavefronts
+// per CU nothing hid it).  Elements that do not get their home go on a list that
+// the lanes work off without waiting for one another.  KV64 at fill 1/2, blocks
+// of 512: doubling 2^26 cells 1.21 -> 0.74 ms (4.3 TB/s), the same size 0.96 ->
+// 0.65; blocks of 256: 0.94 -> 0.76 and 0.84 -> 0.52.  (Kept in registers, one
+// row of the window after the other: 0.74 and 1.08; all rows in step: 0.97 and
+// 1.74, every step issuing an atomic per row for a few lanes.)
 #pragma once
+
+#include <type_traits>
 
 #include "lpht_device.h"
 
 namespace lpht {
 
 constexpr int MIG_HALO = 128;
-constexpr uint16_t kImgEmpty = 0xFFFF;
+constexpr uint32_t kImgEmpty = 0xFFFFFFFFu;
 
 __host__ __device__ constexpr uint32_t mig_window(uint32_t mb) { return mb + 2 * MIG_HALO; }
 
-// LDS of one wavefront: window keys and values (u64 each; PACKED32 keeps the
-// word in the key array), each window cell's state (i16: the new home's image
-// slot, below 2 * 1280, or one of the negative codes below), the image (u16
-// per new cell) and the list of cluster starts (u16 per start, at most half
-// the window).
+// LDS of one wavefront: the window's cells, the image (u32 per new cell) and
+// the list of elements still asking (u32, half the window's cells).
 __host__ __device__ constexpr size_t mig_wave_lds(uint32_t mb, uint32_t layout, uint32_t gamma) {
-  return ((size_t)mig_window(mb) * ((layout == 0 ? 8u : 16u) + 2u + 1u) + (size_t)gamma * mig_window(mb) * 2u +
-          15) &
-         ~(size_t)15;
+  return ((size_t)mig_window(mb) * ((layout == 0 ? 8u : 16u) + 2u) + (size_t)gamma * mig_window(mb) * 4u + 15) & ~(size_t)15;
 }
-// The scattering form keeps keys and values in registers: cell states, the
-// image, the cluster starts and each window cell's new slot (u16).
+// The scattering form keeps keys and values in registers: the image and the
+// list, in whose place each window cell's new slot (u16) is kept afterwards.
 __host__ __device__ constexpr size_t mig_wave_lds_scatter(uint32_t mb, uint32_t gamma) {
-  return ((size_t)mig_window(mb) * (2u + 1u + 2u) + (size_t)gamma * mig_window(mb) * 2u + 15) & ~(size_t)15;
+  return ((size_t)mig_window(mb) * 2u + (size_t)gamma * mig_window(mb) * 4u + 15) & ~(size_t)15;
 }
-constexpr int32_t kCellEmpty = -1, kCellTomb = -2, kCellFar = -3;  // window cell states
-
 
 // The window of block b (cells t = lane + 64 q, q < Q, of [b B - H, ...)),
 // wrapped modulo the old capacity (mask = capacity - 1).  COH: device-coherent
@@ -100,31 +104,32 @@ __device__ __forceinline__ long long mig_block(const u64 (&k)[Q], const u64 (&v)
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t gamma = 1u << g;  // 1 or 2
   const uint32_t IW = gamma * W;   // image slots
-  u64 *wkey = (u64 *)base;  // gather only
-  u64 *wval = wkey + W;     // gather, KV64 only
-  static_assert(2 * 64 * Q < 32768, "image slots fit the 16-bit cell states");
-  int16_t *wnh = (int16_t *)(SCATTER ? base : (unsigned char *)(wkey + (LAYOUT == 0 ? W : 2 * W)));
-  uint16_t *img = (uint16_t *)(wnh + W);
-  uint16_t *starts = img + IW;        // cluster starts of [lo, hi)
-  uint16_t *newpos = starts + W / 2;  // scatter only: image slot each element went to
+  typedef typename std::conditional<LAYOUT == 0, u64, u64x2>::type Cell;
+  Cell *wcell = (Cell *)base;  // gather only: the window
+  uint32_t *img = (uint32_t *)(SCATTER ? base : (unsigned char *)(wcell + W));
+  uint32_t *list = img + IW;                     // W / 2 entries
+  uint16_t *newpos = (uint16_t *)list;           // scatter only, afterwards: owned slot each element went to
+  static_assert(2 * 64 * Q < 0xFFFF, "image slots fit 16 bits");
   const u64 cap = 1ull << log2_old, mask = cap - 1;
   const uint32_t log2_new = log2_old + g;
   long long moved = 0;
   const long long d = (long long)(blk * mb);
   const long long wbase = d - H;  // unwrapped old index of window cell 0
   u64 emp[Q];         // ballot of empty window cells, 64 per word
-  uint32_t elem = 0;  // bit q: this lane's cell of row q holds an element
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const uint32_t t = lane + 64 * q;
     const u64 key = LAYOUT == 0 ? (k[q] & 0xFFFFFFFFull) : k[q];
     if (!SCATTER) {
-      wkey[t] = k[q];
-      if (LAYOUT == 1) wval[t] = v[q];
+      if constexpr (LAYOUT == 0)
+        wcell[t] = k[q];
+      else
+        wcell[t] = u64x2{k[q], v[q]};
     }
     emp[q] = __ballot(key == kEmpty);
   }
-  for (uint32_t t = lane; t < IW / 2; t += 64) ((uint32_t *)img)[t] = 0xFFFFFFFFu;
+  for (uint32_t t = lane; t < IW / 4; t += 64)
+    ((uint4 *)img)[t] = uint4{kImgEmpty, kImgEmpty, kImgEmpty, kImgEmpty};
   // the window range [lo, hi) of the clusters overlapping the block
   // (cell H - 1 and cell H both non-empty: a cluster comes in from before);
   // every index into emp[] is a constant, so it stays in registers
@@ -148,94 +153,81 @@ __device__ __forceinline__ long long mig_block(const u64 (&k)[Q], const u64 (&v)
     if (first < 0) skip = true;
     hi = first;
   }
-  // each cell's state; only the cells of [lo, hi) are walked, so only their
-  // keys are hashed (the halo rows outside it are mostly skipped whole)
-  if (!skip) {
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      if (64 * q + 63 < lo || 64 * q >= hi) continue;  // the row lies outside [lo, hi)
-      const int t = (int)lane + 64 * q;
-      const u64 key = LAYOUT == 0 ? (k[q] & 0xFFFFFFFFull) : k[q];
-      int32_t rel = key == kEmpty ? kCellEmpty : kCellTomb;
-      if (key != kEmpty && key != kTomb && t >= lo && t < hi) {
-        // new home, unwrapped consistently with this cell's old position
-        const u64 hn = home_of<LAYOUT>(T, key, crc_hi, crc_lo, mul, log2_new);
-        const u64 oh = hn >> g;
-        const long long x = wbase + (long long)t;
-        const u64 delta = ((u64)x - oh) & mask;
-        const long long nh = (long long)gamma * (x - (long long)delta) + (long long)(hn & (gamma - 1));
-        const long long r = nh - (long long)gamma * wbase;  // image slot of the home
-        rel = (r < 0 || r >= (long long)IW) ? kCellFar : (int32_t)r;
-        elem |= 1u << q;
-      }
-      wnh[t] = (int16_t)rel;
-    }
-  }
   wave_sync();
   if (skip) {
     overflow = true;
   } else {
-    // the cluster starts in [lo, hi) (non-empty cells after an empty one),
-    // listed in LDS; lanes then take them round-robin, each walking its
-    // clusters in old-array order
-    uint32_t nstarts = 0;
+    // Only the elements of [lo, hi) are hashed and placed (the halo rows
+    // outside it are mostly skipped whole).
+    bool bad = false;
+    int before = -1;  // the last empty cell of the rows so far
+    // Elements that did not get their home are listed (who asks, and for which
+    // slot next) and the list worked off by lanes that take the next entry as
+    // soon as theirs has settled.
+    uint32_t nlist = 0;
+    auto work_list = [&]() {
+      wave_sync();
+      uint32_t next = lane, cur = 0, p = 0;
+      bool act = false;
+      while (true) {
+        if (!act && next < nlist) {
+          const uint32_t e = list[next];
+          cur = e & 0xFFFFu;
+          p = e >> 16;
+          act = true;
+          next += 64;
+        }
+        if (!__any(act)) break;
+        if (act) {
+          if (p >= IW) {
+            bad = true;
+            act = false;
+          } else {
+            const uint32_t old = atomicMin(&img[p], cur);
+            act = old != kImgEmpty;
+            cur = old > cur ? old : cur;  // whoever was pushed out or turned away asks on
+            ++p;
+          }
+        }
+      }
+      wave_sync();
+      nlist = 0;
+    };
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
+      const u64 eq = emp[q];
+      const int row_before = before;
+      if (eq) before = 64 * q + 63 - __builtin_clzll(eq);
+      if (64 * q + 63 < lo || 64 * q >= hi) continue;  // the row lies outside [lo, hi)
       const int t = (int)lane + 64 * q;
-      const bool here_empty = (emp[q] >> lane) & 1ull;
-      const bool prev_empty =
-          lane ? (bool)((emp[q] >> (lane - 1)) & 1ull) : (q == 0 ? true : (bool)(emp[q > 0 ? q - 1 : 0] >> 63));
-      const bool st0 = t >= lo && t < hi && !here_empty && prev_empty;
-      const u64 m = __ballot(st0);
-      if (st0) starts[nstarts + __builtin_popcountll(m & ((1ull << lane) - 1))] = (uint16_t)t;
-      nstarts += (uint32_t)__builtin_popcountll(m);
-    }
-    wave_sync();
-    bool bad = false;
-    for (uint32_t i = lane; i < nstarts && !bad; i += 64) {
-      const int st = starts[i];
-      const int tb = (int)gamma * st;  // first image slot of the cluster's target range
-      u64 taken = 0;                   // its cells tb .. tb + 63 taken so far
-      // places the element of window cell u with state c: 0 placed or a
-      // tombstone, 1 the cluster ended, 2 overflow
-      auto place = [&](int c, int u) -> int {
-        if (c == kCellEmpty) return 1;
-        if (c == kCellTomb) return 0;
-        if (c < tb) return 2;  // far: its home lies before the window
-        int p;
-        const int off = c - tb;
-        const u64 fr = off < 64 ? ~taken & (~0ull << off) : 0ull;
-        if (fr) {
-          p = tb + __builtin_ctzll(fr);
+      const u64 key = LAYOUT == 0 ? (k[q] & 0xFFFFFFFFull) : k[q];
+      uint32_t left = 0;
+      if (key != kEmpty && key != kTomb && t >= lo && t < hi) {
+        // new home, unwrapped consistently with this cell's old position
+        const u64 hn = home_of<LAYOUT>(T, key, crc_hi, crc_lo, mul, log2_new);
+        // how far the element was displaced in the old table
+        const u64 delta = ((u64)(wbase + (long long)t) - (hn >> g)) & mask;
+        // image slot of the home; far elements (homes before the window) fail
+        // the test below
+        const int r = delta < W ? (int)gamma * (t - (int)delta) + (int)(hn & (gamma - 1)) : -1;
+        // its cluster's target range begins at gamma times the cluster's start
+        const u64 eb = eq & ((1ull << lane) - 1);
+        const int start = 1 + (eb ? 64 * q + 63 - __builtin_clzll(eb) : row_before);
+        if (r < (int)gamma * start) {
+          bad = true;
         } else {
-          p = off < 64 ? tb + 64 : c;
-          while (p < (int)IW && img[p] != kImgEmpty) ++p;
+          const uint32_t old = atomicMin(&img[r], (uint32_t)t);
+          if (old != kImgEmpty) left = (old > (uint32_t)t ? old : (uint32_t)t) | ((uint32_t)(r + 1) << 16);
         }
-        if (p >= (int)IW) return 2;
-        if (p - tb < 64) taken |= 1ull << (p - tb);
-        img[p] = (uint16_t)u;
-        if (SCATTER) newpos[u] = (uint16_t)p;
-        return 0;
-      };
-      // the cells' states are loaded four ahead of their placement
-      auto state = [&](int u) -> int { return u < hi ? wnh[u] : kCellEmpty; };
-      int c0 = state(st), c1 = state(st + 1), c2 = state(st + 2), c3 = state(st + 3);
-      for (int u = st;; u += 4) {
-        const int n0 = state(u + 4), n1 = state(u + 5), n2 = state(u + 6), n3 = state(u + 7);
-        int r = place(c0, u);
-        if (!r) r = place(c1, u + 1);
-        if (!r) r = place(c2, u + 2);
-        if (!r) r = place(c3, u + 3);
-        if (r) {
-          bad |= r == 2;
-          break;
-        }
-        c0 = n0;
-        c1 = n1;
-        c2 = n2;
-        c3 = n3;
+      }
+      const u64 m = __ballot(left != 0);  // (a slot to ask for is never 0)
+      if (m) {
+        if (nlist + 64 > W / 2) work_list();
+        if (left) list[nlist + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1))] = left;
+        nlist += (uint32_t)__builtin_popcountll(m);
       }
     }
+    work_list();
     const u64 dst0 = (u64)d * gamma;
     const uint32_t o0 = gamma * H, n_out = gamma * mb;  // the owned image slots [o0, o0 + n_out)
     auto put = [&](u64 x, u64 kw, u64 vw) {
@@ -256,30 +248,41 @@ __device__ __forceinline__ long long mig_block(const u64 (&k)[Q], const u64 (&v)
         overflow = true;  // the caller redoes the move; nothing is written
       } else {
         wave_sync();
-        // the lane's own elements placed in the owned range, then zeros in
-        // the owned cells left empty
+        for (uint32_t t = lane; t < W / 2; t += 64) ((uint32_t *)newpos)[t] = 0xFFFFFFFFu;
+        wave_sync();
+        // zeros in the owned cells left empty, then the lane's own elements
+        // placed in the owned range
+        for (uint32_t t = lane; t < n_out; t += 64) {
+          const uint32_t ix = img[o0 + t];
+          if (ix == kImgEmpty)
+            put(dst0 + t, 0ull, 0ull);
+          else
+            newpos[ix] = (uint16_t)t;
+        }
+        wave_sync();
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-          const int t = (int)lane + 64 * q;
-          if (!((elem >> q) & 1u) || t < lo || t >= hi) continue;
-          const uint32_t o = (uint32_t)newpos[t] - o0;  // wraps when below the owned range
+          const uint32_t o = newpos[lane + 64 * q];
           if (o >= n_out) continue;
           put(dst0 + o, k[q], v[q]);
           ++moved;
         }
-        for (uint32_t t = lane; t < n_out; t += 64)
-          if (img[o0 + t] == kImgEmpty) put(dst0 + t, 0ull, 0ull);
       }
     } else {
       if (bad) overflow = true;
       wave_sync();
       // the owned new cells [g*d, g*(d+B)) = image slots [g*H, g*(H+B))
       for (uint32_t t = lane; t < n_out; t += 64) {
-        const uint16_t ix = img[o0 + t];
+        const uint32_t ix = img[o0 + t];
         const bool e = ix == kImgEmpty;
         const uint32_t j = e ? 0u : ix;
-        const u64 kw = wkey[j], vw = LAYOUT == 1 ? wval[j] : 0ull;
-        put(dst0 + t, e ? 0ull : kw, e ? 0ull : vw);
+        if constexpr (LAYOUT == 0) {
+          const u64 w = wcell[j];
+          put(dst0 + t, e ? 0ull : w, 0ull);
+        } else {
+          const u64x2 w = wcell[j];
+          put(dst0 + t, e ? 0ull : w.x, e ? 0ull : w.y);
+        }
         moved += !e;
       }
     }
