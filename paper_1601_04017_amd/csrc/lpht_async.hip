@@ -97,26 +97,35 @@ __device__ __forceinline__ View view_of(const AsyncArgs &a, uint32_t e, uint32_t
   return v;
 }
 
-// Waits (lane 0 polls) until *p >= target; false if the bound passed.
-__device__ bool wait_ge(const uint32_t *p, uint32_t target, u64 ticks) {
-  uint32_t ok = 1;
-  if ((threadIdx.x & 63) == 0) {
+// The waits of a growth are made by one wavefront for its workgroup: every
+// poll of a line takes its turn at 12 ns, and with 2048 wavefronts polling,
+// each arrival counted on that line queued behind 25 us of polls.
+//
+// Waits until *p >= target; false if the bound passed.  Called by all
+// wavefronts of the workgroup; s_word is LDS of the workgroup's.
+__device__ bool wait_ge(const uint32_t *p, uint32_t target, u64 ticks, uint32_t *s_word) {
+  if (threadIdx.x == 0) {
+    uint32_t ok = 1;
     const u64 t0 = wall_clock64();
     while (ld32(p) < target) {
       if (wall_clock64() - t0 > ticks) {
         ok = 0;
         break;
       }
-      __builtin_amdgcn_s_sleep(2);
+      __builtin_amdgcn_s_sleep(4);
     }
+    *s_word = ok;
   }
-  return uni(ok) != 0;
+  __syncthreads();
+  const bool ok = uni(*s_word) != 0;
+  __syncthreads();  // read before the next wait writes it
+  return ok;
 }
 
 // Waits until gen moved past `g`; returns the new gen, or ~0u on timeout.
-__device__ uint32_t wait_gen_past(const uint32_t *gen, uint32_t g, u64 ticks) {
-  uint32_t r = 0;
-  if ((threadIdx.x & 63) == 0) {
+__device__ uint32_t wait_gen_past(const uint32_t *gen, uint32_t g, u64 ticks, uint32_t *s_word) {
+  if (threadIdx.x == 0) {
+    uint32_t r;
     const u64 t0 = wall_clock64();
     for (;;) {
       r = ld32(gen);
@@ -125,10 +134,14 @@ __device__ uint32_t wait_gen_past(const uint32_t *gen, uint32_t g, u64 ticks) {
         r = ~0u;
         break;
       }
-      __builtin_amdgcn_s_sleep(2);
+      __builtin_amdgcn_s_sleep(4);
     }
+    *s_word = r;
   }
-  return uni(r);
+  __syncthreads();
+  const uint32_t r = uni(*s_word);
+  __syncthreads();
+  return r;
 }
 
 __device__ __forceinline__ uint32_t lane0_add(uint32_t *p, uint32_t d) {
@@ -183,21 +196,23 @@ __device__ bool arrive(AsyncCtl *ctl, uint32_t sh, uint32_t W, uint32_t k) {
 // Outside the migration every access to the tables is device-coherent by
 // itself (agent-scope relaxed atomic loads, stores and read-modify-writes).
 // The block migration uses plain loads and stores, bracketed by two
-// agent-scope fences per wavefront: one after the first arrival (this XCD's
-// L2 may hold lines of the old table older than the inserters' atomics) and
-// one before the second (the new cells sit in this XCD's L2 until written
-// back).
+// agent-scope fences: an acquire per wavefront after the first arrival (this
+// XCD's L2 may hold lines of the old table older than the inserters' atomics)
+// and a release per workgroup before the second (the new cells sit in this
+// XCD's L2 until written back).  A release writes the XCD's whole L2 back, so
+// its number is what a growth costs: a full fence of every wavefront at both
+// places made a growth of 2^22 cells 650 us, 570 like this.
 template <int L>
 __device__ bool migrate(const AsyncArgs &a, const uint32_t (*T)[256], uint32_t e, uint32_t W, uint32_t wid,
-                        u64 ticks, unsigned char *wlds) {
+                        u64 ticks, unsigned char *wlds, uint32_t *s_word) {
   AsyncCtl *ctl = a.ctl;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t sh = wid % kAsyncShards, S = shards_used(W);
   const View o = view_of(a, e, W), nv = view_of(a, e + 1, W);
   // 1.
   arrive(ctl, sh, W, 1);
-  if (!wait_ge(&ctl->arrived, S, ticks)) return false;
-  __threadfence();
+  if (!wait_ge(&ctl->arrived, S, ticks, s_word)) return false;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   // 2. (the capacity is at least 2^19 cells, a whole number of blocks)
   const u64 oc = 1ull << o.log2c;
   const uint32_t nblocks = (uint32_t)(oc / kMigB);
@@ -220,10 +235,14 @@ __device__ bool migrate(const AsyncArgs &a, const uint32_t (*T)[256], uint32_t e
   }
   if (__any(overflow) && lane == 0)
     __hip_atomic_store(&ctl->mig_overflow, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // 3.
-  __threadfence();
+  // 3. (each wavefront's stores have reached L2 before the workgroup's one
+  // write-back)
+  wait_mem();
+  __syncthreads();
+  if ((threadIdx.x >> 6) == 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __syncthreads();
   arrive(ctl, sh, W, 2);
-  if (!wait_ge(&ctl->arrived, 2 * S, ticks)) return false;
+  if (!wait_ge(&ctl->arrived, 2 * S, ticks, s_word)) return false;
   const bool fallback = uni(ld32(&ctl->mig_overflow)) != 0;
   uint32_t last = 3;  // the barrier after which everything is written
   if (fallback) {
@@ -240,7 +259,7 @@ __device__ bool migrate(const AsyncArgs &a, const uint32_t (*T)[256], uint32_t e
       }
     }
     arrive(ctl, sh, W, 3);
-    if (!wait_ge(&ctl->arrived, 3 * S, ticks)) return false;
+    if (!wait_ge(&ctl->arrived, 3 * S, ticks, s_word)) return false;
     last = 4;
     moved = 0;
     for (;;) {
@@ -341,6 +360,7 @@ template <int L>
 __global__ void __launch_bounds__(256) k_async_insert(AsyncArgs a, u64 ticks, uint32_t W) {
   __shared__ uint32_t T[8][256];
   __shared__ __attribute__((aligned(16))) unsigned char wl[4][kWaveLds];
+  __shared__ uint32_t s_word;
   crc_tables_build(T);
   unsigned char *wlds = wl[threadIdx.x >> 6];
   ChunkLds &C = *reinterpret_cast<ChunkLds *>(wlds);
@@ -475,12 +495,12 @@ __global__ void __launch_bounds__(256) k_async_insert(AsyncArgs a, u64 ticks, ui
       apply_slots(C.hot, hot);
       hot = 0;
       local = 0;  // the migration recounts what was inserted
-      if (!migrate<L>(a, T, my, W, wid, ticks, wlds)) {
+      if (!migrate<L>(a, T, my, W, wid, ticks, wlds, &s_word)) {
         err = 1;
         break;
       }
       clear_chunk();  // the migration used its LDS
-      const uint32_t g2 = wait_gen_past(gen, g, ticks);
+      const uint32_t g2 = wait_gen_past(gen, g, ticks, &s_word);
       if (g2 == ~0u) {
         err = 1;
         break;
@@ -495,7 +515,7 @@ __global__ void __launch_bounds__(256) k_async_insert(AsyncArgs a, u64 ticks, ui
         err = 1;
         break;
       }
-      __builtin_amdgcn_s_sleep(4);
+      __builtin_amdgcn_s_sleep(32);  // (the others' counters share the polled lines)
       continue;
     }
     if (pos >= end && hot) {
