@@ -41,7 +41,7 @@ struct BulkMergeCtl {
                                 // staging holds (inconsistent counts); nothing was written
   unsigned int big_blocks;      // target blocks sorted by the global-memory path
   unsigned int mid_blocks;      // target blocks sorted by a whole workgroup
-  unsigned int pad0;
+  unsigned int skewed;          // 1: some first-level bin holds far more than its share
   unsigned long long pad[4];
 };
 

@@ -68,7 +68,20 @@ constexpr uint32_t kL2Max = 2048;
 constexpr uint32_t kGAMax = 1024;
 constexpr uint32_t kEW = 256;       // elements a wavefront sorts in LDS in stage C
 constexpr uint32_t kEMax = 1024;    // elements a workgroup sorts in LDS in stage C
+// Stage C ranks an element among those of its home cell, unless some cell of
+// the block has more than kCrowd (many copies of one key): then a bitonic
+// network's 36 steps beat the comparisons (10^8 Zipf(1.0) keys: 4.1 ms against
+// 5.8; 10^7 keys, a quarter of them twice: 435 us against 216).
+constexpr uint32_t kCrowd = 12;
 constexpr uint32_t kScanPer = 16;   // blocks per thread in stage D
+constexpr uint32_t kCountLoads = 8;
+constexpr uint32_t kTileP = 4096;   // tile of the scatter without skew
+constexpr uint32_t kThreadsP = 512;
+constexpr uint32_t kTileB = 4096;   // tile of stage B without skew
+// A bin of more than so many times the average (and a tile) is skew: its
+// workgroup of stage B would run that much longer than the others, and the
+// passes that combine equal keys on the way are taken instead.
+constexpr uint32_t kSkewTimes = 4;
 constexpr uint32_t kScanTile = 256 * kScanPer;
 
 template <int L>
@@ -254,7 +267,7 @@ __global__ void k_bm_init(BulkMergeCtl *ctl) {
 }
 
 template <int L>
-__global__ void __launch_bounds__(256) k_bm_count(BmK k) {
+__global__ void __launch_bounds__(512) k_bm_count(BmK k) {
   __shared__ uint32_t T[8][256];
   __shared__ uint32_t hist[kL1Max];
   __shared__ uint32_t s_err;
@@ -265,11 +278,29 @@ __global__ void __launch_bounds__(256) k_bm_count(BmK k) {
   const u64 lo = (u64)blockIdx.x * k.per;
   const u64 hi = std::min<u64>(lo + k.per, k.ntot);
   uint32_t err = 0;
-  for (u64 e = lo + threadIdx.x; e < hi; e += blockDim.x) {
-    KT<L> key, val;
-    uint32_t seq;
-    if (!load_elem<L>(k, e, key, val, seq, err)) continue;
-    atomicAdd(&hist[top_bits(sort_hash<L>(T, key, k.crc_hi, k.mul), k.l1_bits)], 1u);
+  // kCountLoads elements' loads in flight per lane: the pass only streams
+  for (u64 e0 = lo; e0 < hi; e0 += (u64)blockDim.x * kCountLoads) {
+    KT<L> key[kCountLoads];
+#pragma unroll
+    for (uint32_t j = 0; j < kCountLoads; ++j) {
+      const u64 e = e0 + (u64)j * blockDim.x + threadIdx.x;
+      key[j] = 0;
+      if (e < hi) {
+        if (e < k.cold)
+          key[j] = L == 0 ? (KT<L>)(((const u64 *)k.old_cells)[e] & 0xFFFFFFFFull)
+                          : (KT<L>)((const u64 *)k.old_cells)[2 * e];
+        else
+          key[j] = ((const KT<L> *)k.keys)[e - k.cold];
+      }
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kCountLoads; ++j) {
+      const u64 e = e0 + (u64)j * blockDim.x + threadIdx.x;
+      if ((u64)key[j] > kTomb)
+        atomicAdd(&hist[top_bits(sort_hash<L>(T, key[j], k.crc_hi, k.mul), k.l1_bits)], 1u);
+      else if (e < hi && e >= k.cold)
+        err |= kErrReserved;  // in the batch, not an empty or erased cell
+    }
   }
   if (err) atomicOr(&s_err, err);
   __syncthreads();
@@ -301,10 +332,14 @@ __global__ void __launch_bounds__(1024) k_bm_scan_bins(BmK k) {
   __shared__ uint32_t sw[17];
   const uint32_t per = (k.L1 + blockDim.x - 1) / blockDim.x;
   const uint32_t b0 = std::min(k.L1, threadIdx.x * per), b1 = std::min(k.L1, b0 + per);
-  uint32_t sum = 0;
-  for (uint32_t b = b0; b < b1; ++b) sum += k.l1_off[b];
+  uint32_t sum = 0, most = 0;
+  for (uint32_t b = b0; b < b1; ++b) {
+    sum += k.l1_off[b];
+    most = std::max(most, k.l1_off[b]);
+  }
   uint32_t total;
   uint32_t acc = block_excl_scan(sum, &total, sw);
+  if (most > kSkewTimes * (total / k.L1) + kTileP) k.ctl->skewed = 1;
   for (uint32_t b = b0; b < b1; ++b) {
     const uint32_t t = k.l1_off[b];
     k.l1_off[b] = acc;
@@ -318,6 +353,96 @@ __global__ void __launch_bounds__(1024) k_bm_scan_bins(BmK k) {
   }
 }
 
+// Without skew: nothing is combined (stage C removes the equal keys of a
+// block).  A tile's elements are ranked inside their bins by LDS atomics, put
+// in bin order in LDS one array at a time and written as runs.
+template <int L>
+__global__ void __launch_bounds__(kThreadsP) k_bm_scatter_plain(BmK k) {
+  __shared__ uint32_t T[8][256];
+  __shared__ KT<L> buf[kTileP];
+  __shared__ uint16_t obin[kTileP];
+  __shared__ uint32_t cur[kL1Max];       // next position of each bin in this share
+  __shared__ uint32_t toff[kL1Max + 1];  // the tile's bins
+  __shared__ uint32_t sw[17];
+  if (k.ctl->full || k.ctl->skewed) return;
+  crc_tables_build(T);
+  constexpr uint32_t PER = kTileP / kThreadsP;
+  const uint32_t w = blockIdx.x;
+  for (uint32_t i = threadIdx.x; i < k.L1; i += blockDim.x) cur[i] = k.l1_off[i] + k.moff[(u64)i * k.GA + w];
+  const u64 lo = (u64)w * k.per;
+  const u64 hi = std::min<u64>(lo + k.per, k.ntot);
+  KT<L> *keyA = (KT<L> *)k.keyA;
+  KT<L> *valA = (KT<L> *)k.valA;
+  uint32_t err = 0;
+  for (u64 tile = lo; tile < hi; tile += kTileP) {
+    for (uint32_t i = threadIdx.x; i <= k.L1; i += blockDim.x) toff[i] = 0;
+    KT<L> key[PER], val[PER];
+    uint32_t seq[PER], at[PER];
+    bool ok[PER];
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j) {
+      const u64 e = tile + threadIdx.x + kThreadsP * j;
+      ok[j] = e < hi && load_elem<L>(k, e, key[j], val[j], seq[j], err);
+    }
+    __syncthreads();
+    // bin (low 16 bits) and rank inside it
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j) {
+      at[j] = 0;
+      if (ok[j]) {
+        const uint32_t b = top_bits(sort_hash<L>(T, key[j], k.crc_hi, k.mul), k.l1_bits);
+        at[j] = b | (atomicAdd(&toff[b], 1u) << 16);
+      }
+    }
+    __syncthreads();
+    {
+      const uint32_t per = (k.L1 + 1 + blockDim.x - 1) / blockDim.x;
+      const uint32_t b0 = std::min(k.L1 + 1, threadIdx.x * per), b1 = std::min(k.L1 + 1, b0 + per);
+      uint32_t s = 0;
+      for (uint32_t b = b0; b < b1; ++b) s += toff[b];
+      uint32_t tot;
+      uint32_t acc = block_excl_scan(s, &tot, sw);
+      for (uint32_t b = b0; b < b1; ++b) {
+        const uint32_t t = toff[b];
+        toff[b] = acc;
+        acc += t;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j) {
+      if (!ok[j]) continue;
+      const uint32_t b = at[j] & 0xFFFFu;
+      at[j] = toff[b] + (at[j] >> 16);
+      buf[at[j]] = key[j];
+      obin[at[j]] = (uint16_t)b;
+    }
+    __syncthreads();
+    const uint32_t total = toff[k.L1];
+    auto place = [&](uint32_t i) -> u64 {
+      const uint32_t b = obin[i];
+      return (u64)cur[b] + (i - toff[b]);
+    };
+    for (uint32_t i = threadIdx.x; i < total; i += blockDim.x) keyA[place(i)] = buf[i];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j)
+      if (ok[j]) buf[at[j]] = val[j];
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < total; i += blockDim.x) valA[place(i)] = buf[i];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j)
+      if (ok[j]) ((uint32_t *)buf)[at[j]] = seq[j];
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < total; i += blockDim.x) k.seqA[place(i)] = ((uint32_t *)buf)[i];
+    __syncthreads();
+    for (uint32_t b = threadIdx.x; b < k.L1; b += blockDim.x) cur[b] += toff[b + 1] - toff[b];
+    __syncthreads();
+  }
+  if (err) atomicOr(&k.st->err, err);
+}
+
 template <int L>
 __global__ void __launch_bounds__(256) k_bm_scatter(BmK k) {
   __shared__ uint32_t T[8][256];
@@ -327,7 +452,7 @@ __global__ void __launch_bounds__(256) k_bm_scatter(BmK k) {
   __shared__ uint16_t order[kTileA];
   __shared__ uint16_t obin[kTileA];
   __shared__ uint32_t sw[17];
-  if (k.ctl->full) return;
+  if (k.ctl->full || !k.ctl->skewed) return;
   crc_tables_build(T);
   const uint32_t w = blockIdx.x;
   for (uint32_t i = threadIdx.x; i < k.L1; i += blockDim.x) cur[i] = k.l1_off[i] + k.moff[(u64)i * k.GA + w];
@@ -423,6 +548,138 @@ __global__ void __launch_bounds__(256) k_bm_scatter(BmK k) {
 
 // ------------------------------------------------------------- stage B
 
+// Without skew: one workgroup of 1024 threads per first-level bin counts its
+// elements per block and moves them.
+template <int L>
+__global__ void __launch_bounds__(1024) k_bm_partition_plain(BmK k) {
+  __shared__ uint32_t T[8][256];
+  __shared__ uint32_t hist[kL2Max];
+  __shared__ uint32_t toff[kL2Max + 1];
+  __shared__ KT<L> buf[kTileB];
+  __shared__ uint16_t obin[kTileB];
+  __shared__ uint32_t sw[17];
+  if (k.ctl->full || k.ctl->skewed) return;
+  crc_tables_build(T);
+  const uint32_t s = blockIdx.x;
+  const uint32_t nl2 = 1u << k.l2_bits;
+  const uint32_t mask2 = nl2 - 1;
+  for (uint32_t i = threadIdx.x; i < nl2; i += blockDim.x) hist[i] = 0;
+  __syncthreads();
+  const u64 out0 = k.l1_off[s];
+  const uint32_t total = k.l1_off[s + 1] - k.l1_off[s];
+  const KT<L> *keyA = (const KT<L> *)k.keyA + out0;
+  const KT<L> *valA = (const KT<L> *)k.valA + out0;
+  const uint32_t *seqA = k.seqA + out0;
+  KT<L> *keyB = (KT<L> *)k.keyB + out0;
+  KT<L> *valB = (KT<L> *)k.valB + out0;
+  uint32_t *seqB = k.seqB + out0;
+  constexpr uint32_t U = 8;
+  auto blk = [&](KT<L> key) { return top_bits(sort_hash<L>(T, key, k.crc_hi, k.mul), k.nb_bits) & mask2; };
+  for (uint32_t j0 = 0; j0 < total; j0 += U * 1024) {
+    KT<L> key[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t j = j0 + u * 1024 + threadIdx.x;
+      key[u] = j < total ? keyA[j] : (KT<L>)0;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u)
+      if (key[u] != 0) atomicAdd(&hist[blk(key[u])], 1u);
+  }
+  __syncthreads();
+  {
+    const uint32_t per = (nl2 + blockDim.x - 1) / blockDim.x;  // <= 2
+    const uint32_t i0 = std::min(nl2, threadIdx.x * per), i1 = std::min(nl2, i0 + per);
+    uint32_t sum = 0;
+    for (uint32_t i = i0; i < i1; ++i) sum += hist[i];
+    uint32_t tot;
+    uint32_t acc = block_excl_scan(sum, &tot, sw);
+    for (uint32_t i = i0; i < i1; ++i) {
+      const uint32_t c = hist[i];
+      const u64 at = ((u64)s << k.l2_bits) + i;
+      k.blk_off[at] = (uint32_t)(out0 + acc);
+      k.blk_cnt[at] = c;
+      hist[i] = acc;  // becomes the cursor
+      acc += c;
+    }
+  }
+  __syncthreads();
+  // tiles in block order through LDS, one array at a time, as in stage A
+  constexpr uint32_t V = kTileB / 1024;
+  for (uint32_t j0 = 0; j0 < total; j0 += kTileB) {
+    for (uint32_t i = threadIdx.x; i <= nl2; i += blockDim.x) toff[i] = 0;
+    KT<L> key[V], val[V];
+    uint32_t seq[V], at[V];
+#pragma unroll
+    for (uint32_t u = 0; u < V; ++u) {
+      const uint32_t j = j0 + u * 1024 + threadIdx.x;
+      const bool in = j < total;
+      key[u] = in ? keyA[j] : (KT<L>)0;
+      val[u] = in ? valA[j] : (KT<L>)0;
+      seq[u] = in ? seqA[j] : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < V; ++u) {
+      at[u] = 0;
+      if (key[u] != 0) {
+        const uint32_t b = blk(key[u]);
+        at[u] = b | (atomicAdd(&toff[b], 1u) << 16);
+      }
+    }
+    __syncthreads();
+    {
+      const uint32_t per = (nl2 + 1 + blockDim.x - 1) / blockDim.x;
+      const uint32_t b0 = std::min(nl2 + 1, threadIdx.x * per), b1 = std::min(nl2 + 1, b0 + per);
+      uint32_t sum = 0;
+      for (uint32_t b = b0; b < b1; ++b) sum += toff[b];
+      uint32_t tot;
+      uint32_t acc = block_excl_scan(sum, &tot, sw);
+      for (uint32_t b = b0; b < b1; ++b) {
+        const uint32_t t = toff[b];
+        toff[b] = acc;
+        acc += t;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < V; ++u) {
+      if (key[u] == 0) continue;
+      const uint32_t b = at[u] & 0xFFFFu;
+      at[u] = toff[b] + (at[u] >> 16);
+      buf[at[u]] = key[u];
+      obin[at[u]] = (uint16_t)b;
+    }
+    __syncthreads();
+    const uint32_t tile = toff[nl2];
+    uint32_t pos[V];
+#pragma unroll
+    for (uint32_t u = 0; u < V; ++u) {
+      const uint32_t i = u * 1024 + threadIdx.x;
+      pos[u] = i < tile ? hist[obin[i]] + (i - toff[obin[i]]) : ~0u;
+      if (i < tile) keyB[pos[u]] = buf[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < V; ++u)
+      if (key[u] != 0) buf[at[u]] = val[u];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < V; ++u)
+      if (pos[u] != ~0u) valB[pos[u]] = buf[u * 1024 + threadIdx.x];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < V; ++u)
+      if (key[u] != 0) ((uint32_t *)buf)[at[u]] = seq[u];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < V; ++u)
+      if (pos[u] != ~0u) seqB[pos[u]] = ((uint32_t *)buf)[u * 1024 + threadIdx.x];
+    for (uint32_t i = threadIdx.x; i < nl2; i += blockDim.x) hist[i] += toff[i + 1] - toff[i];
+    __syncthreads();
+  }
+}
+
 // One workgroup of 1024 threads per first-level bin s.
 template <int L>
 __global__ void __launch_bounds__(1024) k_bm_partition(BmK k) {
@@ -430,7 +687,7 @@ __global__ void __launch_bounds__(1024) k_bm_partition(BmK k) {
   __shared__ uint32_t hist[kL2Max];
   __shared__ Combine<L> cb;
   __shared__ uint32_t sw[17];
-  if (k.ctl->full) return;
+  if (k.ctl->full || !k.ctl->skewed) return;
   crc_tables_build(T);
   const uint32_t s = blockIdx.x;
   const uint32_t nl2 = 1u << k.l2_bits;
@@ -558,7 +815,9 @@ struct WaveLds {
   KT<L> val[kEW];
   uint32_t seq[kEW];
   uint32_t u[kEW];
-  uint16_t ix[kEW];
+  uint32_t bin[257];  // elements per home cell, then where they begin
+  uint16_t grp[kEW];  // elements by home cell
+  uint16_t ix[kEW];   // elements in order
 };
 
 template <int L>
@@ -568,18 +827,38 @@ __device__ __forceinline__ bool witem_less(const WaveLds<L> &b, uint32_t x, uint
   return b.seq[x] < b.seq[y];
 }
 
-__device__ __forceinline__ long long wave_max(long long v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const long long t = __shfl_xor(v, o, 64);
-    v = v > t ? v : t;
+// Sorts ix[0..cnt) by a bitonic network over the next power of two (positions
+// >= cnt act as +infinity), wave barriers only.
+template <int L>
+__device__ __forceinline__ void wave_bitonic(WaveLds<L> &b, uint32_t cnt) {
+  const uint32_t lane = threadIdx.x & 63;
+  auto step = [&](uint32_t i, uint32_t j) {
+    if (j < cnt && witem_less<L>(b, b.ix[j], b.ix[i])) {
+      const uint16_t x = b.ix[i];
+      b.ix[i] = b.ix[j];
+      b.ix[j] = x;
+    }
+  };
+  uint32_t P = 1;
+  while (P < cnt) P <<= 1;
+  for (uint32_t kk = 2; kk <= P; kk <<= 1) {
+    for (uint32_t t = lane; t < P / 2; t += 64) {
+      const uint32_t half = kk >> 1, bl = t / half, r = t % half;
+      step(bl * kk + r, bl * kk + kk - 1 - r);
+    }
+    wave_sync();
+    for (uint32_t jj = kk >> 2; jj >= 1; jj >>= 1) {
+      for (uint32_t t = lane; t < P / 2; t += 64) {
+        const uint32_t i = 2 * jj * (t / jj) + (t % jj);
+        step(i, i + jj);
+      }
+      wave_sync();
+    }
   }
-  return v;
 }
 
 // One wavefront per block (4 per workgroup, no workgroup barrier after the
-// CRC tables): the block's elements are sorted by a bitonic network in the
-// wavefront's LDS, equal keys reduced to their run end, and the carry map
+// CRC tables): the block's elements are sorted in the wavefront's LDS, equal keys reduced to their run end, and the carry map
 // computed.  Larger blocks are listed for the workgroup and global paths.
 template <int L>
 __global__ void __launch_bounds__(256) k_bm_block_wave(BmK k) {
@@ -592,8 +871,51 @@ __global__ void __launch_bounds__(256) k_bm_block_wave(BmK k) {
   KT<L> *keyB = (KT<L> *)k.keyB;
   KT<L> *valB = (KT<L> *)k.valB;
   const uint32_t B = 1u << k.log2b;
-  for (u64 blk = (u64)blockIdx.x * 4 + wv; blk < k.nblocks; blk += (u64)gridDim.x * 4) {
-    const uint32_t off = k.blk_off[blk], cnt = k.blk_cnt[blk];
+  // The next block's elements, and the range of the one after it, are loaded
+  // while a block is worked on: with 12 wavefronts per CU the dependent loads
+  // would be most of a block's time.
+  constexpr uint32_t R = kEW / 64;
+  const u64 step = (u64)gridDim.x * 4;
+  KT<L> nkey[R], nval[R];
+  uint32_t nseq[R], noff = 0, ncnt = 0, off2 = 0, cnt2 = 0;
+  auto load_block = [&]() {
+#pragma unroll
+    for (uint32_t q = 0; q < R; ++q) {
+      const uint32_t i = lane + 64 * q;
+      if (i < ncnt && ncnt <= kEW) {
+        nkey[q] = keyB[(u64)noff + i];
+        nval[q] = valB[(u64)noff + i];
+        nseq[q] = k.seqB[(u64)noff + i];
+      }
+    }
+  };
+  u64 blk = (u64)blockIdx.x * 4 + wv;
+  if (blk < k.nblocks) {
+    noff = k.blk_off[blk];
+    ncnt = k.blk_cnt[blk];
+    load_block();
+  }
+  if (blk + step < k.nblocks) {
+    off2 = k.blk_off[blk + step];
+    cnt2 = k.blk_cnt[blk + step];
+  }
+  for (; blk < k.nblocks; blk += step) {
+    const uint32_t off = noff, cnt = ncnt;
+    KT<L> ckey[R], cval[R];
+    uint32_t cseq[R];
+#pragma unroll
+    for (uint32_t q = 0; q < R; ++q) {
+      ckey[q] = nkey[q];
+      cval[q] = nval[q];
+      cseq[q] = nseq[q];
+    }
+    noff = off2;
+    ncnt = blk + step < k.nblocks ? cnt2 : 0;
+    load_block();
+    if (blk + 2 * step < k.nblocks) {
+      off2 = k.blk_off[blk + 2 * step];
+      cnt2 = k.blk_cnt[blk + 2 * step];
+    }
     if (cnt > kEW) {
       if (lane == 0) {
         if (cnt > kEMax)
@@ -603,74 +925,88 @@ __global__ void __launch_bounds__(256) k_bm_block_wave(BmK k) {
       }
       continue;
     }
-    for (uint32_t i = lane; i < cnt; i += 64) {
-      b.key[i] = keyB[(u64)off + i];
-      b.val[i] = valB[(u64)off + i];
-      b.seq[i] = k.seqB[(u64)off + i];
-      b.u[i] = sort_hash<L>(T, b.key[i], k.crc_hi, k.mul);
-      b.ix[i] = (uint16_t)i;
+    for (uint32_t i = lane; i < 257; i += 64) b.bin[i] = 0;
+    wave_sync();
+    // The order begins with the home cell: count the elements of each of the
+    // block's cells, then rank each among the few of its own cell.
+    uint32_t home[kEW / 64], at[kEW / 64];
+#pragma unroll
+    for (uint32_t q = 0; q < kEW / 64; ++q) {
+      const uint32_t i = lane + 64 * q;
+      if (i >= cnt) continue;
+      b.key[i] = ckey[q];
+      b.val[i] = cval[q];
+      b.seq[i] = cseq[q];
+      b.u[i] = sort_hash<L>(T, ckey[q], k.crc_hi, k.mul);
+      home[q] = top_bits(b.u[i], k.log2c) & (B - 1);
+      at[q] = atomicAdd(&b.bin[home[q]], 1u);
     }
     wave_sync();
-    uint32_t P = 1;
-    while (P < cnt) P <<= 1;
-    for (uint32_t kk = 2; kk <= P; kk <<= 1) {
-      for (uint32_t t = lane; t < P / 2; t += 64) {
-        const uint32_t half = kk >> 1, bl = t / half, r = t % half;
-        const uint32_t i = bl * kk + r, j = bl * kk + kk - 1 - r;
-        if (j < cnt && witem_less<L>(b, b.ix[j], b.ix[i])) {
-          const uint16_t x = b.ix[i];
-          b.ix[i] = b.ix[j];
-          b.ix[j] = x;
+    bool crowded;
+    {
+      const uint32_t c0 = b.bin[4 * lane], c1 = b.bin[4 * lane + 1], c2 = b.bin[4 * lane + 2], c3 = b.bin[4 * lane + 3];
+      crowded = __any(std::max(std::max(c0, c1), std::max(c2, c3)) > kCrowd);
+      const uint32_t s0 = wave_incl_scan(c0 + c1 + c2 + c3) - (c0 + c1 + c2 + c3);
+      wave_sync();
+      b.bin[4 * lane] = s0;
+      b.bin[4 * lane + 1] = s0 + c0;
+      b.bin[4 * lane + 2] = s0 + c0 + c1;
+      b.bin[4 * lane + 3] = s0 + c0 + c1 + c2;
+      if (lane == 63) b.bin[256] = cnt;
+    }
+    wave_sync();
+#pragma unroll
+    for (uint32_t q = 0; q < R; ++q)
+      if (lane + 64 * q < cnt) b.grp[b.bin[home[q]] + at[q]] = (uint16_t)(lane + 64 * q);
+    wave_sync();
+    if (!crowded) {
+#pragma unroll
+      for (uint32_t q = 0; q < R; ++q) {
+        const uint32_t i = lane + 64 * q;
+        if (i >= cnt) continue;
+        const uint32_t g0 = b.bin[home[q]], g1 = b.bin[home[q] + 1];
+        uint32_t r = g0;
+        for (uint32_t j = g0; j < g1; ++j) {
+          const uint32_t x = b.grp[j];
+          r += x != i && witem_less<L>(b, x, i);
         }
+        b.ix[r] = (uint16_t)i;
       }
       wave_sync();
-      for (uint32_t jj = kk >> 2; jj >= 1; jj >>= 1) {
-        for (uint32_t t = lane; t < P / 2; t += 64) {
-          const uint32_t i = 2 * jj * (t / jj) + (t % jj), j = i + jj;
-          if (j < cnt && witem_less<L>(b, b.ix[j], b.ix[i])) {
-            const uint16_t x = b.ix[i];
-            b.ix[i] = b.ix[j];
-            b.ix[j] = x;
-          }
-        }
-        wave_sync();
-      }
+    } else {
+      for (uint32_t i = lane; i < cnt; i += 64) b.ix[i] = (uint16_t)i;
+      wave_sync();
+      wave_bitonic<L>(b, cnt);
     }
-    // run ends of equal keys are kept; 4 consecutive sorted positions per lane
-    uint32_t keep = 0;
-    KT<L> kv[4];
+    // run ends of equal keys are kept, a row of 64 sorted positions at a time
+    uint32_t m = 0;
+    int qmax = INT_MIN;  // max over the kept of home (in the block) - rank
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t r = lane * 4 + q;
-      if (r < cnt && (r + 1 == cnt || b.key[b.ix[r + 1]] != b.key[b.ix[r]])) {
-        keep |= 1u << q;
-        KT<L> v = b.val[b.ix[r]];
+    for (uint32_t q = 0; q < R; ++q) {
+      if (64 * q >= cnt) break;
+      const uint32_t r = lane + 64 * q;
+      const uint32_t x = r < cnt ? b.ix[r] : 0;
+      const KT<L> key = b.key[x];
+      const bool keep = r < cnt && (r + 1 == cnt || b.key[b.ix[r + 1]] != key);
+      const u64 keeps = __ballot(keep);
+      if (keep) {
+        KT<L> v = b.val[x];
         if (k.op == 1)
-          for (uint32_t r2 = r; r2 > 0 && b.key[b.ix[r2 - 1]] == b.key[b.ix[r]]; --r2) v += b.val[b.ix[r2 - 1]];
-        kv[q] = v;
+          for (uint32_t r2 = r; r2 > 0 && b.key[b.ix[r2 - 1]] == key; --r2) v += b.val[b.ix[r2 - 1]];
+        const uint32_t rank = m + (uint32_t)__popcll(keeps & ((1ull << lane) - 1));
+        const int qq = (int)(top_bits(b.u[x], k.log2c) & (B - 1)) - (int)rank;
+        qmax = qmax > qq ? qmax : qq;
+        keyB[(u64)off + rank] = key;
+        valB[(u64)off + rank] = v;
+        k.seqB[(u64)off + rank] = b.u[x];  // the hash, for the placement
       }
+      m += (uint32_t)__popcll(keeps);
     }
-    const uint32_t mine = (uint32_t)__popc(keep);
-    const uint32_t incl = wave_incl_scan(mine);
-    const uint32_t m = __shfl(incl, 63, 64);
-    uint32_t rank = incl - mine;
-    long long qmax = LLONG_MIN;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (!(keep >> q & 1u)) continue;
-      const uint32_t x = b.ix[lane * 4 + q];
-      const long long qq = (long long)top_bits(b.u[x], k.log2c) - (long long)rank;
-      qmax = qmax > qq ? qmax : qq;
-      keyB[(u64)off + rank] = b.key[x];
-      valB[(u64)off + rank] = kv[q];
-      k.seqB[(u64)off + rank] = b.u[x];  // the hash, for the placement
-      ++rank;
-    }
-    const long long mx = wave_max(qmax);
+    for (int o = 32; o > 0; o >>= 1) qmax = std::max(qmax, __shfl_xor(qmax, o, 64));
     if (lane == 0) {
       k.blk_cnt[blk] = m;
-      const long long s0 = (long long)(blk << k.log2b);
-      const long long a = m ? (long long)m + mx - s0 - (long long)B : 0;
+      const int a = m ? (int)m + qmax - (int)B : 0;
       k.car_a[blk] = a > 0 ? a : 0;
       k.car_d[blk] = (long long)m - (long long)B;
     }
@@ -1227,12 +1563,15 @@ hipError_t launch_bulk_merge(const BulkMergeArgs &a, hipStream_t s) {
       hipLaunchKernelGGL(KERN<1>, dim3(GRID), dim3(THREADS), 0, s, k);                 \
     if ((e = hipGetLastError()) != hipSuccess) return e;                               \
   } while (0)
-  LPHT_BM(k_bm_count, g.GA, 256);
+  LPHT_BM(k_bm_count, g.GA, 512);
   hipLaunchKernelGGL(k_bm_scan_rows, dim3(g.L1), dim3(256), 0, s, k);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(k_bm_scan_bins, dim3(1), dim3(1024), 0, s, k);
   if ((e = hipGetLastError()) != hipSuccess) return e;
+  // of each pair the one that the bins' sizes ask for runs, the other returns
+  LPHT_BM(k_bm_scatter_plain, g.GA, kThreadsP);
   LPHT_BM(k_bm_scatter, g.GA, 256);
+  LPHT_BM(k_bm_partition_plain, g.L1, 1024);
   LPHT_BM(k_bm_partition, g.L1, 1024);
   LPHT_BM(k_bm_block_wave, gwave, 256);
   LPHT_BM(k_bm_block, 256, 256);
