@@ -14,6 +14,7 @@
 #include "lpht_async.h"
 #include "lpht_bulk.h"
 #include "lpht_lane.h"
+#include "lpht_load.h"
 #include "lpht_part.h"
 #include "lpht_shrink.h"
 #include "lpht_special.h"
@@ -343,6 +344,22 @@ int run_bulk(lpht_table *t, OpKind op, const void *keys, const void *vals, uint6
   const uint64_t c = 1ull << t->log2c;
   // bound on used before this call (the growth rule already counted it)
   const uint64_t used0 = t->known_used + t->pending - (inserting ? n : 0);
+  if ((op == OP_INSERT || (op == OP_UPSERT && up == LPHT_ASSIGN)) &&
+      load_applies(n, t->log2c, t->cfg.layout, used0, flags != nullptr) && !capturing(s)) {
+    // loading a table that is nearly empty: region by region in LDS
+    const size_t sb = load_scratch_bytes(n, t->log2c, t->cfg.layout, flags != nullptr);
+    void *scratch = dev_alloc(t, sb, s);
+    if (scratch) {
+      const hipError_t e = launch_load(op, a, used0 == 0, scratch, s);
+      dev_free(t, scratch, sb, s);
+      if (e != hipSuccess) return from_hip(e);
+      if (t->special)
+        return from_hip(launch_special(t->cfg.layout, op, up, keys, vals, n, vals_out, flags, t->special,
+                                       t->special_scratch, false, s));
+      return LPHT_OK;
+    }
+    // no memory for it: one lane per operation
+  }
   bool by_fill = false;
   for (uint8_t g : t->tuning.g_modify) by_fill |= g != 0;
   const uint32_t kb = t->cfg.layout == LPHT_PACKED32 ? 4 : 8;

@@ -68,6 +68,9 @@ void dev_free(lpht_table *t, void *p, size_t bytes, hipStream_t s);
 void *pool_alloc(int device, size_t bytes, hipStream_t s, bool in_order = true);
 void pool_free(void *p, hipStream_t s);
 int release_pools();
+// Whether s is being captured into a graph (allocations then come from a pool
+// of their own, and calls keep to what they do without scratch).
+bool capturing(hipStream_t s);
 void fill_launch(lpht_table *t);
 bool tuning_ok(const lpht_tuning *u);
 bool within_fill(const lpht_table *t, uint64_t x, uint64_t c);

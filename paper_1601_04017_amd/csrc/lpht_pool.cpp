@@ -40,6 +40,16 @@
 namespace lpht {
 namespace host {
 
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    // the legacy stream while another one is captured: nothing is captured here
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
 namespace {
 
 constexpr int kMaxDevices = 64;
@@ -111,16 +121,6 @@ struct OnDevice {
     if (before >= 0) (void)hipSetDevice(before);
   }
 };
-
-bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-    // the legacy stream while another one is captured: nothing is captured here
-    (void)hipGetLastError();
-    return false;
-  }
-  return st != hipStreamCaptureStatusNone;
-}
 
 void spare(hipEvent_t ev) {
   if (ev) g_events.push_back(ev);
