@@ -33,8 +33,9 @@
 // would fill their buckets and be carried out one by one in the scatter), the
 // passes return at once and one lane per operation does the call.
 //
-// KV64, 10^8 distinct keys into an empty table of 2^28 cells: LOAD_BIG; PACKED32, 2^20 into 2^21
-// cells: LOAD_SMALL.
+// KV64, 10^8 distinct keys into an empty table of 2^28 cells: 5.84 -> 2.95 ms
+// (scatters 0.89 and 0.96 ms, 3.5 TB/s; apply 1.07 ms, 5.5 TB/s); PACKED32, 2^20
+// with flags into 2^21 cells: 69 -> 50 us.
 
 #include <hip/hip_runtime.h>
 
@@ -55,7 +56,7 @@ constexpr uint32_t kMaxBits = 9;             // buckets of one level: 512
 constexpr uint32_t kImageBytes = 64 * 1024;  // a region in LDS: two workgroups per CU
 constexpr uint32_t kApplyThreads = 1024;
 constexpr uint32_t kPad = 32;                // first-level counters on lines of their own
-constexpr uint64_t kMinOps = 1ull << 19;
+constexpr uint64_t kMinOps = 1ull << 20;
 constexpr uint64_t kMaxFlagged = 1ull << 23;
 constexpr uint64_t kSampled = 1ull << 22;
 
@@ -478,15 +479,30 @@ hipError_t enqueue(const LoadK &k, const Plan &p, hipStream_t s) {
 
 }  // namespace
 
+// Where the line lies (one lane per operation against this, us, the faster
+// last; both sides of the rule, distinct keys):
+//   KV64, 2^26 operations, empty table: c = 8 n 3844 / 2819, c = 4 n 3815 / 2109;
+//     2^24: c = 16 n 1.02 times as fast, 32 n 0.71;
+//   with n / 4 to n cells used before: c = 4 n 1.25 to 1.36 times, 8 n 0.78;
+//   flags, empty: c = 4 n 1.19 to 1.42 times, 8 n 0.97;
+//   2^20 operations, empty: c = 4 n 1.26 times (flags 1.09), 8 n 1.10 (0.93);
+//   2^19: 1.12 to 0.8 (0.99 to 0.75), too few for its launches;
+//   PACKED32, whose cells cost half: 2^22 operations, empty: c = 16 n 1.29 times,
+//     32 n 1.08; used before: c = 8 n 1.13, 16 n 0.75.
+// So the bytes of cells written (and read, unless empty) per operation decide,
+// half as many below 2^21 operations.
 bool load_applies(uint64_t n, uint32_t log2c, uint32_t layout, uint64_t used0, bool with_flags) {
   if (n < kMinOps || n >= (1ull << 31) || log2c > 34) return false;
   if (with_flags && n > kMaxFlagged) return false;
   const uint64_t c = 1ull << log2c;
   // at most 3/4 full afterwards, so that few probes leave their region
   if (used0 + n > c / 4 * 3) return false;
-  // per operation the partition and, per cell, the region's write (and read)
-  // against one compare-and-swap
-  if (used0 == 0 ? c > 8 * n : (c > 2 * n || used0 > n / 2)) return false;
+  // the batch may hold many keys of a table with more, and a present key costs
+  // a lane no more than a lookup (3 * 10^6 insert-or-assigns with flags, half of
+  // them present, on 3 * 10^6 of 2^23 cells: 187 us by lanes, 205 here)
+  if (used0 > n / 2) return false;
+  const uint64_t per_op = (used0 == 0 && !with_flags ? 128 : 64) / (n < 2 * kMinOps ? 2 : 1);
+  if ((layout == 0 ? 8 : 16) * c > per_op * n) return false;
   return plan_of(n, log2c, layout, with_flags).ok;
 }
 

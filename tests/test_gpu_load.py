@@ -15,7 +15,7 @@ from tests.gpu_util import cells_host, keys_dtype, to_dev, to_host
 pytestmark = pytest.mark.gpu
 
 LAYOUTS = [oracle.PACKED32, oracle.KV64]
-N0 = 1 << 19  # the smallest call
+N0 = 1 << 20  # the smallest call
 
 
 def _keys(layout, n, seed, absent=False):
@@ -38,7 +38,7 @@ def _same(t, o, layout, log2c):
 
 
 @pytest.mark.parametrize("layout", LAYOUTS)
-@pytest.mark.parametrize("n,log2c", [(N0, 20), (N0 + 1, 22), (1_000_003, 21), (1_100_000, 23)])
+@pytest.mark.parametrize("n,log2c", [(N0, 21), (N0 + 1, 21), (1_200_000, 21), (1_500_001, 22), ((1 << 22) + 1, 24)])
 @pytest.mark.parametrize("flags", [True, False])
 def test_distinct_keys_into_an_empty_table(layout, n, log2c, flags):
     dt = keys_dtype(layout)
@@ -56,10 +56,10 @@ def test_distinct_keys_into_an_empty_table(layout, n, log2c, flags):
 @pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("op", ["insert", "assign"])
 def test_elements_and_tombstones_already_there(layout, op):
-    # 2 * 10^5 elements, half of them erased, then 6 * 10^5 operations, some on
+    # 2 * 10^5 elements, half of them erased, then 1.12 * 10^6 operations, some on
     # live keys, some on erased ones, some reserved
     dt = keys_dtype(layout)
-    log2c = 20
+    log2c = 21
     t, o = _pair(layout, log2c)
     k0 = _keys(layout, 200_000, 5)
     t.insert(to_dev(k0), None)
@@ -67,7 +67,7 @@ def test_elements_and_tombstones_already_there(layout, op):
     t.erase(to_dev(k0[::2].copy()))
     o.erase(k0[::2].copy())
     t.count()  # (the host's bound on used cells becomes exact)
-    k = _keys(layout, 560_000, 6)
+    k = _keys(layout, 1_120_000, 6)
     k[1::3] = np.resize(k0, k[1::3].size)[:k[1::3].size]
     k[0] = 0
     k[100_000] = 1
@@ -107,7 +107,7 @@ def test_elements_and_tombstones_already_there(layout, op):
 def test_equal_keys(layout, distinct):
     # far more operations per bucket than its room, or many copies in each
     dt = keys_dtype(layout)
-    n, log2c = 700_001, 20
+    n, log2c = 1_400_001, 21
     rng = np.random.default_rng(distinct)
     base = _keys(layout, distinct, 8)
     k = base[rng.integers(0, distinct, n)]
@@ -129,7 +129,7 @@ def test_keys_crowded_at_the_end_of_regions():
     # multiplier 1: the position is the key's top bits; runs of keys at the last
     # cells of regions go on in the next region, and past the table's end
     from paper_1601_04017_amd import lpht
-    log2c, n = 20, N0 + 5
+    log2c, n = 21, N0 + 5
     rng = np.random.default_rng(3)
     c = 1 << log2c
     pos = rng.integers(0, c, n).astype(np.uint64)
