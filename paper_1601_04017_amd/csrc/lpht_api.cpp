@@ -133,8 +133,7 @@ int resize_empty(lpht_table *t, uint32_t log2_new, hipStream_t s, uint32_t steps
   const size_t nb = (size_t)cell_bytes(t->cfg.layout) << log2_new;
   void *nc = dev_alloc(t, nb, s);
   if (!nc) return LPHT_ERR_OOM;
-  hipError_t e = launch_fill_zero(nc, nb, t->launch, s);
-  if (e == hipSuccess) e = launch_set_status(t->status, 0, 0, 0, s);
+  hipError_t e = launch_clear(nc, nb, t->status, 0, s);
   if (e != hipSuccess) {
     dev_free(t, nc, nb, s);
     return from_hip(e);
@@ -610,12 +609,6 @@ int lpht_create(const lpht_config *cfg, void *stream, lpht_table **out) {
     delete t;
     return LPHT_ERR_OOM;
   }
-  hipError_t e = launch_set_status(t->status, 0, 0, 1, s);
-  if (e != hipSuccess) {
-    dev_free(t, t->status, sizeof(DevStatus), s);
-    delete t;
-    return from_hip(e);
-  }
   const size_t nb = (size_t)cell_bytes(cfg->layout) << cfg->log2_capacity;
   t->cells = dev_alloc(t, nb, s);
   if (!t->cells) {
@@ -625,7 +618,7 @@ int lpht_create(const lpht_config *cfg, void *stream, lpht_table **out) {
   }
   t->log2c = cfg->log2_capacity;
   t->log2_min = cfg->log2_capacity;
-  e = launch_fill_zero(t->cells, nb, t->launch, s);
+  hipError_t e = launch_clear(t->cells, nb, t->status, 1, s);
   if (e == hipSuccess && cfg->full_keys) {
     t->special = (SpecialSlots *)dev_alloc(t, sizeof(SpecialSlots), s);
     t->special_scratch = (uint32_t *)dev_alloc(t, kSpecialScratchBytes, s);
@@ -649,8 +642,7 @@ int lpht_clear(lpht_table *t, void *stream) {
   if (!t) return LPHT_ERR_INVALID;
   hipStream_t s = (hipStream_t)stream;
   if (hipSetDevice(t->device) != hipSuccess) return LPHT_ERR_DEVICE;
-  hipError_t e = launch_fill_zero(t->cells, (size_t)cell_bytes(t->cfg.layout) << t->log2c, t->launch, s);
-  if (e == hipSuccess) e = launch_set_status(t->status, 0, 0, 1, s);
+  hipError_t e = launch_clear(t->cells, (size_t)cell_bytes(t->cfg.layout) << t->log2c, t->status, 1, s);
   if (e == hipSuccess && t->special) e = launch_fill_zero(t->special, sizeof(SpecialSlots), t->launch, s);
   if (e != hipSuccess) return from_hip(e);
   t->known_used = t->known_live = 0;

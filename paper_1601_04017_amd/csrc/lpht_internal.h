@@ -85,6 +85,9 @@ hipError_t launch_bulk_multi(OpKind op, uint32_t up, uint32_t layout, const Bulk
                              const uint64_t *round_start, uint32_t ndesc, uint64_t total_rounds,
                              const LaunchCfg &cfg, hipStream_t s);
 hipError_t launch_fill_zero(void *ptr, uint64_t bytes, const LaunchCfg &cfg, hipStream_t s);
+// The cells of an empty table and its counts (and error bits, clear_err) in
+// one launch.
+hipError_t launch_clear(void *cells, uint64_t bytes, DevStatus *st, int clear_err, hipStream_t s);
 hipError_t launch_set_status(DevStatus *st, uint64_t used, uint64_t live, int clear_err,
                              hipStream_t s);
 hipError_t launch_recount(const void *cells, uint32_t log2c, uint32_t layout, DevStatus *st,

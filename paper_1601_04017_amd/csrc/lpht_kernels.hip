@@ -682,9 +682,8 @@ __global__ void k_fill_zero(u64x2 *p, u64 n16) {
     __builtin_nontemporal_store(z, p + i);
 }
 
-__global__ void k_set_status(DevStatus *st, u64 used, u64 live, int clear_err) {
+__device__ __forceinline__ void set_status(DevStatus *st, u64 used, u64 live, int clear_err) {
   const uint32_t t = threadIdx.x;
-  if (blockIdx.x != 0) return;
   if (t < kCountSlots) {
     st->slot[t].used = t == 0 ? used : 0;
     st->slot[t].live = t == 0 ? live : 0;
@@ -693,6 +692,18 @@ __global__ void k_set_status(DevStatus *st, u64 used, u64 live, int clear_err) {
     st->overflow = 0;
     if (clear_err) st->err = 0;
   }
+}
+
+__global__ void k_set_status(DevStatus *st, u64 used, u64 live, int clear_err) { set_status(st, used, live, clear_err); }
+
+// An empty table: zeroed cells, and the counts by the first workgroup (a
+// launch of its own for them cost a small table's clear half of its time).
+__global__ void k_clear(u64x2 *p, u64 n16, DevStatus *st, int clear_err) {
+  if (blockIdx.x == 0) set_status(st, 0, 0, clear_err);
+  const u64 stride = (u64)gridDim.x * blockDim.x;
+  const u64x2 z = {0ull, 0ull};
+  for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += stride)
+    __builtin_nontemporal_store(z, p + i);
 }
 
 // Zeroes `n16` 16-byte units when the migration overflow flag is set (and
@@ -1605,17 +1616,28 @@ hipError_t launch_bulk(OpKind op, const BulkArgs &a, const LaunchCfg &cfg, hipSt
   return a.layout == 0 ? launch_layout<0>(op, a, cfg, s) : launch_layout<1>(op, a, cfg, s);
 }
 
+// A pure store stream needs many more stores in flight than the table
+// kernels' grid gives: one store per thread up to 1024 workgroups, then about
+// 16 per thread, up to 65536 workgroups (a 4 GiB fill: 4.0 TB/s with 2048 x 512
+// threads, 6.0 TB/s like this).
+static uint32_t fill_blocks(u64 n16) {
+  const u64 few = std::min<u64>((n16 + 255) / 256, 1024), many = (n16 + 256 * 16 - 1) / (256 * 16);
+  return (uint32_t)std::min<u64>(std::max(few, many), 65536);
+}
+
+hipError_t launch_clear(void *cells, uint64_t bytes, DevStatus *st, int clear_err, hipStream_t s) {
+  drop_stale_error();
+  const u64 n16 = bytes / 16;
+  hipLaunchKernelGGL(k_clear, dim3(fill_blocks(n16)), dim3(256), 0, s, (u64x2 *)cells, n16, st, clear_err);
+  return hipGetLastError();
+}
+
 hipError_t launch_fill_zero(void *ptr, uint64_t bytes, const LaunchCfg &cfg, hipStream_t s) {
   drop_stale_error();
   (void)cfg;
   u64 n16 = bytes / 16;
   if (n16 == 0) return hipSuccess;
-  // A pure store stream needs many more stores in flight than the table
-  // kernels' grid gives: about 16 stores per thread, up to 65536 workgroups
-  // (a 4 GiB fill: 4.0 TB/s with 2048 x 512 threads, 6.0 TB/s like this).
-  u64 blocks = (n16 + 256 * 16 - 1) / (256 * 16);
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(k_fill_zero, dim3((uint32_t)blocks), dim3(256), 0, s, (u64x2 *)ptr, n16);
+  hipLaunchKernelGGL(k_fill_zero, dim3(fill_blocks(n16)), dim3(256), 0, s, (u64x2 *)ptr, n16);
   return hipGetLastError();
 }
 
