@@ -10,14 +10,15 @@
 // start at 8, so no reference is 0 or 1.
 //
 // A pool record is a 32-bit length followed by the bytes, rounded up to 8
-// bytes.  Records are allocated by bumping a device cursor; an insertion
-// writes its record, makes it visible (release fence), then publishes the
-// reference with compare-and-swap; a reader that meets a reference written
-// during its own launch fences (acquire) before reading the record.  Records
-// of erased keys, and the rare
-// record of an insertion that lost a race to an equal key, stay in the pool
-// until the next migration, which copies only live keys into a new pool
-// (the paper reclaims key space when the array is migrated).
+// bytes.  Records are allocated by bumping a device cursor.  An inserting call
+// takes two launches: the first looks every key up and writes the records of
+// the absent ones, the second publishes their references with
+// compare-and-swap.  The boundary between them makes the records visible, so
+// no operation fences (an agent-scope release writes back the XCD's L2).
+// Records of erased keys, and of insertions that lost to an equal key of the
+// same call, stay in the pool until the next migration, which copies only live
+// keys into a new pool (the paper reclaims key space when the array is
+// migrated).
 //
 // The hash is the pair of CRC-32C register updates over the key's bytes with
 // the two seeds (Sec. 8.3), the same function as for word keys.
@@ -89,21 +90,16 @@ __device__ __forceinline__ void rec_write(uint8_t *pool, u64 off, const uint8_t 
   for (; i < len; ++i) r[i] = s[i];
 }
 
-__device__ __forceinline__ u64 ld_ref(const u64 *cells, u64 p) {
-  return __hip_atomic_load(cells + 2 * p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// A cell: reference and value.  Plain loads: within a launch a cell only goes
+// from empty to a reference (insertions) or from a reference to the tombstone
+// (erases), each by compare-and-swap, and a probe that read the cell before
+// learns so from its own compare-and-swap.
+__device__ __forceinline__ u64x2 ld_cell(const void *cells, u64 p) { return ((const u64x2 *)cells)[p]; }
 
-// Whether the cell's reference word r names the key s[0..len).  Records at
-// pool offsets below `fresh_from` were written by earlier launches, which
-// the kernel boundary has made visible; a record this launch may have
-// written is read after an acquire fence, which pairs with the writer's
-// release fence before its compare-and-swap.
-__device__ __forceinline__ bool same_key(const uint8_t *pool, u64 r, u64 sig, const uint8_t *s, u64 len,
-                                         u64 fresh_from) {
-  if (r == kTomb || (r >> 48) != sig) return false;
-  const u64 off = r & kOffMask;
-  if (off >= fresh_from) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  return rec_equal(pool, off, s, len);
+// Whether the cell's reference word r names the key s[0..len).  Every record
+// that a reference names was written by an earlier launch.
+__device__ __forceinline__ bool same_key(const uint8_t *pool, u64 r, u64 sig, const uint8_t *s, u64 len) {
+  return r != kTomb && (r >> 48) == sig && rec_equal(pool, r & kOffMask, s, len);
 }
 
 // Exclusive prefix sum of v over the wavefront's 64 lanes (all active);
@@ -119,146 +115,172 @@ __device__ __forceinline__ u64 wave_excl_scan(u64 v, u64 &total) {
   return x - v;
 }
 
-// Operations per lane between release fences in inserting launches: the
-// fence writes back the L2 and costs far more than a probe.
-constexpr int kStrGroup = 8;
-
-// A lane takes K operations (K = kStrGroup when inserting, else 1); for each
-// a read-only probe ends at the key or at the first empty cell.  Inserting
-// operations that ended at an empty cell then take their records from one
-// pool allocation per wavefront, write them, make them visible with one
-// release fence per wavefront, and publish their references with
-// compare-and-swap from that cell on; a lost race continues the probe, and
-// finding the key there leaves the record unused until the next migration.
-template <int KIND>
-__global__ void __launch_bounds__(256) k_str_op(StrArgs a) {
-  constexpr bool kInserting = KIND == kStrInsert || KIND == kStrUpsert;
-  constexpr int K = kInserting ? kStrGroup : 1;
-  __shared__ uint32_t T[8][256];
-  crc_tables_build(T);
-  const u64 mask = (1ull << a.log2c) - 1;
-  u64 *cells = (u64 *)a.cells;
-  // A table is used from one stream at a time, so only an inserting launch
-  // can meet a record written while it runs.
-  const u64 fresh_from = kInserting ? a.ctl->pool_start : ~0ull;
-  const u64 stride = (u64)gridDim.x * blockDim.x * K;
-  uint32_t err = 0;
-  // the bound is uniform over the workgroup: every lane reaches the
-  // wavefront's allocation, idle lanes with nothing to allocate
-  for (u64 i0 = (u64)blockIdx.x * blockDim.x * K; i0 < a.n; i0 += stride) {
-    u64 len[K], sig[K], p[K], step[K], r[K], d[K], mine[K];
-    const uint8_t *s[K];
-    bool found[K], at_empty[K];
-    uint8_t flag[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const u64 i = i0 + (u64)j * blockDim.x + threadIdx.x;
-      len[j] = sig[j] = p[j] = step[j] = mine[j] = 0;
-      r[j] = kEmpty;
-      d[j] = 1;
-      s[j] = nullptr;
-      found[j] = at_empty[j] = false;
-      flag[j] = kInserting ? 0xFF : 0;
-      if (i >= a.n) continue;
-      const u64 o0 = a.offsets[i];
-      len[j] = a.offsets[i + 1] - o0;
-      s[j] = a.bytes + o0;
-      if (a.vals) d[j] = a.vals[i];
-      const u64 h = str_hash(T, s[j], len[j], a.crc_hi, a.crc_lo);
-      sig[j] = h & 0xFFFFull;
-      p[j] = h >> (64 - a.log2c);
-      for (; step[j] <= mask; ++step[j], p[j] = (p[j] + 1) & mask) {
-        r[j] = ld_ref(cells, p[j]);
-        if (r[j] == kEmpty) {
-          at_empty[j] = true;
-          break;
-        }
-        if (same_key(a.pool, r[j], sig[j], s[j], len[j], fresh_from)) {
-          found[j] = true;
-          break;
-        }
-      }
+// Looks a key up: the cell that holds it (found) or the empty cell its probe
+// ended at; neither: every cell holds another key.
+struct StrProbe {
+  u64 p, r, v, sig;  // r, v: the cell's words
+  bool found, at_empty;
+};
+__device__ __forceinline__ StrProbe str_probe(const StrArgs &a, const uint32_t (*T)[256], const uint8_t *s, u64 len) {
+  const u64 mask = (1ull << a.log2c) - 1, h = str_hash(T, s, len, a.crc_hi, a.crc_lo);
+  StrProbe q{h >> (64 - a.log2c), kEmpty, 0, h & 0xFFFFull, false, false};
+  for (u64 step = 0; step <= mask; ++step, q.p = (q.p + 1) & mask) {
+    const u64x2 c = ld_cell(a.cells, q.p);
+    q.r = c.x;
+    q.v = c.y;
+    if (q.r == kEmpty) {
+      q.at_empty = true;
+      break;
     }
-    if (kInserting) {
-      // one allocation per wavefront, laid out by j: the records of the
-      // wavefront's j-th operations are consecutive
-      u64 total = 0;
-#pragma unroll
-      for (int j = 0; j < K; ++j) total += (u64)wave_sum((long long)(at_empty[j] ? rec_bytes(len[j]) : 0));
-      u64 base = 0;
-      if ((threadIdx.x & 63) == 0 && total)
-        base = atomicAdd((unsigned long long *)&a.ctl->pool_used, (unsigned long long)total);
-      base = __shfl(base, 0, 64);
-      bool wrote = false;
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        const u64 need = at_empty[j] ? rec_bytes(len[j]) : 0;
-        u64 tj;
-        const u64 off = base + wave_excl_scan(need, tj);
-        base += tj;
-        if (!need) continue;
-        if (off + need > a.pool_cap) {
-          err |= kErrFull;  // flag stays 0xFF
-        } else {
-          rec_write(a.pool, off, s[j], len[j]);
-          mine[j] = (sig[j] << 48) | off;
-          wrote = true;
-        }
-      }
-      if (wrote) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        if (!mine[j]) continue;
-        // cell p[j] was empty when the probe passed it
-        for (r[j] = kEmpty; step[j] <= mask; ++step[j], p[j] = (p[j] + 1) & mask, r[j] = ld_ref(cells, p[j])) {
-          if (r[j] == kEmpty) {
-            const u64 prev = cas64(cells + 2 * p[j], kEmpty, mine[j]);
-            if (prev == kEmpty) {
-              if (KIND == kStrInsert || a.up == 0)
-                __hip_atomic_store(cells + 2 * p[j] + 1, d[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              else
-                add64(cells + 2 * p[j] + 1, d[j]);
-              flag[j] = 1;
-              break;
-            }
-            r[j] = prev;
-          }
-          if (same_key(a.pool, r[j], sig[j], s[j], len[j], fresh_from)) {
-            found[j] = true;
-            break;
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const u64 i = i0 + (u64)j * blockDim.x + threadIdx.x;
-      if (i >= a.n) continue;
-      u64 out = 0;
-      if (found[j]) {
-        // the key is present in cell p[j], whose reference word is r[j]
-        const u64 q = p[j];
-        if (KIND == kStrFind) {
-          out = __hip_atomic_load(cells + 2 * q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          flag[j] = 1;
-        } else if (KIND == kStrErase) {
-          flag[j] = cas64(cells + 2 * q, r[j], kTomb) == r[j] ? 1 : 0;
-        } else {
-          if (KIND == kStrUpsert) {
-            if (a.up == 0)
-              __hip_atomic_store(cells + 2 * q + 1, d[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else
-              add64(cells + 2 * q + 1, d[j]);
-          }
-          flag[j] = 0;
-        }
-      }
-      if (kInserting && flag[j] == 0xFF) err |= kErrFull;
-      if (a.flags) a.flags[i] = flag[j];
-      if (KIND == kStrFind && a.vals_out) a.vals_out[i] = out;
+    if (same_key(a.pool, q.r, q.sig, s, len)) {
+      q.found = true;
+      break;
     }
   }
+  return q;
+}
+
+// The value of the present key in cell p.
+template <int KIND>
+__device__ __forceinline__ void str_update(const StrArgs &a, u64 p, u64 d) {
+  if (KIND != kStrUpsert) return;
+  u64 *v = (u64 *)a.cells + 2 * p + 1;
+  if (a.up == 0)
+    __hip_atomic_store(v, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    add64(v, d);
+}
+
+// Finds and erases, one lane each.
+template <int KIND>
+__global__ void __launch_bounds__(256) k_str_op(StrArgs a) {
+  __shared__ uint32_t T[8][256];
+  crc_tables_build(T);
+  u64 *cells = (u64 *)a.cells;
+  const u64 stride = (u64)gridDim.x * blockDim.x;
+  for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < a.n; i += stride) {
+    const u64 o0 = a.offsets[i];
+    const StrProbe q = str_probe(a, T, a.bytes + o0, a.offsets[i + 1] - o0);
+    uint8_t flag = 0;
+    u64 out = 0;
+    if (q.found) {
+      if (KIND == kStrFind) {
+        out = q.v;
+        flag = 1;
+      } else {
+        flag = cas64(cells + 2 * q.p, q.r, kTomb) == q.r ? 1 : 0;
+      }
+    }
+    if (a.flags) a.flags[i] = flag;
+    if (KIND == kStrFind && a.vals_out) a.vals_out[i] = out;
+  }
+}
+
+// What the first launch of an inserting call leaves for the second: the
+// reference of the operation's record (0: the operation is done) and the empty
+// cell its probe ended at.
+typedef u64x2 Staged;
+
+// First launch, one lane per operation: present keys are done here, absent
+// ones get a record.  One addition to the pool's cursor per workgroup (of 1024:
+// every addition is 12 ns on the one line, 2 * 10^6 operations by wavefronts
+// would be 375 us).
+//
+// Bound: random lines (cell, and record for hits) and the latency of each key's
+// chain of loads, which one operation per lane and full occupancy hide: eight
+// operations per lane, one after the other, with one fence per wavefront took
+// 502 us for 2 * 10^6 keys of 8 to 40 bytes in 2^23 cells, the two launches
+// 296 us.
+template <int KIND>
+__global__ void __launch_bounds__(1024, 8) k_str_stage(StrArgs a, Staged *staged) {
+  __shared__ uint32_t T[8][256];
+  __shared__ u64 s_w[16];
+  crc_tables_build(T);
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const u64 stride = (u64)gridDim.x * blockDim.x;
+  uint32_t err = 0;
+  // the bound is uniform over the workgroup, which allocates together
+  for (u64 i0 = (u64)blockIdx.x * blockDim.x; i0 < a.n; i0 += stride) {
+    const u64 i = i0 + threadIdx.x;
+    const uint8_t *s = nullptr;
+    u64 len = 0, need = 0;
+    StrProbe q{};
+    uint8_t flag = 0xFF;
+    if (i < a.n) {
+      const u64 o0 = a.offsets[i];
+      len = a.offsets[i + 1] - o0;
+      s = a.bytes + o0;
+      q = str_probe(a, T, s, len);
+      if (q.found) {
+        str_update<KIND>(a, q.p, a.vals ? a.vals[i] : 1);
+        flag = 0;
+      }
+      need = q.at_empty ? rec_bytes(len) : 0;
+    }
+    u64 total;
+    u64 off = wave_excl_scan(need, total);
+    if (lane == 0) s_w[wave] = total;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      u64 sum = 0;
+      for (uint32_t w = 0; w < 16; ++w) {
+        const u64 t = s_w[w];
+        s_w[w] = sum;
+        sum += t;
+      }
+      const u64 base = sum ? atomicAdd((unsigned long long *)&a.ctl->pool_used, (unsigned long long)sum) : 0;
+      for (uint32_t w = 0; w < 16; ++w) s_w[w] += base;
+    }
+    __syncthreads();
+    off += s_w[wave];
+    __syncthreads();  // read before the next round writes it
+    if (i >= a.n) continue;
+    Staged out = {0, q.p};
+    if (need && off + need <= a.pool_cap) {
+      rec_write(a.pool, off, s, len);
+      out.x = (q.sig << 48) | off;
+    } else if (flag == 0xFF) {
+      err |= kErrFull;  // no cell, or no room in the pool
+    }
+    staged[i] = out;
+    if (!out.x && a.flags) a.flags[i] = flag;
+  }
   if (err) atomicOr(&a.ctl->err, err);
+}
+
+// Second launch: the records' references are published from the empty cell
+// on; an equal key of the call that was faster is met on the way.
+template <int KIND>
+__global__ void __launch_bounds__(256) k_str_publish(StrArgs a, const Staged *staged) {
+  const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= a.n) return;
+  const Staged st = staged[i];
+  if (!st.x) return;
+  const u64 mask = (1ull << a.log2c) - 1, sig = st.x >> 48, off = st.x & kOffMask;
+  const u64 d = a.vals ? a.vals[i] : 1;
+  u64 *cells = (u64 *)a.cells;
+  uint8_t flag = 0xFF;
+  u64 p = st.y, r = kEmpty;
+  for (u64 step = 0; step <= mask; ++step, p = (p + 1) & mask, r = cells[2 * p]) {
+    if (r == kEmpty) {
+      r = cas64(cells + 2 * p, kEmpty, st.x);
+      if (r == kEmpty) {
+        if (KIND == kStrInsert || a.up == 0)
+          __hip_atomic_store(cells + 2 * p + 1, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+          add64(cells + 2 * p + 1, d);
+        flag = 1;
+        break;
+      }
+    }
+    if (same_key(a.pool, r, sig, a.pool + off + 4, *(const uint32_t *)(a.pool + off))) {
+      str_update<KIND>(a, p, d);
+      flag = 0;
+      break;
+    }
+  }
+  if (flag == 0xFF) atomicOr(&a.ctl->err, kErrFull);
+  if (a.flags) a.flags[i] = flag;
 }
 
 // Migration: every live key of the old table is copied into the new pool
@@ -321,11 +343,6 @@ __global__ void __launch_bounds__(256) k_str_recount(const u64 *cells, u64 cap, 
   }
 }
 
-// Marks where records of the next launch will start.
-__global__ void k_str_snap(StrCtl *ctl) {
-  if (threadIdx.x == 0) ctl->pool_start = ctl->pool_used;
-}
-
 __global__ void k_str_ctl(StrCtl *ctl, u64 pool_used, int keep_pool) {
   if (threadIdx.x == 0) {
     ctl->used = 0;
@@ -345,21 +362,38 @@ uint32_t grid_of(u64 items, uint32_t num_cus) {
 
 hipError_t launch_str_op(int kind, const StrArgs &a, uint32_t num_cus, hipStream_t s) {
   drop_stale_error();
-  const bool inserting = kind == kStrInsert || kind == kStrUpsert;
-  const uint32_t g = grid_of(inserting ? (a.n + kStrGroup - 1) / kStrGroup : a.n, num_cus);
-  if (inserting) {
-    hipLaunchKernelGGL(k_str_snap, dim3(1), dim3(64), 0, s, a.ctl);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+  const uint32_t g = grid_of(a.n, num_cus);
   switch (kind) {
-    case kStrInsert: hipLaunchKernelGGL(k_str_op<kStrInsert>, dim3(g), dim3(256), 0, s, a); break;
-    case kStrUpsert: hipLaunchKernelGGL(k_str_op<kStrUpsert>, dim3(g), dim3(256), 0, s, a); break;
     case kStrFind: hipLaunchKernelGGL(k_str_op<kStrFind>, dim3(g), dim3(256), 0, s, a); break;
     case kStrErase: hipLaunchKernelGGL(k_str_op<kStrErase>, dim3(g), dim3(256), 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_str_insert(int kind, const StrArgs &all, void *scratch, uint32_t num_cus, hipStream_t s) {
+  drop_stale_error();
+  if (kind != kStrInsert && kind != kStrUpsert) return hipErrorInvalidValue;
+  for (u64 lo = 0; lo < all.n; lo += kStrSlice) {
+    StrArgs a = all;
+    a.n = all.n - lo < kStrSlice ? all.n - lo : kStrSlice;
+    a.offsets = all.offsets + lo;
+    a.vals = all.vals ? all.vals + lo : nullptr;
+    a.flags = all.flags ? all.flags + lo : nullptr;
+    const u64 want = (a.n + 1023) / 1024, most = 2ull * (num_cus ? num_cus : 1);
+    const uint32_t gs = (uint32_t)(want < most ? want : most), gp = (uint32_t)((a.n + 255) / 256);
+    Staged *st = (Staged *)scratch;
+    if (kind == kStrInsert) {
+      hipLaunchKernelGGL(k_str_stage<kStrInsert>, dim3(gs), dim3(1024), 0, s, a, st);
+      hipLaunchKernelGGL(k_str_publish<kStrInsert>, dim3(gp), dim3(256), 0, s, a, (const Staged *)st);
+    } else {
+      hipLaunchKernelGGL(k_str_stage<kStrUpsert>, dim3(gs), dim3(1024), 0, s, a, st);
+      hipLaunchKernelGGL(k_str_publish<kStrUpsert>, dim3(gp), dim3(256), 0, s, a, (const Staged *)st);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_str_migrate(const StrMigArgs &a, uint32_t num_cus, hipStream_t s) {

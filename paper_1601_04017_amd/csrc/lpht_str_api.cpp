@@ -107,11 +107,9 @@ int migrate(lpht_str_table *t, uint32_t log2_new, uint64_t new_pool_cap, hipStre
 
 // The word tables' growth rule (trigger at alpha on non-empty cells; cleanup
 // that may shrink when live + b <= alpha c / 2; else doubling), plus room in
-// the pool for `bytes` more record bytes.
-int grow_before(lpht_str_table *t, uint64_t b, uint64_t bytes, hipStream_t s) {
+// the pool, of which `pused` bytes are handed out, for `bytes` more record bytes.
+int grow_before(lpht_str_table *t, uint64_t b, uint64_t pused, uint64_t bytes, hipStream_t s) {
   int rc = LPHT_OK;
-  const uint64_t pused = pool_cursor(t, s, &rc);
-  if (rc) return rc;
   const bool pool_ok = pused + bytes <= t->pool_cap;
   const uint64_t c = 1ull << t->log2c;
   if (pool_ok && (!t->cfg.auto_grow || fits(t, t->known_used + t->pending + b, c))) {
@@ -163,13 +161,15 @@ int run(lpht_str_table *t, int kind, const uint8_t *bytes, const uint64_t *offse
   if (hipSetDevice(t->device) != hipSuccess) return LPHT_ERR_DEVICE;
   if (kind == kStrInsert || kind == kStrUpsert) {
     uint64_t o[2];
+    unsigned long long pused = 0;
     hipError_t e = hipMemcpyAsync(&o[0], offsets, 8, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipMemcpyAsync(&o[1], offsets + n, 8, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&pused, &t->ctl->pool_used, sizeof(pused), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return from_hip(e);
     if (o[1] < o[0]) return LPHT_ERR_INVALID;
     // each record takes at most its length + 11 bytes
-    const int rc = grow_before(t, n, (o[1] - o[0]) + 12 * n, s);
+    const int rc = grow_before(t, n, pused, (o[1] - o[0]) + 12 * n, s);
     if (rc) return rc;
   }
   StrArgs a{};
@@ -187,7 +187,12 @@ int run(lpht_str_table *t, int kind, const uint8_t *bytes, const uint64_t *offse
   a.vals = vals;
   a.vals_out = vals_out;
   a.flags = flags;
-  return from_hip(launch_str_op(kind, a, t->num_cus, s));
+  if (kind == kStrFind || kind == kStrErase) return from_hip(launch_str_op(kind, a, t->num_cus, s));
+  void *scratch = alloc(t, std::min(n, kStrSlice) * 16, s);
+  if (!scratch) return LPHT_ERR_OOM;
+  const hipError_t e = launch_str_insert(kind, a, scratch, t->num_cus, s);
+  release(scratch, s);
+  return from_hip(e);
 }
 
 }  // namespace
