@@ -95,6 +95,45 @@ __device__ __forceinline__ u64 hash_direct(u64 key, uint32_t crc_hi, uint32_t cr
   return ((u64)(c ^ crc_hi) << 32) | (u64)(c ^ crc_lo);
 }
 
+// Slicing by four: the first four of the tables above, 4 KiB, copied to LDS
+// from constant data (a short launch builds nothing).  Eight lookups a 64-bit
+// key as with eight tables, the second four after the first; about 40 VALU
+// instructions in place of crc0_bits' 130, for kernels whose keys keep the
+// VALU busy.
+struct CrcSlices {
+  uint32_t t[4 * 256];
+};
+constexpr CrcSlices crc_slices() {
+  CrcSlices s{};
+  for (uint32_t b = 0; b < 256; ++b) {
+    uint32_t r = b;
+    for (int k = 0; k < 8; ++k) r = (r >> 1) ^ (kPolyRefl & (0u - (r & 1u)));
+    s.t[b] = r;
+  }
+  for (int j = 1; j < 4; ++j)
+    for (uint32_t b = 0; b < 256; ++b) {
+      const uint32_t r = s.t[(j - 1) * 256 + b];
+      s.t[j * 256 + b] = (r >> 8) ^ s.t[r & 0xFFu];
+    }
+  return s;
+}
+static __device__ const CrcSlices kCrcSlices = crc_slices();
+
+// T: 1024 words of LDS; a barrier must follow.
+__device__ __forceinline__ void crc_slices_load(uint32_t *T) {
+  for (uint32_t i = threadIdx.x; i < 1024; i += blockDim.x) T[i] = kCrcSlices.t[i];
+}
+__device__ __forceinline__ uint32_t crc0_sliced(const uint32_t *T, uint32_t x) {
+  return T[3 * 256 + (x & 0xFF)] ^ T[2 * 256 + ((x >> 8) & 0xFF)] ^ T[256 + ((x >> 16) & 0xFF)] ^ T[x >> 24];
+}
+template <int LAYOUT>
+__device__ __forceinline__ u64 hash_sliced(const uint32_t *T, u64 key, uint32_t crc_hi, uint32_t crc_lo, u64 mul) {
+  if (mul) return key * mul;
+  uint32_t c = crc0_sliced(T, (uint32_t)key);
+  if (LAYOUT == 1) c = crc0_sliced(T, c ^ (uint32_t)(key >> 32));
+  return ((u64)(c ^ crc_hi) << 32) | (u64)(c ^ crc_lo);
+}
+
 // The table's 64-bit hash of a key.  mul == 0: the CRC-32C pair
 // h = CRC(seed_hi, x) * 2^32 + CRC(seed_lo, x) (Sec. 8.3), where the CRC
 // register update is linear over GF(2), so CRC(seed, x) = CRC(0, x) ^

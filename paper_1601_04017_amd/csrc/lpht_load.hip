@@ -35,7 +35,11 @@
 //
 // KV64, 10^8 distinct keys into an empty table of 2^28 cells: 5.84 -> 2.95 ms
 // (scatters 0.89 and 0.96 ms, 3.5 TB/s; apply 1.07 ms, 5.5 TB/s); PACKED32, 2^20
-// with flags into 2^21 cells: 69 -> 50 us.
+// with flags into 2^21 cells: 69 -> 50 us.  Scatter and apply hash by sliced
+// tables in LDS: with the lanes' direct hash (130 VALU instructions a key) they
+// were bound by the VALU where the batch is small (a pass of 2^20 PACKED32
+// insertions with flags and their finds: 102 -> 98 us; 3 * 10^6 KV64 inserted,
+// assigned, found and erased: 652 -> 624 us).
 
 #include <hip/hip_runtime.h>
 
@@ -60,10 +64,8 @@ constexpr uint64_t kMinOps = 1ull << 20;
 constexpr uint64_t kMaxFlagged = 1ull << 23;
 constexpr uint64_t kSampled = 1ull << 22;
 
-// region cells: 8192 of 8 bytes, 4096 of 16; and the most operations a region
-// has room for (three quarters of its cells and eight standard deviations)
+// region cells: 8192 of 8 bytes, 4096 of 16
 constexpr uint32_t region_bits(uint32_t layout) { return layout == 0 ? 13 : 12; }
-constexpr uint32_t kMaxLast[2] = {7168, 4096};
 
 template <int L>
 using Elem = typename std::conditional<L == 0, u64, u64x2>::type;
@@ -153,9 +155,11 @@ __global__ void __launch_bounds__((scatter_threads<L, IDX>()), 4) k_load_scatter
   __shared__ Elem<L> buf[kTile];
   __shared__ uint32_t ibuf[IDX ? kTile : 1];
   __shared__ uint16_t bkt[kTile];
-  __shared__ uint32_t toff[NB], gbase[NB];
+  __shared__ uint32_t toff[NB];  // by bucket: elements, their start in the tile, then start in the room less that
+  __shared__ uint32_t T[1024];
   __shared__ uint32_t s_w[NT / 64];
   if (k.ctl->skewed) return;
+  crc_slices_load(T);
   const BulkArgs &A = k.A;
   const uint32_t nb = 1u << k.bits[LV], lane = threadIdx.x & 63;
   // this workgroup's elements [base, base + m) of the batch or of bucket b of
@@ -208,13 +212,14 @@ __global__ void __launch_bounds__((scatter_threads<L, IDX>()), 4) k_load_scatter
       if (IDX) A.flags[ix[j]] = ok[j] ? 1 : 0xFE;
     }
     if (ok[j]) {
-      const u64 pos = hash_direct<L>(elem_key<L>(e[j]), A.crc_hi, A.crc_lo, A.mul) >> (64 - A.log2c);
+      const u64 pos = hash_sliced<L>(T, elem_key<L>(e[j]), A.crc_hi, A.crc_lo, A.mul) >> (64 - A.log2c);
       const uint32_t region = (uint32_t)(pos >> k.rbits);
       const uint32_t bk = LV == 0 ? region >> k.bits[1] : region & (nb - 1);
       at[j] = bk | (atomicAdd(&toff[bk], 1u) << 16);
     }
   }
   __syncthreads();
+  uint32_t room_at = 0;
   {
     // where each bucket's elements begin in the tile, and in the bucket
     const uint32_t c = threadIdx.x < nb ? toff[threadIdx.x] : 0;
@@ -230,10 +235,8 @@ __global__ void __launch_bounds__((scatter_threads<L, IDX>()), 4) k_load_scatter
     __syncthreads();
     uint32_t before = 0;
     for (uint32_t w = 0; w < (threadIdx.x >> 6); ++w) before += s_w[w];
-    if (threadIdx.x < nb) {
-      toff[threadIdx.x] = before + x - c;
-      gbase[threadIdx.x] = g;
-    }
+    if (threadIdx.x < nb) toff[threadIdx.x] = before + x - c;
+    room_at = g - (before + x - c);
   }
   __syncthreads();
   uint32_t total = 0;
@@ -247,13 +250,15 @@ __global__ void __launch_bounds__((scatter_threads<L, IDX>()), 4) k_load_scatter
     if (IDX) ibuf[p] = ix[j];
   }
   __syncthreads();
+  if (threadIdx.x < nb) toff[threadIdx.x] = room_at;
+  __syncthreads();
   const uint32_t cap = k.cap[LV];
   uint32_t hits = 0;
   for (uint32_t i0 = 0; i0 < total; i0 += NT) {
     const uint32_t i = i0 + threadIdx.x;
     bool spill = false;
     if (i < total) {
-      const uint32_t bk = bkt[i], q = gbase[bk] + (i - toff[bk]);
+      const uint32_t bk = bkt[i], q = toff[bk] + i;
       spill = q >= cap;
       if (!spill) {
         const u64 to = (((LV == 0 ? 0ull : (u64)b << k.bits[1]) + bk) * cap) + q;
@@ -284,7 +289,7 @@ __global__ void __launch_bounds__((scatter_threads<L, IDX>()), 4) k_load_scatter
 template <int L, int OP, bool IDX>
 __global__ void __launch_bounds__(kApplyThreads) k_load_apply(LoadK k) {
   __shared__ __attribute__((aligned(16))) u64 img[kImageBytes / 8];  // the region's cells
-  __shared__ uint16_t late[kMaxLast[L]];                             // elements put off
+  __shared__ uint32_t T[1024];
   __shared__ uint32_t s_hits, s_off;
   if (k.ctl->skewed) return;
   const BulkArgs &A = k.A;
@@ -301,6 +306,7 @@ __global__ void __launch_bounds__(kApplyThreads) k_load_apply(LoadK k) {
     if (threadIdx.x == 0) k.n_put_off[r] = 0;
     return;
   }
+  crc_slices_load(T);
   const bool fresh = k.fresh && !k.ctl->spilled;
   u64x2 *cells = (u64x2 *)((unsigned char *)A.cells + (u64)r * kImageBytes);
   constexpr uint32_t N16 = kImageBytes / 16, PER = N16 / kApplyThreads;
@@ -324,10 +330,10 @@ __global__ void __launch_bounds__(kApplyThreads) k_load_apply(LoadK k) {
     const Elem<L> e = next;
     if (i + kApplyThreads < m) next = src[i + kApplyThreads];
     const u64 key = elem_key<L>(e), val = elem_val<L>(e);
-    uint32_t p = (uint32_t)(hash_direct<L>(key, A.crc_hi, A.crc_lo, A.mul) >> (64 - A.log2c)) & (R - 1);
+    uint32_t p = (uint32_t)(hash_sliced<L>(T, key, A.crc_hi, A.crc_lo, A.mul) >> (64 - A.log2c)) & (R - 1);
     while (true) {
       if (p == R) {
-        late[atomicAdd(&s_off, 1u)] = (uint16_t)i;
+        k.put_off[(u64)r * cap + atomicAdd(&s_off, 1u)] = (uint16_t)i;
         break;
       }
       u64 *w = img + (L == 0 ? p : 2 * p);
@@ -365,10 +371,8 @@ __global__ void __launch_bounds__(kApplyThreads) k_load_apply(LoadK k) {
     if (!fresh || ((any >> (threadIdx.x & 56u)) & 0xFFull))
       __builtin_nontemporal_store(c, cells + j * kApplyThreads + threadIdx.x);
   }
-  const uint32_t off = s_off;
-  for (uint32_t i = threadIdx.x; i < off; i += kApplyThreads) k.put_off[(u64)r * cap + i] = late[i];
   if (threadIdx.x == 0) {
-    k.n_put_off[r] = off;
+    k.n_put_off[r] = s_off;
     CountSlot *cs = &A.status->slot[r % kCountSlots];
     if (s_hits) {
       add64(&cs->used, s_hits);
@@ -434,7 +438,7 @@ Plan plan_of(uint64_t n, uint32_t log2c, uint32_t layout, bool with_flags) {
   p.regions = 1u << bits;
   const uint64_t c0 = room(n, p.bits[0]), c1 = p.bits[1] ? room(n, bits) : 0;
   const uint64_t last = p.bits[1] ? c1 : c0;
-  p.ok = bits >= 4 && p.bits[0] <= kMaxBits && p.bits[1] <= kMaxBits && c0 < (1ull << 31) && last <= kMaxLast[layout];
+  p.ok = bits >= 4 && p.bits[0] <= kMaxBits && p.bits[1] <= kMaxBits && c0 < (1ull << 31) && last < (1u << 16);  // put_off has 16 bits
   if (!p.ok) return p;
   p.cap[0] = (uint32_t)c0;
   p.cap[1] = (uint32_t)c1;
