@@ -16,19 +16,19 @@
 // partition instead of a full sort, since the result of "add" does not depend
 // on the order.
 //
-// Passes: the partition runs in two levels, 256 buckets of the top 8 hash
-// bits and then 32 sub-buckets of the next 5 bits inside each (on tables of
-// 2^21 cells or more), so that a workgroup's scatter has few open output runs
-// at a time and its writes complete whole lines in L2 (one level of 4096
-// buckets left each XCD's L2 with far more partly written lines than it
-// holds).  Skewed streams put one key on most lanes of a wavefront, so the
-// LDS atomics of the first level and of the apply first combine the lanes
-// that share the leading lane's bucket or key.  Each level is a count
-// (per-workgroup histograms of a contiguous share; each workgroup reserves
-// its share of every bucket with one atomic on the bucket's total), a scan of
-// the bucket totals by one workgroup (bucket starts; after the second level
-// also the work items: at most kItemOps operations inside one bucket), and a
-// scatter (keys, values and indices into bucket order).  Then apply: one
+// Passes: the partition runs in two levels, 128 buckets of the top 7 hash
+// bits and then 64 sub-buckets of the next 6 bits inside each (on tables of
+// 2^21 cells or more).  A count (histograms over all buckets of contiguous
+// shares) and a scan by one workgroup give every bucket's start in both
+// levels, and two scatters, tile by tile through LDS, bring keys, values and
+// indices into bucket order: bound by memory, 1.6 GB per 10^8 keys and level
+// at 4.1 TB/s.  Skewed streams put one key on most lanes of a wavefront, so
+// the LDS atomics of the count and of the apply first combine the lanes that
+// share the leading lane's bucket or key.  The scan also lays out the work
+// items (at most kItemOps operations inside one bucket).
+// 10^8 keys of a Zipf(1) stream: count 0.21 ms, sum and scan 0.04, scatters
+// 0.40 and 0.39 ms (a count of each level, 0.49 ms, and scatters of single
+// elements behind cursors, 0.80 and 0.53 ms, before).  Then apply: one
 // workgroup per work item combines the item in LDS and makes one single-lane
 // upsert per distinct key.  When a bucket is a single work item, every
 // operation on its keys is in that workgroup, and after the workgroup
@@ -52,10 +52,13 @@ namespace lpht {
 
 namespace {
 
-constexpr uint32_t kBits1 = 8;          // first-level buckets: 256
-constexpr uint32_t kMaxBits = 13;       // at most 8192 buckets in all (a bucket fits in 13 bits)
-constexpr uint32_t kCountWG = 512;      // workgroups of the count and scatter passes
+constexpr uint32_t kBits1 = 7;          // first-level buckets: 128
+constexpr uint32_t kMaxBits = 13;       // at most 8192 buckets in all
+constexpr uint32_t kCountWG = 512;      // workgroups of the count pass
 constexpr uint32_t kCountThreads = 512;
+constexpr uint32_t kTile = 4096;        // elements of one scatter workgroup
+constexpr uint32_t kPad = 32;           // first-level cursors on lines of their own
+constexpr uint32_t kSumSplit = 8;       // rows of workgroups a bucket's total is summed in
 // apply workgroups: without flags two of 512 threads per CU (one combines
 // while the other makes its upserts), with flags one of 1024
 template <bool FL>
@@ -67,30 +70,25 @@ constexpr uint32_t kItemOps = 32768;    // operations per apply work item
 constexpr uint32_t kSlotsNoFlags = 4096;
 constexpr uint32_t kSlotsFlags = 4096;
 constexpr uint32_t kProbe = 32;
-constexpr uint32_t kUnroll = 8;         // loads in flight per lane in the streaming passes
-
-// One level of the partition: src (n elements, or the first level's output)
-// into dst by the top `bits` bits of the hash.
-struct Level {
-  const void *skeys, *svals;
-  const uint32_t *sidx;  // source indices (null: the element's own index, first level)
-  void *dkeys, *dvals;
-  uint32_t *didx;
-  uint32_t bits, nb;     // this level's buckets: the top `bits` bits (all levels so far)
-  uint64_t *btot;        // [nb + 1]: totals (zeroed), then bucket starts; btot[nb] = elements
-  uint32_t *hist;        // [nwg][nb]: this workgroup's offset inside each bucket
-  uint32_t *items;       // [nb + 1] (second level only): first work item of each bucket
-  // (second level only) [items + 1]: first element of each work item, bit 63
-  // set when the item is its bucket's only one; the last entry is the total
-  uint64_t *istart;
-};
+constexpr uint32_t kUnroll = 8;         // loads in flight per lane in count and apply
 
 struct PartK {
   BulkArgs A;
-  uint32_t nwg;          // workgroups of the count and scatter passes
-  uint32_t pad;
-  uint64_t chunk;        // elements per count/scatter workgroup (contiguous)
-  Level L[2];
+  uint32_t nwg;          // workgroups of the count pass
+  uint32_t bits;         // buckets in all: the top `bits` bits of the hash
+  uint64_t chunk;        // elements per count workgroup (contiguous)
+  uint32_t *hist;        // [nwg][buckets]: the count workgroups' counts
+  uint64_t *btot;        // [buckets + 1]: totals (zeroed), then bucket starts; the last: all elements
+  uint32_t *cur[2];      // by level: next free position of each bucket (the first level's kPad apart)
+  uint32_t *tiles;       // [first-level buckets + 1]: first second-level tile of each
+  uint32_t *items;       // [buckets + 1]: first work item of each bucket
+  // [items + 1]: first element of each work item, bit 63 set when the item is
+  // its bucket's only one; the last entry is the total
+  uint64_t *istart;
+  // by level: keys, values (calls with values) and operation indices (calls
+  // with flags) in bucket order
+  void *keys[2], *vals[2];
+  uint32_t *idx[2];
 };
 
 uint32_t bucket_bits(uint32_t log2c) { return std::min<uint32_t>(kMaxBits, log2c - 8); }
@@ -106,14 +104,6 @@ template <int L>
 __device__ __forceinline__ u64 part_key_nt(const void *p, u64 i) {
   return L == 0 ? (u64)__builtin_nontemporal_load((const uint32_t *)p + i)
                 : __builtin_nontemporal_load((const u64 *)p + i);
-}
-
-template <int L>
-__device__ __forceinline__ void part_store(void *p, u64 i, u64 v) {
-  if (L == 0)
-    ((uint32_t *)p)[i] = (uint32_t)v;
-  else
-    ((u64 *)p)[i] = v;
 }
 
 // LDS slot of a key: a mix of all its bits (the table hash's top bits are the
@@ -146,11 +136,6 @@ __device__ __forceinline__ u64 match_first(bool active, u64 tag, u64 &lead_tag, 
   return __ballot(active && tag == lead_tag);
 }
 
-__device__ __forceinline__ uint32_t lanes_below(u64 m) {
-  const uint32_t lane = threadIdx.x & 63;
-  return (uint32_t)__popcll(m & ((1ull << lane) - 1));
-}
-
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -162,25 +147,23 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
 
 constexpr int kAggRounds = 2;  // leading tags combined per wavefront step
 
-__global__ void k_part_zero(PartK k) {
-  for (uint32_t lv = 0; lv < 2; ++lv)
-    for (uint32_t b = threadIdx.x; b <= k.L[lv].nb; b += blockDim.x) k.L[lv].btot[b] = 0;
+__global__ void __launch_bounds__(1024) k_part_zero(PartK k) {
+  for (uint32_t b = threadIdx.x; b <= (1u << k.bits); b += blockDim.x) k.btot[b] = 0;
 }
 
-// Count pass of level `lv`: histogram of this workgroup's contiguous share,
-// then one atomic per touched bucket reserves the share's place in it.
+// Count pass: histogram of this workgroup's contiguous share over all buckets
+// (both levels are laid out from it; a count of the first level's output for
+// the second, 245 us per 10^8 keys, is not needed).
 template <int L>
-__global__ void __launch_bounds__(kCountThreads) k_part_count(PartK k, uint32_t lv) {
+__global__ void __launch_bounds__(kCountThreads) k_part_count(PartK k) {
   __shared__ uint32_t T[8][256];
   __shared__ uint32_t h[1u << kMaxBits];
   crc_tables_build(T);
-  const Level &V = k.L[lv];
-  for (uint32_t b = threadIdx.x; b < V.nb; b += blockDim.x) h[b] = 0;
+  const uint32_t nb = 1u << k.bits;
+  for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x) h[b] = 0;
   __syncthreads();
   const BulkArgs &A = k.A;
-  // the second level reads the first level's output, whose length is its
-  // element count (reserved keys dropped)
-  const u64 n = lv == 0 ? A.n : k.L[0].btot[k.L[0].nb];
+  const u64 n = A.n;
   const u64 lo = (u64)blockIdx.x * k.chunk;
   const u64 hi = lo + k.chunk < n ? lo + k.chunk : n;
   uint32_t err = 0;
@@ -193,7 +176,7 @@ __global__ void __launch_bounds__(kCountThreads) k_part_count(PartK k, uint32_t 
 #pragma unroll
     for (uint32_t j = 0; j < kUnroll; ++j) {
       const u64 i = base + (u64)j * blockDim.x + threadIdx.x;
-      key[j] = i < hi ? part_key<L>(V.skeys, i) : 0;
+      key[j] = i < hi ? part_key<L>(A.keys, i) : 0;
     }
   };
   if (lo < hi) load(lo);
@@ -206,7 +189,7 @@ __global__ void __launch_bounds__(kCountThreads) k_part_count(PartK k, uint32_t 
     for (uint32_t j = 0; j < kUnroll; ++j) {
       const u64 i = base + (u64)j * blockDim.x + threadIdx.x;
       bool act = i < hi;
-      if (act && lv == 0) {
+      if (act) {
         if (ck[j] == kEmpty || ck[j] == kTomb) {
           err |= kErrReserved;
           if (A.flags) A.flags[i] = 0xFE;
@@ -215,7 +198,7 @@ __global__ void __launch_bounds__(kCountThreads) k_part_count(PartK k, uint32_t 
           A.flags[i] = 0;
         }
       }
-      const uint32_t b = act ? (uint32_t)(hash_of<L>(T, ck[j], A.crc_hi, A.crc_lo, A.mul) >> (64 - V.bits)) : 0;
+      const uint32_t b = act ? (uint32_t)(hash_of<L>(T, ck[j], A.crc_hi, A.crc_lo, A.mul) >> (64 - k.bits)) : 0;
       for (int r = 0; r < kAggRounds; ++r) {
         u64 lt = 0;
         uint32_t ll = 0;
@@ -227,12 +210,19 @@ __global__ void __launch_bounds__(kCountThreads) k_part_count(PartK k, uint32_t 
       if (act) atomicAdd(&h[b], 1u);
     }
   }
-  if (lv == 0) wave_err(A.status, err);
+  wave_err(A.status, err);
   __syncthreads();
-  for (uint32_t b = threadIdx.x; b < V.nb; b += blockDim.x) {
-    const uint32_t c = h[b];
-    if (c) V.hist[(u64)blockIdx.x * V.nb + b] = (uint32_t)atomicAdd((unsigned long long *)&V.btot[b], (u64)c);
-  }
+  for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x) k.hist[(u64)blockIdx.x * nb + b] = h[b];
+}
+
+// Bucket totals: the columns of the count workgroups' histograms, in
+// kSumSplit parts (an atomic per workgroup and bucket would be 4 million).
+__global__ void __launch_bounds__(256) k_part_sum(PartK k) {
+  const uint32_t b = blockIdx.x * 256 + threadIdx.x, nb = 1u << k.bits;
+  u64 sum = 0;
+#pragma unroll 8
+  for (uint32_t w = blockIdx.y; w < k.nwg; w += kSumSplit) sum += k.hist[(u64)w * nb + b];
+  if (sum) atomicAdd((unsigned long long *)&k.btot[b], (unsigned long long)sum);
 }
 
 // Exclusive scan of one value per thread over a workgroup of 1024 threads.
@@ -259,21 +249,21 @@ __device__ __forceinline__ u64 block_scan_1024(u64 v, u64 *s_w, u64 *total) {
   return s_w[w] + x - v;
 }
 
-// One workgroup of 1024 threads, up to eight buckets per thread: bucket starts
-// and (with V.items) the first work item of each bucket and each item's
-// range.
-__global__ void __launch_bounds__(1024) k_part_scan(PartK k, uint32_t lv) {
+// One workgroup of 1024 threads, up to eight buckets per thread: bucket
+// starts, the first work item of each bucket and each item's range, the
+// cursors of both levels and the second level's tiles.
+__global__ void __launch_bounds__(1024) k_part_scan(PartK k) {
   __shared__ u64 s_w[16];
   __shared__ u64 s_tot;
-  const Level &V = k.L[lv];
-  const uint32_t per = (V.nb + blockDim.x - 1) / blockDim.x;
+  const uint32_t nb = 1u << k.bits;
+  const uint32_t per = (nb + blockDim.x - 1) / blockDim.x;
   const uint32_t b0 = threadIdx.x * per;
   u64 tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   u64 els = 0, its = 0;
   for (uint32_t j = 0; j < per && j < 8; ++j) {
     const uint32_t b = b0 + j;
-    if (b < V.nb) {
-      tot[j] = V.btot[b];
+    if (b < nb) {
+      tot[j] = k.btot[b];
       els += tot[j];
       its += (tot[j] + kItemOps - 1) / kItemOps;
     }
@@ -286,164 +276,166 @@ __global__ void __launch_bounds__(1024) k_part_scan(PartK k, uint32_t lv) {
   u64 e = e0, it = i0;
   for (uint32_t j = 0; j < per && j < 8; ++j) {
     const uint32_t b = b0 + j;
-    if (b < V.nb) {
-      V.btot[b] = e;
+    if (b < nb) {
+      k.btot[b] = e;
+      k.cur[1][b] = (uint32_t)e;
       const u64 ni = (tot[j] + kItemOps - 1) / kItemOps;
-      if (V.items) {
-        V.items[b] = (uint32_t)it;
-        for (u64 q = 0; q < ni; ++q) V.istart[it + q] = (e + q * kItemOps) | (ni == 1 ? 1ull << 63 : 0);
-      }
+      k.items[b] = (uint32_t)it;
+      for (u64 q = 0; q < ni; ++q) k.istart[it + q] = (e + q * kItemOps) | (ni == 1 ? 1ull << 63 : 0);
       e += tot[j];
       it += ni;
     }
   }
   if (threadIdx.x == 0) {
-    V.btot[V.nb] = etotal;
-    if (V.items) {
-      V.items[V.nb] = (uint32_t)itotal;
-      V.istart[itotal] = etotal;
-    }
+    k.btot[nb] = etotal;
+    k.items[nb] = (uint32_t)itotal;
+    k.istart[itotal] = etotal;
   }
-}
-
-// Scatter pass of level LV.  VALS, IDX: the level moves values and operation
-// indices along with the keys.  Keys are read once, by non-temporal loads, so
-// that L2 keeps the lines the stores are still filling.
-template <int L, bool VALS, bool IDX, int LV>
-__global__ void __launch_bounds__(kCountThreads) k_part_scatter(PartK k) {
-  __shared__ uint32_t T[8][256];
-  // next free position of each bucket in this share (positions are below
-  // 2^32: calls of 2^32 - 1 or more operations are not partitioned)
-  __shared__ uint32_t cur[1u << kMaxBits];
-  crc_tables_build(T);
-  const Level &V = k.L[LV];
-  const BulkArgs &A = k.A;
-  const u64 n = LV == 0 ? A.n : k.L[0].btot[k.L[0].nb];
-  const u64 lo = (u64)blockIdx.x * k.chunk;
-  const u64 hi = lo + k.chunk < n ? lo + k.chunk : n;
-  const uint32_t lane = threadIdx.x & 63;
-  // elements per lane and tile: where two tiles' loads are held with values
-  // or indices moved too, half as many keep the occupancy
-  constexpr uint32_t U = (LV == 1 && (VALS || IDX)) ? kUnroll / 2 : kUnroll;
-  // only the buckets this share touched hold a valid reservation; the others
-  // are never used below
-  for (uint32_t b = threadIdx.x; b < V.nb; b += blockDim.x)
-    cur[b] = (uint32_t)(V.btot[b] + V.hist[(u64)blockIdx.x * V.nb + b]);
   __syncthreads();
-  const u64 step = (u64)blockDim.x * U;
-  u64 key[U], val[U];
-  uint32_t idx[U];
-  auto load = [&](u64 base) {
+  const uint32_t sub = k.bits - kBits1, f = threadIdx.x;
+  u64 start = 0, tiles = 0;
+  if (f < (1u << kBits1)) {
+    start = k.btot[f << sub];
+    tiles = (k.btot[(f + 1) << sub] - start + kTile - 1) / kTile;
+  }
+  const u64 t0 = block_scan_1024(tiles, s_w, &s_tot);
+  if (f < (1u << kBits1)) {
+    k.cur[0][f * kPad] = (uint32_t)start;
+    k.tiles[f] = (uint32_t)t0;
+  }
+  if (f == 0) k.tiles[1u << kBits1] = (uint32_t)s_tot;
+}
+
+// Scatter pass of level LV in tiles of 4096 elements: ranked inside their
+// bucket by LDS atomics, put in bucket order in LDS and written as runs behind
+// one reservation per bucket and tile (of a uniform hash 32 elements a run in
+// the first level and 64 in the second, so most written lines are whole;
+// written one by one, behind cursors in LDS, L2 wrote lines back part-filled).
+// The first level's tiles are those of the batch, the second level's lie in
+// one first-level bucket each.  VALS, IDX: the level moves values and
+// operation indices along with the keys.  Equal keys cost same-address LDS
+// atomics and still one reservation per tile; a wavefront whose elements all
+// lie in one bucket ranks itself (2^24 operations on one key: the call 357 ->
+// 309 us; 402 with single elements behind cursors).
+// A KV64 call with values and indices needs 92 KiB of LDS, so one workgroup
+// per CU: of twice the wavefronts then.
+template <int L, bool VALS, bool IDX>
+constexpr uint32_t scatter_threads() { return L == 1 && VALS && IDX ? 1024 : 512; }
+
+template <int L, bool VALS, bool IDX, int LV>
+__global__ void __launch_bounds__((scatter_threads<L, VALS, IDX>()), 4) k_part_scatter(PartK k) {
+  using Word = typename std::conditional<L == 0, uint32_t, u64>::type;
+  constexpr uint32_t NT = scatter_threads<L, VALS, IDX>(), PER = kTile / NT;
+  constexpr uint32_t NB = 1u << (LV == 0 ? kBits1 : kMaxBits - kBits1);
+  __shared__ Word kbuf[kTile];
+  __shared__ Word vbuf[VALS ? kTile : 1];
+  __shared__ uint32_t ibuf[IDX ? kTile : 1];
+  __shared__ uint16_t bkt[kTile];
+  // by bucket: elements, their start in the tile, then their position less that
+  __shared__ uint32_t toff[NB];
+  __shared__ uint32_t T[1024];
+  __shared__ uint32_t s_w[NB / 64], s_f;
+  const BulkArgs &A = k.A;
+  const uint32_t sub = k.bits - kBits1, nb = LV == 0 ? NB : 1u << sub, lane = threadIdx.x & 63;
+  u64 base;
+  uint32_t m, f = 0;
+  if (LV == 0) {
+    base = (u64)blockIdx.x * kTile;
+    m = (uint32_t)std::min<u64>(kTile, A.n - base);
+  } else {
+    // each XCD (workgroups are dealt out over eight) takes a range of the
+    // tiles, so that one L2 joins the runs of a bucket
+    const uint32_t all = k.tiles[1u << kBits1];
+    const uint32_t t = (blockIdx.x & 7) * ((all + 7) / 8) + (blockIdx.x >> 3);
+    if (blockIdx.x >> 3 >= (all + 7) / 8 || t >= all) return;
+    if (threadIdx.x < (1u << kBits1) && k.tiles[threadIdx.x] <= t && t < k.tiles[threadIdx.x + 1]) s_f = threadIdx.x;
+    __syncthreads();
+    f = s_f;
+    base = k.btot[f << sub] + (u64)(t - k.tiles[f]) * kTile;
+    m = (uint32_t)std::min<u64>(kTile, k.btot[(f + 1) << sub] - base);
+  }
+  crc_slices_load(T);
+  if (threadIdx.x < nb) toff[threadIdx.x] = 0;
+  Word key[PER], val[PER];
+  uint32_t ix[PER], at[PER];
+  bool ok[PER];
 #pragma unroll
-    for (uint32_t j = 0; j < U; ++j) {
-      const u64 i = base + (u64)j * blockDim.x + threadIdx.x;
-      const bool in = i < hi;
-      key[j] = in ? part_key_nt<L>(V.skeys, i) : 0;
-      val[j] = VALS && in ? part_key_nt<L>(V.svals, i) : 0;
-      idx[j] = IDX && in ? (V.sidx ? __builtin_nontemporal_load(V.sidx + i) : (uint32_t)i) : 0;
+  for (uint32_t j = 0; j < PER; ++j) {
+    const uint32_t t = j * NT + threadIdx.x;
+    const u64 i = base + t;
+    ok[j] = t < m;
+    key[j] = ok[j] ? (Word)part_key_nt<L>(LV == 0 ? A.keys : k.keys[0], i) : 0;
+    val[j] = VALS && ok[j] ? (Word)part_key_nt<L>(LV == 0 ? A.vals : k.vals[0], i) : 0;
+    ix[j] = IDX && ok[j] ? (LV == 0 ? (uint32_t)i : __builtin_nontemporal_load(k.idx[0] + i)) : 0;
+    if (LV == 0) ok[j] = key[j] != (Word)kEmpty && key[j] != (Word)kTomb;  // kEmpty past the end, too
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t j = 0; j < PER; ++j) {
+    const uint32_t all = (uint32_t)(hash_sliced<L>(T, (u64)key[j], A.crc_hi, A.crc_lo, A.mul) >> (64 - k.bits));
+    const uint32_t b = LV == 0 ? all >> sub : all & (nb - 1);
+    // a wavefront of one bucket ranks itself
+    if (__all(ok[j] && b == (uint32_t)__builtin_amdgcn_readfirstlane((int)b))) {
+      uint32_t r = 0;
+      if (lane == 0) r = atomicAdd(&toff[b], 64u);
+      at[j] = b | (((uint32_t)__builtin_amdgcn_readfirstlane((int)r) + lane) << 16);
+      continue;
     }
-  };
-  // The second level loads the next tile while it places this one.  The
-  // first level does not: its stores go to 256 open runs per workgroup, and
-  // with twice the reads in flight L2 wrote more of those lines back
-  // part-filled.
-  if (LV == 1 && lo < hi) load(lo);
-  for (u64 base = lo; base < hi; base += step) {
-    if (LV == 0) load(base);
-    u64 ck[U], cv[U];
-    uint32_t ci[U];
+    if (ok[j]) at[j] = b | (atomicAdd(&toff[b], 1u) << 16);
+  }
+  __syncthreads();
+  uint32_t to = 0;
+  {
+    const uint32_t c = threadIdx.x < nb ? toff[threadIdx.x] : 0;
+    uint32_t x = c;
 #pragma unroll
-    for (uint32_t j = 0; j < U; ++j) {
-      ck[j] = key[j];
-      cv[j] = val[j];
-      ci[j] = idx[j];
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o, 64);
+      if (lane >= (uint32_t)o) x += y;
     }
-    if (LV == 1 && base + step < hi) load(base + step);
-    // per element: bucket (bits 0-12), its lane's share to reserve (bits
-    // 13-19), the lane holding the reservation (bits 20-25) and the place in
-    // the group (bits 26-31)
-    uint32_t w[U];
-    bool valid[U];
+    if (threadIdx.x < NB && lane == 63) s_w[threadIdx.x >> 6] = x;
+    if (c) to = atomicAdd(LV == 0 ? &k.cur[0][threadIdx.x * kPad] : &k.cur[1][((u64)f << sub) + threadIdx.x], c);
+    __syncthreads();
+    uint32_t before = x - c;
+    if (threadIdx.x < NB)
+      for (uint32_t w = 0; w < (threadIdx.x >> 6); ++w) before += s_w[w];
+    if (threadIdx.x < nb) toff[threadIdx.x] = before;
+    to -= before;
+  }
+  __syncthreads();
+  uint32_t total = 0;
+  for (uint32_t w = 0; w < NB / 64; ++w) total += s_w[w];
 #pragma unroll
-    for (uint32_t j = 0; j < U; ++j) {
-      const u64 i = base + (u64)j * blockDim.x + threadIdx.x;
-      valid[j] = i < hi && !(LV == 0 && (ck[j] == kEmpty || ck[j] == kTomb));
-      const uint32_t b = valid[j] ? (uint32_t)(hash_of<L>(T, ck[j], A.crc_hi, A.crc_lo, A.mul) >> (64 - V.bits)) : 0;
-      w[j] = b | (valid[j] ? 1u << 13 : 0u) | (lane << 20);
-    }
-    // Lanes that share the leading lane's bucket reserve their places with
-    // one atomic by the leading lane (decided by ballots alone).  Only the
-    // first level: its hot buckets hold the stream's most frequent keys,
-    // while the second level's lanes spread over the 32 sub-buckets of one
-    // or two first-level buckets, rarely more than two or three to one, and
-    // the ballot rounds cost more than the LDS atomics they save.
-    constexpr int kRounds = LV == 0 ? kAggRounds : 0;
-#pragma unroll
-    for (uint32_t j = 0; j < U; ++j) {
-      bool open = valid[j];
-      const uint32_t b = w[j] & 0x1FFFu;
-      for (int r = 0; r < kRounds; ++r) {
-        u64 lt = 0;
-        uint32_t ll = 0;
-        const u64 m = match_first(open, b, lt, ll);
-        if (__popcll(m) < 2) break;
-        if ((m >> lane) & 1) {
-          open = false;
-          const uint32_t add = lane == ll ? (uint32_t)__popcll(m) : 0u;
-          w[j] = b | (add << 13) | (ll << 20) | (lanes_below(m) << 26);
-        }
-      }
-    }
-    auto put = [&](uint32_t j, uint32_t at) {
-      const u64 pos = (u64)(uint32_t)__shfl((int)at, (int)((w[j] >> 20) & 63u), 64) + (w[j] >> 26);
-      if (!valid[j]) return;
-      part_store<L>(V.dkeys, pos, ck[j]);
-      if (VALS) part_store<L>(V.dvals, pos, cv[j]);
-      if (IDX) V.didx[pos] = ci[j];
-    };
-    if (LV == 0) {
-      // one element's reservation and stores at a time
-#pragma unroll
-      for (uint32_t j = 0; j < U; ++j) {
-        const uint32_t add = (w[j] >> 13) & 0x7Fu;
-        put(j, add ? atomicAdd(&cur[w[j] & 0x1FFFu], add) : 0u);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    } else {
-      // all of the tile's LDS atomics issued before any result is awaited
-      uint32_t at[U];
-#pragma unroll
-      for (uint32_t j = 0; j < U; ++j) {
-        const uint32_t add = (w[j] >> 13) & 0x7Fu;
-        at[j] = add ? atomicAdd(&cur[w[j] & 0x1FFFu], add) : 0u;
-      }
-#pragma unroll
-      for (uint32_t j = 0; j < U; ++j) put(j, at[j]);
-    }
+  for (uint32_t j = 0; j < PER; ++j) {
+    if (!ok[j]) continue;
+    const uint32_t b = at[j] & 0xFFFFu, p = toff[b] + (at[j] >> 16);
+    kbuf[p] = key[j];
+    bkt[p] = (uint16_t)b;
+    if (VALS) vbuf[p] = val[j];
+    if (IDX) ibuf[p] = ix[j];
+  }
+  __syncthreads();
+  if (threadIdx.x < nb) toff[threadIdx.x] = to;
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < total; i += NT) {
+    const u64 q = toff[bkt[i]] + i;
+    ((Word *)k.keys[LV])[q] = kbuf[i];
+    if (VALS) ((Word *)k.vals[LV])[q] = vbuf[i];
+    if (IDX) k.idx[LV][q] = ibuf[i];
   }
 }
 
-// Open output runs: a first-level workgroup fills one run per bucket, 256
-// at once, and an XCD's L2 holds the partly written last line of every run of
-// the workgroups resident on its 32 CUs.  With two workgroups per CU (the
-// occupancy their registers allow) those lines were written back part-filled:
-// 1.38 GB written to HBM for 0.8 GB of keys and 920 us per 10^8 Zipf(1.0)
-// keys.  The first level therefore reserves LDS it does not use so that one
-// workgroup runs per CU: 0.92 GB and 775 us.  The second level has at most a
-// few dozen runs per workgroup and keeps the full occupancy.
-constexpr size_t kScatter1LdsPad = 64 * 1024;
-
-template <int L, int LV>
-void launch_scatter(const PartK &k, bool vals, bool idx, hipStream_t s) {
-  const size_t pad = LV == 0 ? kScatter1LdsPad : 0;
-  if (vals && idx)
-    hipLaunchKernelGGL((k_part_scatter<L, true, true, LV>), dim3(k.nwg), dim3(kCountThreads), pad, s, k);
-  else if (vals)
-    hipLaunchKernelGGL((k_part_scatter<L, true, false, LV>), dim3(k.nwg), dim3(kCountThreads), pad, s, k);
-  else if (idx)
-    hipLaunchKernelGGL((k_part_scatter<L, false, true, LV>), dim3(k.nwg), dim3(kCountThreads), pad, s, k);
-  else
-    hipLaunchKernelGGL((k_part_scatter<L, false, false, LV>), dim3(k.nwg), dim3(kCountThreads), pad, s, k);
+template <int L, bool VALS, bool IDX>
+hipError_t launch_scatters(const PartK &k, hipStream_t s) {
+  const uint32_t tiles = (uint32_t)((k.A.n + kTile - 1) / kTile);
+  constexpr uint32_t NT = scatter_threads<L, VALS, IDX>();
+  hipLaunchKernelGGL((k_part_scatter<L, VALS, IDX, 0>), dim3(tiles), dim3(NT), 0, s, k);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // a first-level bucket's last tile may be short; a multiple of eight
+  const uint32_t tiles2 = (tiles + (1u << kBits1) + 7) & ~7u;
+  hipLaunchKernelGGL((k_part_scatter<L, VALS, IDX, 1>), dim3(tiles2), dim3(NT), 0, s, k);
+  return hipGetLastError();
 }
 
 // insertOrUpdate(k, d, add) by the only lane that updates k in this call
@@ -498,10 +490,9 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
   if (threadIdx.x == 0) s_claims = 0;
   __syncthreads();
   const BulkArgs &A = k.A;
-  const Level &V = k.L[1];
   long long d_used = 0, d_live = 0;
   uint32_t err = 0;
-  const uint32_t nitems = V.items[V.nb];
+  const uint32_t nitems = k.items[1u << k.bits];
   const u64 step = (u64)blockDim.x * kUnroll;
   constexpr u64 kAlone = 1ull << 63;
   u64 keys[kUnroll], ds[kUnroll];
@@ -511,18 +502,18 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
     for (uint32_t u = 0; u < kUnroll; ++u) {
       const u64 p = pb + (u64)u * blockDim.x + threadIdx.x;
       const bool in = p < hi;
-      keys[u] = in ? part_key<L>(V.dkeys, p) : 0;
-      ds[u] = in ? (V.dvals ? part_key<L>(V.dvals, p) : 1) : 0;
-      idxs[u] = in && FL ? V.didx[p] : 0;
+      keys[u] = in ? part_key<L>(k.keys[1], p) : 0;
+      ds[u] = in ? (k.vals[1] ? part_key<L>(k.vals[1], p) : 1) : 0;
+      idxs[u] = in && FL ? k.idx[1][p] : 0;
     }
   };
   // item j covers [istart[j], istart[j + 1]) without the flag bit
   u64 lo = 0, hi = 0;
   bool alone = false;
   if (blockIdx.x < nitems) {
-    const u64 s0 = V.istart[blockIdx.x];
+    const u64 s0 = k.istart[blockIdx.x];
     lo = s0 & ~kAlone;
-    hi = V.istart[blockIdx.x + 1] & ~kAlone;
+    hi = k.istart[blockIdx.x + 1] & ~kAlone;
     alone = (s0 & kAlone) != 0;
     load(lo, hi);
   }
@@ -542,7 +533,7 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
      if (pb + step < hi) {
        load(pb + step, hi);
      } else if (nx < nitems) {
-       load(V.istart[nx] & ~kAlone, V.istart[nx + 1] & ~kAlone);
+       load(k.istart[nx] & ~kAlone, k.istart[nx + 1] & ~kAlone);
      }
      for (uint32_t u = 0; u < kUnroll; ++u) {
       // equal keys on the lanes of this step first (a batch key is never 0
@@ -560,7 +551,7 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
         if (__popcll(m) < 2) break;
         const bool in = (m >> (threadIdx.x & 63)) & 1;
         // without values every operation adds 1
-        const u64 sum = V.dvals ? (u64)wave_sum(in ? (long long)d : 0) : (u64)__popcll(m);
+        const u64 sum = k.vals[1] ? (u64)wave_sum(in ? (long long)d : 0) : (u64)__popcll(m);
         const uint32_t imin = FL ? wave_min_u32(in ? idx : ~0u) : 0;
         if (in) {
           open = false;
@@ -624,9 +615,9 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
     }
     __syncthreads();
     if (nx < nitems) {
-      const u64 s0 = V.istart[nx];
+      const u64 s0 = k.istart[nx];
       lo = s0 & ~kAlone;
-      hi = V.istart[nx + 1] & ~kAlone;
+      hi = k.istart[nx + 1] & ~kAlone;
       alone = (s0 & kAlone) != 0;
     }
   }
@@ -634,32 +625,31 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
 }
 
 struct Carved {
-  size_t btot[2], hist[2], items, istart, keys[2], vals[2], idx[2], total;
+  size_t btot, hist, cur[2], tiles, items, istart, keys[2], vals[2], idx[2], total;
 };
 
 Carved carve(uint64_t n, uint32_t log2c, uint32_t layout, bool with_vals, bool with_flags, uint32_t nwg) {
-  const uint32_t nb[2] = {1u << kBits1, 1u << bucket_bits(log2c)};
+  const uint32_t nb0 = 1u << kBits1, nb = 1u << bucket_bits(log2c);
   const size_t kb = layout == 0 ? 4 : 8;
   Carved o{};
   size_t at = 0;
-  for (int lv = 0; lv < 2; ++lv) {
-    o.btot[lv] = at;
-    at += round256(((size_t)nb[lv] + 1) * 8);
-    o.hist[lv] = at;
-    at += round256((size_t)nwg * nb[lv] * 4);
-  }
-  o.items = at;
-  at += round256(((size_t)nb[1] + 1) * 4);
+  auto take = [&](size_t bytes) {
+    const size_t p = at;
+    at += round256(bytes);
+    return p;
+  };
+  o.btot = take(((size_t)nb + 1) * 8);
+  o.hist = take((size_t)nwg * nb * 4);
+  o.cur[0] = take((size_t)nb0 * kPad * 4);
+  o.cur[1] = take((size_t)nb * 4);
+  o.tiles = take(((size_t)nb0 + 1) * 4);
+  o.items = take(((size_t)nb + 1) * 4);
   // a bucket of c elements has ceil(c / kItemOps) items
-  o.istart = at;
-  at += round256((n / kItemOps + nb[1] + 2) * 8);
+  o.istart = take((n / kItemOps + nb + 2) * 8);
   for (int lv = 0; lv < 2; ++lv) {
-    o.keys[lv] = at;
-    at += round256(n * kb);
-    o.vals[lv] = at;
-    at += with_vals ? round256(n * kb) : 0;
-    o.idx[lv] = at;
-    at += with_flags ? round256(n * 4) : 0;
+    o.keys[lv] = take(n * kb);
+    o.vals[lv] = take(with_vals ? n * kb : 0);
+    o.idx[lv] = take(with_flags ? n * 4 : 0);
   }
   o.total = at;
   return o;
@@ -692,50 +682,39 @@ hipError_t launch_upsert_add_part(const BulkArgs &a, void *scratch, uint32_t num
   k.chunk = (a.n + k.nwg - 1) / k.nwg;
   const Carved o = carve(a.n, a.log2c, a.layout, a.vals != nullptr, a.flags != nullptr, k.nwg);
   unsigned char *base = (unsigned char *)scratch;
+  k.bits = bucket_bits(a.log2c);
+  k.btot = (uint64_t *)(base + o.btot);
+  k.hist = (uint32_t *)(base + o.hist);
+  k.tiles = (uint32_t *)(base + o.tiles);
+  k.items = (uint32_t *)(base + o.items);
+  k.istart = (uint64_t *)(base + o.istart);
   for (int lv = 0; lv < 2; ++lv) {
-    Level &V = k.L[lv];
-    V.bits = lv == 0 ? kBits1 : bucket_bits(a.log2c);
-    V.nb = 1u << V.bits;
-    V.btot = (uint64_t *)(base + o.btot[lv]);
-    V.hist = (uint32_t *)(base + o.hist[lv]);
-    V.items = lv == 1 ? (uint32_t *)(base + o.items) : nullptr;
-    V.istart = lv == 1 ? (uint64_t *)(base + o.istart) : nullptr;
-    V.dkeys = base + o.keys[lv];
-    V.dvals = a.vals ? (void *)(base + o.vals[lv]) : nullptr;
-    V.didx = a.flags ? (uint32_t *)(base + o.idx[lv]) : nullptr;
+    k.cur[lv] = (uint32_t *)(base + o.cur[lv]);
+    k.keys[lv] = base + o.keys[lv];
+    k.vals[lv] = a.vals ? (void *)(base + o.vals[lv]) : nullptr;
+    k.idx[lv] = a.flags ? (uint32_t *)(base + o.idx[lv]) : nullptr;
   }
-  k.L[0].skeys = a.keys;
-  k.L[0].svals = a.vals;
-  k.L[0].sidx = nullptr;
-  k.L[1].skeys = k.L[0].dkeys;
-  k.L[1].svals = k.L[0].dvals;
-  k.L[1].sidx = k.L[0].didx;
   const uint32_t cus = std::max<uint32_t>(1, num_cus);
   hipError_t e;
   hipLaunchKernelGGL(k_part_zero, dim3(1), dim3(1024), 0, s, k);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  for (uint32_t lv = 0; lv < 2; ++lv) {
-#define LPHT_PART(KERN, GRID, THREADS, ...)                                          \
-  do {                                                                               \
-    if (a.layout == 0)                                                               \
-      hipLaunchKernelGGL(KERN<0>, dim3(GRID), dim3(THREADS), 0, s, __VA_ARGS__);     \
-    else                                                                             \
-      hipLaunchKernelGGL(KERN<1>, dim3(GRID), dim3(THREADS), 0, s, __VA_ARGS__);     \
-    if ((e = hipGetLastError()) != hipSuccess) return e;                             \
-  } while (0)
-    LPHT_PART(k_part_count, k.nwg, kCountThreads, k, lv);
-    hipLaunchKernelGGL(k_part_scan, dim3(1), dim3(1024), 0, s, k, lv);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    {
-      const bool vals = a.vals != nullptr, idx = a.flags != nullptr;
-      if (a.layout == 0)
-        lv == 0 ? launch_scatter<0, 0>(k, vals, idx, s) : launch_scatter<0, 1>(k, vals, idx, s);
-      else
-        lv == 0 ? launch_scatter<1, 0>(k, vals, idx, s) : launch_scatter<1, 1>(k, vals, idx, s);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-#undef LPHT_PART
-  }
+  if (a.layout == 0)
+    hipLaunchKernelGGL(k_part_count<0>, dim3(k.nwg), dim3(kCountThreads), 0, s, k);
+  else
+    hipLaunchKernelGGL(k_part_count<1>, dim3(k.nwg), dim3(kCountThreads), 0, s, k);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_part_sum, dim3((1u << k.bits) / 256, kSumSplit), dim3(256), 0, s, k);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_part_scan, dim3(1), dim3(1024), 0, s, k);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const bool vals = a.vals != nullptr, idx = a.flags != nullptr;
+  if (a.layout == 0)
+    e = vals ? (idx ? launch_scatters<0, true, true>(k, s) : launch_scatters<0, true, false>(k, s))
+             : (idx ? launch_scatters<0, false, true>(k, s) : launch_scatters<0, false, false>(k, s));
+  else
+    e = vals ? (idx ? launch_scatters<1, true, true>(k, s) : launch_scatters<1, true, false>(k, s))
+             : (idx ? launch_scatters<1, false, true>(k, s) : launch_scatters<1, false, false>(k, s));
+  if (e != hipSuccess) return e;
   // as many apply workgroups as fit at once (LDS bounds them)
   if (a.flags) {
     if (a.layout == 0)
