@@ -329,7 +329,8 @@ int run_bulk(lpht_table *t, OpKind op, const void *keys, const void *vals, uint6
                                          t->launch.num_cus);
     void *scratch = dev_alloc(t, sb, s);
     if (scratch) {
-      const hipError_t e = launch_upsert_add_part(a, scratch, t->launch.num_cus, s);
+      const bool fresh = t->known_used + t->pending == n && !capturing(s);
+      const hipError_t e = launch_upsert_add_part(a, fresh, scratch, t->launch.num_cus, s);
       dev_free(t, scratch, sb, s);
       if (e != hipSuccess) return from_hip(e);
       if (t->special)

@@ -24,6 +24,7 @@ bool part_applies(uint64_t n, uint32_t log2c);
 // bits of its hash, i.e. by table region, equal keys of a bucket are combined
 // in LDS, and one upsert per distinct key is applied.  The table must not
 // run out of empty cells during the call (as for the LDS-combining kernel).
-hipError_t launch_upsert_add_part(const BulkArgs &a, void *scratch, uint32_t num_cus, hipStream_t s);
+// `fresh`: the table has no non-empty cell.
+hipError_t launch_upsert_add_part(const BulkArgs &a, bool fresh, void *scratch, uint32_t num_cus, hipStream_t s);
 
 }  // namespace lpht

@@ -34,7 +34,9 @@
 // operation on its keys is in that workgroup, and after the workgroup
 // barrier each combined key is applied by one lane only: a new key is
 // claimed with compare-and-swap and its sum written by a plain store, which
-// halves the atomics of a fresh table.  Flags: the count pass writes 0 for
+// halves the atomics of a fresh table; on a KV64 table without a used cell, in a
+// call without flags, no compare-and-swap is needed at all (FRESH below).
+// Flags: the count pass writes 0 for
 // every operation (0xFE for reserved keys), and the operation with the
 // smallest index among a slot's operations receives the upsert's result.
 // Keys that find no LDS slot (the table is three quarters full, or kProbe
@@ -46,6 +48,7 @@
 #include <algorithm>
 
 #include "lpht_device.h"
+#include "lpht_lane_op.h"
 #include "lpht_part.h"
 
 namespace lpht {
@@ -59,10 +62,13 @@ constexpr uint32_t kCountThreads = 512;
 constexpr uint32_t kTile = 4096;        // elements of one scatter workgroup
 constexpr uint32_t kPad = 32;           // first-level cursors on lines of their own
 constexpr uint32_t kSumSplit = 8;       // rows of workgroups a bucket's total is summed in
-// apply workgroups: without flags two of 512 threads per CU (one combines
-// while the other makes its upserts), with flags one of 1024
-template <bool FL>
-constexpr uint32_t apply_threads() { return FL ? 1024 : 512; }
+// apply workgroups: without flags two per CU (one combines while the other
+// makes its upserts), with flags one
+// The apply waits for LDS: 1024 threads of four operations each (64 VGPRs) in
+// place of 512 of eight, 2^24 Zipf(1) keys 519 -> 460 us for the call, PACKED32
+// 643 -> 508.
+constexpr uint32_t kApplyThreads = 1024;
+constexpr uint32_t kApplyUnroll = 4;
 constexpr uint32_t kItemOps = 32768;    // operations per apply work item
 // LDS combining slots: 4096 of 16 B (64 KiB, two workgroups per CU; with
 // flags each slot also keeps its representative's index) hold the ~2.2k
@@ -70,7 +76,7 @@ constexpr uint32_t kItemOps = 32768;    // operations per apply work item
 constexpr uint32_t kSlotsNoFlags = 4096;
 constexpr uint32_t kSlotsFlags = 4096;
 constexpr uint32_t kProbe = 32;
-constexpr uint32_t kUnroll = 8;         // loads in flight per lane in count and apply
+constexpr uint32_t kUnroll = 8;         // loads in flight per lane in the count
 
 struct PartK {
   BulkArgs A;
@@ -85,6 +91,14 @@ struct PartK {
   // [items + 1]: first element of each work item, bit 63 set when the item is
   // its bucket's only one; the last entry is the total
   uint64_t *istart;
+  // keys put off (a fresh table), in the first level's arrays, which are free by
+  // then: with values, off[0] of keys and values; without, off[0] keys of one
+  // operation from the front and off[1] keys with their sums from the back
+  uint32_t *off;
+  // work items taken, past the two each apply workgroup begins with (items
+  // differ: of a hot key, of a short bucket; dealt out in turn, 10^8 Zipf(1)
+  // keys took 1.07 ms in the apply, now 0.96)
+  uint32_t *next;
   // by level: keys, values (calls with values) and operation indices (calls
   // with flags) in bucket order
   void *keys[2], *vals[2];
@@ -107,12 +121,13 @@ __device__ __forceinline__ u64 part_key_nt(const void *p, u64 i) {
 }
 
 // LDS slot of a key: a mix of all its bits (the table hash's top bits are the
-// same for every key of a bucket).
+// same for every key of a bucket) by 32-bit products, which take a fifth of
+// the VALU's time for a 64-bit one.
 __device__ __forceinline__ uint32_t lds_slot(u64 key, uint32_t bits) {
-  u64 z = key ^ (key >> 31);
-  z *= 0xBF58476D1CE4E5B9ull;
-  z ^= z >> 29;
-  return (uint32_t)(z >> (64 - bits));
+  uint32_t z = (uint32_t)key ^ ((uint32_t)(key >> 32) * 0x85EBCA6Bu);
+  z = (z ^ (z >> 15)) * 0xC2B2AE35u;
+  z = (z ^ (z >> 13)) * 0x9E3779B1u;
+  return z >> (32 - bits);
 }
 
 // Reports the wavefront's sticky error bits once.
@@ -125,14 +140,17 @@ __device__ __forceinline__ void wave_err(DevStatus *st, uint32_t err) {
 }
 
 // Wavefront-level aggregation: the mask of the active lanes whose tag equals
-// the first active lane's, that lane and its tag.  Skewed streams put one
-// key (or bucket) on most lanes of a wavefront; combining them first turns
-// up to 64 serialised LDS atomics on one address into one.
-__device__ __forceinline__ u64 match_first(bool active, u64 tag, u64 &lead_tag, uint32_t &lead) {
+// the first active lane's, that lane and its tag (read as scalars).  Skewed
+// streams put one key (or bucket) on most lanes of a wavefront; combining them
+// first turns up to 64 serialised LDS atomics on one address into one.
+template <class Tag>
+__device__ __forceinline__ u64 match_first(bool active, Tag tag, Tag &lead_tag, uint32_t &lead) {
   const u64 act = __ballot(active);
   if (!act) return 0;
   lead = (uint32_t)__builtin_ctzll(act);
-  lead_tag = __shfl(tag, (int)lead, 64);
+  lead_tag = (Tag)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)tag, (int)lead);
+  if constexpr (sizeof(Tag) == 8)
+    lead_tag |= (Tag)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((u64)tag >> 32), (int)lead) << 32;
   return __ballot(active && tag == lead_tag);
 }
 
@@ -146,9 +164,13 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
 }
 
 constexpr int kAggRounds = 2;  // leading tags combined per wavefront step
+// lanes of one tag worth combining: fewer cost the LDS less than the round
+constexpr int kAggLanes = 6;
 
 __global__ void __launch_bounds__(1024) k_part_zero(PartK k) {
   for (uint32_t b = threadIdx.x; b <= (1u << k.bits); b += blockDim.x) k.btot[b] = 0;
+  if (threadIdx.x < 2) k.off[threadIdx.x] = 0;
+  if (threadIdx.x == 2) *k.next = 0;
 }
 
 // Count pass: histogram of this workgroup's contiguous share over all buckets
@@ -200,11 +222,10 @@ __global__ void __launch_bounds__(kCountThreads) k_part_count(PartK k) {
       }
       const uint32_t b = act ? (uint32_t)(hash_of<L>(T, ck[j], A.crc_hi, A.crc_lo, A.mul) >> (64 - k.bits)) : 0;
       for (int r = 0; r < kAggRounds; ++r) {
-        u64 lt = 0;
-        uint32_t ll = 0;
+        uint32_t lt = 0, ll = 0;
         const u64 m = match_first(act, b, lt, ll);
-        if (__popcll(m) < 2) break;
-        if ((threadIdx.x & 63) == ll) atomicAdd(&h[(uint32_t)lt], (uint32_t)__popcll(m));
+        if (__popcll(m) < kAggLanes) break;
+        if ((threadIdx.x & 63) == ll) atomicAdd(&h[lt], (uint32_t)__popcll(m));
         if ((m >> (threadIdx.x & 63)) & 1) act = false;
       }
       if (act) atomicAdd(&h[b], 1u);
@@ -469,19 +490,82 @@ __device__ __forceinline__ uint8_t upsert_add_excl_kv64(const BulkArgs &A, const
   return 0xFF;
 }
 
-template <int L, bool FL>
-__global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
+// A key that found no cell in its bucket's region of a fresh table.  Without
+// values a sum is a number of operations, so that keys and sums of two and
+// more take no more words than the operations they combine.
+__device__ __forceinline__ void put_off(const PartK &k, u64 key, u64 d) {
+  u64 *keys = (u64 *)k.keys[0];
+  if (k.vals[0]) {
+    const uint32_t i = atomicAdd(&k.off[0], 1u);
+    keys[i] = key;
+    ((u64 *)k.vals[0])[i] = d;
+  } else if (d == 1) {
+    keys[atomicAdd(&k.off[0], 1u)] = key;
+  } else {
+    u64 *e = keys + (k.A.n - 2 - 2 * (u64)atomicAdd(&k.off[1], 1u));
+    e[0] = d;
+    e[1] = key;
+  }
+}
+
+// insertOrUpdate(k, d, add) from cell p up to the cell `end` of the bucket's
+// region; false: no cell found.
+__device__ __forceinline__ bool upsert_add_region(void *cells, u64 p, u64 end, u64 key, u64 d, long long &d_new) {
+  for (; p < end; ++p) {
+    u64 *kp = (u64 *)cells + 2 * p;
+    u64 ck = *kp;
+    if (ck == kEmpty) {
+      ck = cas64(kp, kEmpty, key);
+      if (ck == kEmpty) {
+        add64(kp + 1, d);
+        d_new += 1;
+        return true;
+      }
+    }
+    if (ck == key) {
+      add64(kp + 1, d);
+      return true;
+    }
+  }
+  return false;
+}
+
+// FRESH (KV64 without flags; the table has no used cell): a bucket that is one
+// work item owns its region of the table, and its combined keys are distinct,
+// so each takes a cell by one bit of a map in LDS and writes key and sum with
+// one store; no compare-and-swap, whose memory-side rate (17.9 G/s) bounds the
+// other form.  Probes that run past the region's end are put off until all
+// regions are done (k_part_rest), also those of the buckets that go by
+// compare-and-swap here: of several items, or with more keys than LDS slots.
+// 10^8 keys of a Zipf(1) stream (18 * 10^6 distinct) on 2^28 cells: the apply
+// 1.60 -> 1.23 ms; 2^24 distinct keys on 2^26 cells: the call 1646 -> 751 us.
+// Of what is left (0.96 ms) 0.24 are loads, 0.2 the stores, and the rest the
+// combining in LDS.
+constexpr uint32_t kFreshBits = 16;  // cells of a region: at most 2^16 (a map of 8 KiB; two workgroups per CU)
+
+template <int L, bool VALS, bool FL, bool FRESH>
+__global__ void __launch_bounds__(kApplyThreads, FL ? 4 : 8) k_part_apply(PartK k) {
   constexpr uint32_t S = FL ? kSlotsFlags : kSlotsNoFlags;
   constexpr uint32_t SB = 12;
   static_assert((1u << SB) == S, "slot bits");
-  __shared__ uint32_t T[8][256];
+  static_assert(!FRESH || (L == 1 && !FL), "fresh: KV64 without flags");
+  __shared__ uint32_t T[FRESH ? 4 : 8][256];
+  __shared__ uint32_t s_taken[FRESH ? (1u << kFreshBits) / 32 : 1];
+  __shared__ uint32_t s_spilled[2];  // by turn: some key of the item found no LDS slot
   __shared__ u64 s_key[S];
   __shared__ u64 s_sum[S];
   __shared__ uint32_t s_rep[FL ? S : 1];
-  __shared__ uint32_t s_claims;
+  __shared__ uint32_t s_claims, s_next;
   __shared__ long long s_acc[2];
   __shared__ uint32_t s_err;
-  crc_tables_build(T);
+  const uint32_t rbits = k.A.log2c - k.bits, map = FRESH ? ((1u << rbits) + 31) / 32 : 0;
+  if constexpr (FRESH) {
+    crc_slices_load(&T[0][0]);
+    for (uint32_t q = threadIdx.x; q < map; q += blockDim.x) s_taken[q] = 0;
+  } else {
+    crc_tables_build(T);
+  }
+  if (threadIdx.x < 2) s_spilled[threadIdx.x] = 0;
   for (uint32_t q = threadIdx.x; q < S; q += blockDim.x) {
     s_key[q] = 0;
     s_sum[q] = 0;
@@ -493,17 +577,17 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
   long long d_used = 0, d_live = 0;
   uint32_t err = 0;
   const uint32_t nitems = k.items[1u << k.bits];
-  const u64 step = (u64)blockDim.x * kUnroll;
+  const u64 step = (u64)blockDim.x * kApplyUnroll;
   constexpr u64 kAlone = 1ull << 63;
-  u64 keys[kUnroll], ds[kUnroll];
-  uint32_t idxs[kUnroll];
+  u64 keys[kApplyUnroll], ds[kApplyUnroll];
+  uint32_t idxs[kApplyUnroll];
   auto load = [&](u64 pb, u64 hi) {
 #pragma unroll
-    for (uint32_t u = 0; u < kUnroll; ++u) {
+    for (uint32_t u = 0; u < kApplyUnroll; ++u) {
       const u64 p = pb + (u64)u * blockDim.x + threadIdx.x;
       const bool in = p < hi;
       keys[u] = in ? part_key<L>(k.keys[1], p) : 0;
-      ds[u] = in ? (k.vals[1] ? part_key<L>(k.vals[1], p) : 1) : 0;
+      ds[u] = VALS ? (in ? part_key<L>(k.vals[1], p) : 0) : 1;
       idxs[u] = in && FL ? k.idx[1][p] : 0;
     }
   };
@@ -517,13 +601,13 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
     alone = (s0 & kAlone) != 0;
     load(lo, hi);
   }
-  for (uint32_t it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const uint32_t nx = it + gridDim.x;
+  uint32_t turn = 0;
+  for (uint32_t it = blockIdx.x, nx = it + gridDim.x; it < nitems; turn ^= 1) {
     for (u64 pb = lo; pb < hi; pb += step) {
-     u64 ck[kUnroll], cd[kUnroll];
-     uint32_t ci[kUnroll];
+     u64 ck[kApplyUnroll], cd[kApplyUnroll];
+     uint32_t ci[kApplyUnroll];
 #pragma unroll
-     for (uint32_t u = 0; u < kUnroll; ++u) {
+     for (uint32_t u = 0; u < kApplyUnroll; ++u) {
        ck[u] = keys[u];
        cd[u] = ds[u];
        ci[u] = idxs[u];
@@ -535,7 +619,8 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
      } else if (nx < nitems) {
        load(k.istart[nx] & ~kAlone, k.istart[nx + 1] & ~kAlone);
      }
-     for (uint32_t u = 0; u < kUnroll; ++u) {
+#pragma unroll
+     for (uint32_t u = 0; u < kApplyUnroll; ++u) {
       // equal keys on the lanes of this step first (a batch key is never 0
       // here, so 0 marks lanes past the end)
       bool act = ck[u] != 0;
@@ -548,10 +633,10 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
         u64 lk = 0;
         uint32_t ll = 0;
         const u64 m = match_first(open, key, lk, ll);
-        if (__popcll(m) < 2) break;
+        if (__popcll(m) < kAggLanes) break;
         const bool in = (m >> (threadIdx.x & 63)) & 1;
         // without values every operation adds 1
-        const u64 sum = k.vals[1] ? (u64)wave_sum(in ? (long long)d : 0) : (u64)__popcll(m);
+        const u64 sum = VALS ? (u64)wave_sum(in ? (long long)d : 0) : (u64)__popcll(m);
         const uint32_t imin = FL ? wave_min_u32(in ? idx : ~0u) : 0;
         if (in) {
           open = false;
@@ -567,43 +652,90 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
       if (!act) continue;
       const bool claim = __hip_atomic_load(&s_claims, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <
                          S / 4 * 3;
-      uint32_t slot = lds_slot(key, SB);
+      // two slots a step: most keys are present, and a wavefront goes on until
+      // its last lane has found its own
+      auto slot_key = [&](uint32_t q) {
+        return __hip_atomic_load(&s_key[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      };
+      uint32_t slot = lds_slot(key, SB - 1) * 2;
       bool held = false;
-      for (uint32_t t = 0; t < kProbe; ++t, slot = (slot + 1) & (S - 1)) {
-        u64 cur;
-        if (claim) {
-          cur = atomicCAS((unsigned long long *)&s_key[slot], 0ull, (unsigned long long)key);
+      for (uint32_t t = 0; t < kProbe;) {
+        const u64 k0 = slot_key(slot), k1 = slot_key(slot + 1);
+        const uint32_t at = slot + (k0 == key || k0 == 0 ? 0 : 1);
+        u64 cur = k0 == key || k0 == 0 ? k0 : k1;
+        if (cur == 0) {
+          if (!claim) break;  // absent: no lane claims slots any more in this item
+          cur = atomicCAS((unsigned long long *)&s_key[at], 0ull, (unsigned long long)key);
           if (cur == 0) {
             atomicAdd(&s_claims, 1u);
-            held = true;
-            break;
+            cur = key;
+          } else if (cur != key) {
+            continue;  // another key took it: the pair again
           }
-        } else {
-          cur = __hip_atomic_load(&s_key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (cur == 0) break;  // absent: no lane claims slots any more in this item
         }
         if (cur == key) {
+          slot = at;
           held = true;
           break;
         }
+        slot = (slot + 2) & (S - 1);
+        t += 2;
       }
       if (held) {
         atomicAdd((unsigned long long *)&s_sum[slot], (unsigned long long)d);
         if (FL) atomicMin(&s_rep[slot], idx);
       } else {
         // applied on its own, by atomics, before the barrier below
-        const uint8_t f = upsert_add_one<L>(A, T, key, d, d_used, d_live, err);
-        if (FL) A.flags[idx] = f;
+        if constexpr (FRESH) {
+          const u64 p = hash_sliced<1>(&T[0][0], key, A.crc_hi, A.crc_lo, A.mul) >> (64 - A.log2c);
+          if (!upsert_add_region(A.cells, p, ((p >> rbits) + 1) << rbits, key, d, d_used)) put_off(k, key, d);
+          s_spilled[turn] = 1;
+        } else {
+          const uint8_t f = upsert_add_one<L>(A, T, key, d, d_used, d_live, err);
+          if (FL) A.flags[idx] = f;
+        }
       }
      }
     }
     __syncthreads();
     // nothing reads the claim count again before the barrier that ends the item
-    if (threadIdx.x == 0) s_claims = 0;
+    if (threadIdx.x == 0) {
+      s_claims = 0;
+      s_spilled[turn ^ 1] = 0;  // (the next item's)
+      s_next = 2 * gridDim.x + atomicAdd(k.next, 1u);
+    }
+    const bool own = FRESH && alone && !s_spilled[turn];
     // one upsert per distinct key of the item
     for (uint32_t q = threadIdx.x; q < S; q += blockDim.x) {
       const u64 key = s_key[q];
       if (key == 0) continue;
+      if constexpr (FRESH) {
+        const u64 d = s_sum[q], p = hash_sliced<1>(&T[0][0], key, A.crc_hi, A.crc_lo, A.mul) >> (64 - A.log2c);
+        const u64 first = p >> rbits << rbits;
+        if (own) {
+          uint32_t c = (uint32_t)(p - first);
+          while (c < (1u << rbits)) {
+            const uint32_t free = ~s_taken[c >> 5] & (~0u << (c & 31));
+            if (free) {
+              c = (c & ~31u) | (uint32_t)__builtin_ctz(free);
+              if (!(atomicOr(&s_taken[c >> 5], 1u << (c & 31)) >> (c & 31) & 1u)) break;
+            } else {
+              c = (c | 31u) + 1;
+            }
+          }
+          if (c < (1u << rbits)) {
+            ((u64x2 *)A.cells)[first + c] = u64x2{key, d};
+            d_used += 1;
+          } else {
+            put_off(k, key, d);
+          }
+        } else if (!upsert_add_region(A.cells, p, first + (1ull << rbits), key, d, d_used)) {
+          put_off(k, key, d);
+        }
+        s_key[q] = 0;
+        s_sum[q] = 0;
+        continue;
+      }
       const uint8_t f = (L == 1 && alone) ? upsert_add_excl_kv64(A, T, key, s_sum[q], d_used, d_live, err)
                                           : upsert_add_one<L>(A, T, key, s_sum[q], d_used, d_live, err);
       if (FL) {
@@ -614,18 +746,71 @@ __global__ void __launch_bounds__(apply_threads<FL>()) k_part_apply(PartK k) {
       s_sum[q] = 0;
     }
     __syncthreads();
+    if (own)
+      for (uint32_t q = threadIdx.x; q < map; q += blockDim.x) s_taken[q] = 0;
     if (nx < nitems) {
       const u64 s0 = k.istart[nx];
       lo = s0 & ~kAlone;
       hi = k.istart[nx + 1] & ~kAlone;
       alone = (s0 & kAlone) != 0;
     }
+    it = nx;
+    nx = s_next;
   }
+  if (FRESH) d_live = d_used;
   flush_counts(A.status, d_used, d_live, err, s_acc, &s_err);
 }
 
+// The keys put off, one lane each on the whole table.
+__global__ void __launch_bounds__(256) k_part_rest(PartK k) {
+  __shared__ long long s_acc[2];
+  __shared__ uint32_t s_err;
+  const u64 *keys = (const u64 *)k.keys[0];
+  const u64 n0 = k.off[0], n = n0 + k.off[1];
+  long long d_used = 0;
+  uint32_t err = 0;
+  for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < n; i += (u64)gridDim.x * 256) {
+    u64 key, d = 1, none;
+    if (i < n0) {
+      key = keys[i];
+      if (k.vals[0]) d = ((const u64 *)k.vals[0])[i];
+    } else {
+      const u64 *e = keys + (k.A.n - 2 - 2 * (i - n0));
+      d = e[0];
+      key = e[1];
+    }
+    const uint8_t f = lane_op<1, OP_UPSERT, 1, 4>(k.A, key, d, none);
+    if (f == 0xFF)
+      err |= kErrFull;
+    else
+      d_used += f;
+  }
+  flush_counts(k.A.status, d_used, d_used, err, s_acc, &s_err);
+}
+
+// As many apply workgroups as fit at once (LDS bounds them).
+template <int L, bool VALS>
+hipError_t launch_apply(const PartK &k, bool fresh, uint32_t num_cus, hipStream_t s) {
+  const uint32_t cus = std::max<uint32_t>(1, num_cus);
+  if (k.A.flags) {
+    hipLaunchKernelGGL((k_part_apply<L, VALS, true, false>), dim3(cus), dim3(kApplyThreads), 0, s, k);
+    return hipGetLastError();
+  }
+  if constexpr (L == 1) {
+    if (fresh && k.A.log2c - k.bits <= kFreshBits) {
+      hipLaunchKernelGGL((k_part_apply<L, VALS, false, true>), dim3(2 * cus), dim3(kApplyThreads), 0, s, k);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(k_part_rest, dim3(cus), dim3(256), 0, s, k);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_part_apply<L, VALS, false, false>), dim3(2 * cus), dim3(kApplyThreads), 0, s, k);
+  return hipGetLastError();
+}
+
 struct Carved {
-  size_t btot, hist, cur[2], tiles, items, istart, keys[2], vals[2], idx[2], total;
+  size_t off, btot, hist, cur[2], tiles, items, istart, keys[2], vals[2], idx[2], total;
 };
 
 Carved carve(uint64_t n, uint32_t log2c, uint32_t layout, bool with_vals, bool with_flags, uint32_t nwg) {
@@ -638,6 +823,7 @@ Carved carve(uint64_t n, uint32_t log2c, uint32_t layout, bool with_vals, bool w
     at += round256(bytes);
     return p;
   };
+  o.off = take(16);
   o.btot = take(((size_t)nb + 1) * 8);
   o.hist = take((size_t)nwg * nb * 4);
   o.cur[0] = take((size_t)nb0 * kPad * 4);
@@ -672,7 +858,7 @@ size_t part_scratch_bytes(uint64_t n, uint32_t log2c, uint32_t layout, bool with
   return carve(n, log2c, layout, with_vals, with_flags, count_wgs(n)).total;
 }
 
-hipError_t launch_upsert_add_part(const BulkArgs &a, void *scratch, uint32_t num_cus, hipStream_t s) {
+hipError_t launch_upsert_add_part(const BulkArgs &a, bool fresh, void *scratch, uint32_t num_cus, hipStream_t s) {
   drop_stale_error();
   if (a.n == 0) return hipSuccess;
   if (!part_applies(a.n, a.log2c) || a.layout > 1 || !scratch || a.kinds) return hipErrorInvalidValue;
@@ -683,6 +869,8 @@ hipError_t launch_upsert_add_part(const BulkArgs &a, void *scratch, uint32_t num
   const Carved o = carve(a.n, a.log2c, a.layout, a.vals != nullptr, a.flags != nullptr, k.nwg);
   unsigned char *base = (unsigned char *)scratch;
   k.bits = bucket_bits(a.log2c);
+  k.off = (uint32_t *)(base + o.off);
+  k.next = k.off + 2;
   k.btot = (uint64_t *)(base + o.btot);
   k.hist = (uint32_t *)(base + o.hist);
   k.tiles = (uint32_t *)(base + o.tiles);
@@ -694,7 +882,6 @@ hipError_t launch_upsert_add_part(const BulkArgs &a, void *scratch, uint32_t num
     k.vals[lv] = a.vals ? (void *)(base + o.vals[lv]) : nullptr;
     k.idx[lv] = a.flags ? (uint32_t *)(base + o.idx[lv]) : nullptr;
   }
-  const uint32_t cus = std::max<uint32_t>(1, num_cus);
   hipError_t e;
   hipLaunchKernelGGL(k_part_zero, dim3(1), dim3(1024), 0, s, k);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -715,19 +902,11 @@ hipError_t launch_upsert_add_part(const BulkArgs &a, void *scratch, uint32_t num
     e = vals ? (idx ? launch_scatters<1, true, true>(k, s) : launch_scatters<1, true, false>(k, s))
              : (idx ? launch_scatters<1, false, true>(k, s) : launch_scatters<1, false, false>(k, s));
   if (e != hipSuccess) return e;
-  // as many apply workgroups as fit at once (LDS bounds them)
-  if (a.flags) {
-    if (a.layout == 0)
-      hipLaunchKernelGGL((k_part_apply<0, true>), dim3(cus), dim3(apply_threads<true>()), 0, s, k);
-    else
-      hipLaunchKernelGGL((k_part_apply<1, true>), dim3(cus), dim3(apply_threads<true>()), 0, s, k);
-  } else {
-    if (a.layout == 0)
-      hipLaunchKernelGGL((k_part_apply<0, false>), dim3(2 * cus), dim3(apply_threads<false>()), 0, s, k);
-    else
-      hipLaunchKernelGGL((k_part_apply<1, false>), dim3(2 * cus), dim3(apply_threads<false>()), 0, s, k);
-  }
-  return hipGetLastError();
+  if (a.layout == 0)
+    e = vals ? launch_apply<0, true>(k, fresh, num_cus, s) : launch_apply<0, false>(k, fresh, num_cus, s);
+  else
+    e = vals ? launch_apply<1, true>(k, fresh, num_cus, s) : launch_apply<1, false>(k, fresh, num_cus, s);
+  return e;
 }
 
 }  // namespace lpht
