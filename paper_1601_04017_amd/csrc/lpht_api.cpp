@@ -218,6 +218,7 @@ int migrate_once(lpht_table *t, uint32_t log2_new, hipStream_t s) {
 // migration out.
 int grow_before_batch(lpht_table *t, uint64_t b, hipStream_t s) {
   if (b == 0) return LPHT_OK;
+  if (!t->captured && capturing(s)) t->captured = true;
   if (!t->cfg.auto_grow) {
     t->pending += b;
     return LPHT_OK;
@@ -329,7 +330,7 @@ int run_bulk(lpht_table *t, OpKind op, const void *keys, const void *vals, uint6
                                          t->launch.num_cus);
     void *scratch = dev_alloc(t, sb, s);
     if (scratch) {
-      const bool fresh = t->known_used + t->pending == n && !capturing(s);
+      const bool fresh = t->known_used + t->pending == n && !t->captured;
       const hipError_t e = launch_upsert_add_part(a, fresh, scratch, t->launch.num_cus, s);
       dev_free(t, scratch, sb, s);
       if (e != hipSuccess) return from_hip(e);
@@ -350,7 +351,7 @@ int run_bulk(lpht_table *t, OpKind op, const void *keys, const void *vals, uint6
     const size_t sb = load_scratch_bytes(n, t->log2c, t->cfg.layout, flags != nullptr);
     void *scratch = dev_alloc(t, sb, s);
     if (scratch) {
-      const hipError_t e = launch_load(op, a, used0 == 0, scratch, s);
+      const hipError_t e = launch_load(op, a, used0 == 0 && !t->captured, scratch, s);
       dev_free(t, scratch, sb, s);
       if (e != hipSuccess) return from_hip(e);
       if (t->special)
@@ -619,6 +620,7 @@ int lpht_create(const lpht_config *cfg, void *stream, lpht_table **out) {
   }
   t->log2c = cfg->log2_capacity;
   t->log2_min = cfg->log2_capacity;
+  t->captured = capturing(s);
   hipError_t e = launch_clear(t->cells, nb, t->status, 1, s);
   if (e == hipSuccess && cfg->full_keys) {
     t->special = (SpecialSlots *)dev_alloc(t, sizeof(SpecialSlots), s);
@@ -646,6 +648,7 @@ int lpht_clear(lpht_table *t, void *stream) {
   hipError_t e = launch_clear(t->cells, (size_t)cell_bytes(t->cfg.layout) << t->log2c, t->status, 1, s);
   if (e == hipSuccess && t->special) e = launch_fill_zero(t->special, sizeof(SpecialSlots), t->launch, s);
   if (e != hipSuccess) return from_hip(e);
+  if (capturing(s)) t->captured = true;
   t->known_used = t->known_live = 0;
   t->pending = 0;
   t->mods_since_exact = 0;

@@ -32,6 +32,9 @@ struct lpht_table {
   // modifying calls since known_used/known_live were last read exactly; when
   // zero the growth rule decides without reading the device counters
   uint64_t mods_since_exact;
+  // an insertion or a clear of this table was captured into a graph: a replay
+  // changes the table without the host's counts, which prove no emptiness then
+  bool captured;
   lpht_tuning tuning;
   lpht::LaunchCfg launch;
   lpht_stats stats;
