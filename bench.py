@@ -70,14 +70,26 @@ def algorithmic_bytes_per_op(alpha):
         # key in + value out + found flag out
         "find_hit": lines_s * LINE + 17,
         "find_miss": lines_u * LINE + 17,
-        # average insertion cost over the fill from 0 to alpha equals the
-        # successful-search cost; the line is read and written back; key and
-        # value in
-        "insert": 2 * lines_s * LINE + 16,
+        # the load of an empty table by region: key and value read from the
+        # batch, written and read by each of two partition levels, and the
+        # lines that hold an element written once
+        "insert": 16 + 2 * 2 * 16 + LINE * lines_written_per_op(alpha),
     }
 
 
-OP_CODE = {"insert": 1, "find_hit": 0, "find_miss": 0}
+def lines_written_per_op(alpha):
+    """128-byte lines with an element, per element, of a table at fill alpha."""
+    return (1 - (1 - alpha) ** CELLS_PER_LINE) / (alpha * CELLS_PER_LINE)
+
+
+def phase_kernels(phase, widths):
+    """The kernels of a phase of the headline step: the insertion of 10^8 keys
+    into an empty table goes region by region whatever the width; a find of
+    width 1 is one lane per operation (two cells looked ahead up to half
+    full)."""
+    if phase == "insert":
+        return ["k_load_scatter<1, 1, false, 0>", "k_load_scatter<1, 1, false, 1>", "k_load_apply<1, 1, false>"]
+    return ["k_lane<1, 0, 0, 2>" if g == 1 else f"k_bulk<1, 0, 0, {g}>" for g in widths]
 
 
 def phase_widths(tun, op, used0, n, c):
@@ -107,9 +119,9 @@ def phase_widths(tun, op, used0, n, c):
 
 
 def measured_traffic(phase, widths):
-    """HBM bytes of the phase's launches (one per width) from the committed
-    rocprofv3 counter summary (FETCH_SIZE + WRITE_SIZE, calibrated), or None
-    when the summary is missing or was taken with a different kernel source."""
+    """HBM bytes of the phase's launches from the committed rocprofv3 counter
+    summary (FETCH_SIZE + WRITE_SIZE, calibrated), or None when the summary is
+    missing or was taken with a different kernel source."""
     from paper_1601_04017_amd import profsum
 
     path = os.path.join(ROOT, "profiles", "k_bulk_kv64_headline_step.traffic.json")
@@ -119,8 +131,8 @@ def measured_traffic(phase, widths):
     if rec.get("kernel_source_sha") != profsum.kernel_source_sha():
         return None
     total = 0
-    for g in widths:
-        k = rec.get("per_kernel", {}).get(f"k_bulk<1, {OP_CODE[phase]}, 0, {g}>")
+    for name in phase_kernels(phase, widths):
+        k = rec.get("per_kernel", {}).get(name)
         if k is None:
             return None
         total += k["read_bytes"] + k["write_bytes"]
@@ -879,7 +891,8 @@ def main():
         "find_miss": bpo["find_miss"] * N_OPS / (ph_ms["find_miss"] / 1e3) / 1e9,
     }
     dominant = max(("insert", "find_hit", "find_miss"), key=lambda p: ph_ms[p])
-    # the group widths each phase's launches ran with
+    # the group widths the library picks for each phase's calls (the insertion
+    # into the empty table takes none)
     tun = t1.get_tuning()
     width = {"insert": phase_widths(tun, "insert", 0, N_OPS, 1 << LOG2C),
              "find_hit": phase_widths(tun, "find", N_OPS, 0, 1 << LOG2C),
@@ -887,15 +900,15 @@ def main():
     traffic = measured_traffic(dominant, width[dominant])
     roofline_out = {
         "bound": "hbm",
-        "kernel": " + ".join(f"k_bulk<KV64,{dominant},G={g}>" for g in width[dominant]),
-        "launches": len(width[dominant]),
+        "kernel": " + ".join(phase_kernels(dominant, width[dominant])),
+        "launches": len(phase_kernels(dominant, width[dominant])),
         "achieved": round(ach[dominant], 1),
         "peak": HBM_PEAK_GBS,
         "unit": "GB/s",
         "frac": round(ach[dominant] / HBM_PEAK_GBS, 4),
         "traffic": traffic,
-        # the phase's launches together (one per group width), timed with
-        # HIP events on the stream they run on
+        # the phase's launches together, timed with HIP events on the stream
+        # they run on
         "algorithmic_bytes_per_phase": round(bpo[dominant] * N_OPS),
     }
     if traffic:
@@ -959,7 +972,8 @@ def main():
         out["ceilings"] = ceil
         lines_s, lines_u = lines_per_op(alpha)
         r_line = ceil["gather16_Gps"]  # every random access fetches one whole line
-        bound_mops = {"insert": min(r_line / (2 * lines_s), ceil["cas_Gps"]) * 1e3,
+        # the region load streams: its bytes at the measured copy rate
+        bound_mops = {"insert": ceil["copy_GBs"] / bpo["insert"] * 1e3,
                       "find_hit": r_line / lines_s * 1e3, "find_miss": r_line / lines_u * 1e3}
         roofline_out["measured_random_access"] = {
             "R_line_G_per_s": r_line, "R_cas_G_per_s": ceil["cas_Gps"],

@@ -138,10 +138,11 @@ typedef struct lpht_tuning {
   uint32_t migrate_block; /* old cells per migration workgroup, power of two 256..8192 */
   uint32_t aggregate;     /* LPHT_ADD upserts: 1 (default): combine equal keys in LDS; calls of
                            * at least 2^22 operations on tables of at least 2^20 cells are first
-                           * partitioned by table region (top 12 hash bits), so that every
+                           * partitioned by table region (top 13 hash bits), so that every
                            * occurrence of a key is combined and each distinct key costs one
-                           * upsert (scratch: about (key width [+ value width] [+ 4 with flags])
-                           * bytes per operation, from the table's allocator); 2: LDS combining
+                           * upsert (scratch: about twice (key width [+ value width] [+ 4 with
+                           * flags]) bytes per operation and 32 MiB at most beside, from the
+                           * table's allocator; without it 2 is done); 2: LDS combining
                            * of 2048-operation chunks only; 0: no combining */
   /* Group width by fill quarter, used / capacity in [0, 1/4], (1/4, 1/2],
    * (1/2, 3/4], (3/4, 1] (the host's bound on `used` after the operations):
@@ -192,7 +193,11 @@ int lpht_destroy(lpht_table *t, void *stream);
  * value d; if several operations of the call carry the same absent key exactly
  * one of them succeeds and the stored value is the value of that operation.
  * `vals` NULL means every value is 1.  With auto_grow the table first grows so
- * that used + n <= alpha * c (bulk pre-growth, Sec. 5.5). */
+ * that used + n <= alpha * c (bulk pre-growth, Sec. 5.5).  Calls of 2^20
+ * operations and more on a nearly empty table are partitioned by table region
+ * first (scratch: about twice (key width + value width [+ 4 with flags]) bytes
+ * per operation from the table's allocator; without it the operations go to
+ * the table one by one). */
 int lpht_insert(lpht_table *t, const void *keys, const void *vals, uint64_t n, uint8_t *flags,
                 void *stream);
 

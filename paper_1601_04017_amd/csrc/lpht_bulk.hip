@@ -20,13 +20,15 @@
 //      range (k_bm_scan_rows, k_bm_scan_bins), and each workgroup writes its
 //      share in tiles of 1024 elements, equal keys of a tile combined in an
 //      LDS hash table (k_bm_scatter), the entries freed by combining marked
-//      with the empty key -- no global atomics;
+//      with the empty key -- no global atomics; without skew (no bin of
+//      more than kSkewTimes the average) nothing is combined, and tiles of
+//      4096 are put in bin order in LDS (k_bm_scatter_plain);
 //   B. one workgroup per first-level bin partitions its elements by the
 //      remaining l2 bits into blocks (k_bm_partition), combining equal keys
 //      again per chunk of 1024 elements, so a hot key reaches its block at
-//      most once per chunk;
-//   C. one wavefront per block sorts the block's elements in LDS (bitonic,
-//      k_bm_block_wave; a workgroup for blocks of more than 256 elements,
+//      most once per chunk (k_bm_partition_plain without skew, likewise);
+//   C. one wavefront per block sorts the block's elements in LDS (counting by
+//      home cell, bitonic where a cell is crowded: k_bm_block_wave; a workgroup for blocks of more than 256 elements,
 //      k_bm_block), removes equal keys and computes the block's carry
 //      function: the number of elements that run past the block's end is
 //      f(c) = max(a, c + m - B) when c elements run in from the left, with m

@@ -8,10 +8,10 @@
 // ---------------
 // A "group" of G lanes (G = 2, 4, 8, 16; all in one wavefront) works on one
 // operation at a time (G = 1, the default, has kernels of its own in
-// lpht_lane.hip; here it remains for the resident serving kernel).  The group scans the table in windows of G consecutive
-// cells aligned to G, so that for G = 8 (16-byte cells) or G = 16 (8-byte
-// cells) one window is one 128-byte line read by one coalesced load.  The
-// first window starts at the operation's home cell; lanes before it are
+// lpht_lane.hip; here it remains for the resident serving kernel).  The group
+// scans the table in windows of G consecutive cells aligned to G, so that for
+// G = 8 (16-byte cells) or G = 16 (8-byte cells) one window is one 128-byte
+// line read by one coalesced load.  The first window starts at the operation's home cell; lanes before it are
 // masked.  Group-wide decisions come from wave ballots, so the lanes of a
 // group always take the same branches.  When an operation finishes, its group
 // immediately takes the next one (grid-stride over operations), so short and

@@ -23,13 +23,16 @@ import os
 from collections import OrderedDict
 
 PKG = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SRCS = [os.path.join(PKG, "csrc", f) for f in ("lpht_kernels.hip", "lpht_migrate.h", "lpht_device.h", "lpht_internal.h")]
+KERNEL_SRCS = [os.path.join(PKG, "csrc", f) for f in (
+    "lpht_kernels.hip", "lpht_lane.hip", "lpht_lane.h", "lpht_lane_op.h", "lpht_load.hip", "lpht_load.h",
+    "lpht_migrate.h", "lpht_device.h", "lpht_internal.h")]
 SHRINK_SRCS = [os.path.join(PKG, "csrc", f)
                for f in ("lpht_shrink.hip", "lpht_shrink.h", "lpht_device.h", "lpht_internal.h")]
 STR_SRCS = [os.path.join(PKG, "csrc", f) for f in ("lpht_str.hip", "lpht_str.h", "lpht_device.h", "lpht_internal.h")]
 ASYNC_SRCS = [os.path.join(PKG, "csrc", f)
               for f in ("lpht_async.hip", "lpht_async.h", "lpht_migrate.h", "lpht_device.h", "lpht_internal.h")]
-PART_SRCS = [os.path.join(PKG, "csrc", f) for f in ("lpht_part.hip", "lpht_part.h", "lpht_device.h", "lpht_internal.h")]
+PART_SRCS = [os.path.join(PKG, "csrc", f) for f in ("lpht_part.hip", "lpht_part.h", "lpht_lane_op.h", "lpht_device.h",
+                                                     "lpht_internal.h")]
 
 
 def kernel_source_sha(srcs=None) -> str:
@@ -88,7 +91,7 @@ def main():
     ap.add_argument("--copy-bytes", type=float, default=float(1 << 31),
                     help="bytes read (= bytes written) by one calibration copy")
     ap.add_argument("--cmd", required=True, help="the commands that produced the CSV files")
-    ap.add_argument("--dominant", default="k_bulk<1, 1, 0, 1>",
+    ap.add_argument("--dominant", default="k_lane<1, 0, 0, 2>",
                     help="kernel whose bytes per launch go into the benchmark's roofline")
     ap.add_argument("--min-frac", type=float, default=0.05,
                     help="ignore dispatches whose count is below this fraction of the kernel's "
