@@ -371,12 +371,13 @@ hipError_t launch_str_op(int kind, const StrArgs &a, uint32_t num_cus, hipStream
   return hipGetLastError();
 }
 
-hipError_t launch_str_insert(int kind, const StrArgs &all, void *scratch, uint32_t num_cus, hipStream_t s) {
+hipError_t launch_str_insert(int kind, const StrArgs &all, uint64_t slice, void *scratch, uint32_t num_cus, hipStream_t s) {
   drop_stale_error();
   if (kind != kStrInsert && kind != kStrUpsert) return hipErrorInvalidValue;
-  for (u64 lo = 0; lo < all.n; lo += kStrSlice) {
+  if (slice == 0) return hipErrorInvalidValue;
+  for (u64 lo = 0; lo < all.n; lo += slice) {
     StrArgs a = all;
-    a.n = all.n - lo < kStrSlice ? all.n - lo : kStrSlice;
+    a.n = all.n - lo < slice ? all.n - lo : slice;
     a.offsets = all.offsets + lo;
     a.vals = all.vals ? all.vals + lo : nullptr;
     a.flags = all.flags ? all.flags + lo : nullptr;

@@ -188,9 +188,15 @@ int run(lpht_str_table *t, int kind, const uint8_t *bytes, const uint64_t *offse
   a.vals_out = vals_out;
   a.flags = flags;
   if (kind == kStrFind || kind == kStrErase) return from_hip(launch_str_op(kind, a, t->num_cus, s));
-  void *scratch = alloc(t, std::min(n, kStrSlice) * 16, s);
+  // where memory is short, in smaller slices
+  uint64_t slice = std::min(n, kStrSlice);
+  void *scratch = alloc(t, slice * 16, s);
+  while (!scratch && slice > 256) {
+    slice /= 2;
+    scratch = alloc(t, slice * 16, s);
+  }
   if (!scratch) return LPHT_ERR_OOM;
-  const hipError_t e = launch_str_insert(kind, a, scratch, t->num_cus, s);
+  const hipError_t e = launch_str_insert(kind, a, slice, scratch, t->num_cus, s);
   release(scratch, s);
   return from_hip(e);
 }
