@@ -41,6 +41,7 @@
 #include "lpht_async.h"
 #include "lpht_device.h"
 #include "lpht_migrate.h"
+#include "lpht_wgwait.h"
 
 namespace lpht {
 
@@ -97,6 +98,11 @@ __device__ __forceinline__ View view_of(const AsyncArgs &a, uint32_t e, uint32_t
   return v;
 }
 
+struct ThisWorkgroup {
+  __device__ bool leader() const { return threadIdx.x == 0; }
+  __device__ void sync() const { __syncthreads(); }
+};
+
 // The waits of a growth are made by one wavefront for its workgroup: every
 // poll of a line takes its turn at 12 ns, and with 2048 wavefronts polling,
 // each arrival counted on that line queued behind 25 us of polls.
@@ -104,44 +110,28 @@ __device__ __forceinline__ View view_of(const AsyncArgs &a, uint32_t e, uint32_t
 // Waits until *p >= target; false if the bound passed.  Called by all
 // wavefronts of the workgroup; s_word is LDS of the workgroup's.
 __device__ bool wait_ge(const uint32_t *p, uint32_t target, u64 ticks, uint32_t *s_word) {
-  if (threadIdx.x == 0) {
-    uint32_t ok = 1;
-    const u64 t0 = wall_clock64();
-    while (ld32(p) < target) {
-      if (wall_clock64() - t0 > ticks) {
-        ok = 0;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(4);
-    }
-    *s_word = ok;
-  }
-  __syncthreads();
-  const bool ok = uni(*s_word) != 0;
-  __syncthreads();  // read before the next wait writes it
-  return ok;
+  return uni(wg_wait(ThisWorkgroup{}, s_word, [&]() -> uint32_t {
+           const u64 t0 = wall_clock64();
+           while (ld32(p) < target) {
+             if (wall_clock64() - t0 > ticks) return 0;
+             __builtin_amdgcn_s_sleep(4);
+           }
+           return 1;
+         })) != 0;
 }
 
-// Waits until gen moved past `g`; returns the new gen, or ~0u on timeout.
+// Waits until gen moved past `g`; returns the new gen, or 0 if the bound
+// passed (a growth ends with a gen of at least 2).
 __device__ uint32_t wait_gen_past(const uint32_t *gen, uint32_t g, u64 ticks, uint32_t *s_word) {
-  if (threadIdx.x == 0) {
-    uint32_t r;
+  return uni(wg_wait(ThisWorkgroup{}, s_word, [&]() -> uint32_t {
     const u64 t0 = wall_clock64();
     for (;;) {
-      r = ld32(gen);
-      if (r != g) break;
-      if (wall_clock64() - t0 > ticks) {
-        r = ~0u;
-        break;
-      }
+      const uint32_t r = ld32(gen);
+      if (r != g) return r;
+      if (wall_clock64() - t0 > ticks) return 0;
       __builtin_amdgcn_s_sleep(4);
     }
-    *s_word = r;
-  }
-  __syncthreads();
-  const uint32_t r = uni(*s_word);
-  __syncthreads();
-  return r;
+  }));
 }
 
 __device__ __forceinline__ uint32_t lane0_add(uint32_t *p, uint32_t d) {
@@ -361,6 +351,7 @@ __global__ void __launch_bounds__(256) k_async_insert(AsyncArgs a, u64 ticks, ui
   __shared__ uint32_t T[8][256];
   __shared__ __attribute__((aligned(16))) unsigned char wl[4][kWaveLds];
   __shared__ uint32_t s_word;
+  if (threadIdx.x == 0) s_word = 0;
   crc_tables_build(T);
   unsigned char *wlds = wl[threadIdx.x >> 6];
   ChunkLds &C = *reinterpret_cast<ChunkLds *>(wlds);
@@ -500,8 +491,7 @@ __global__ void __launch_bounds__(256) k_async_insert(AsyncArgs a, u64 ticks, ui
         break;
       }
       clear_chunk();  // the migration used its LDS
-      const uint32_t g2 = wait_gen_past(gen, g, ticks, &s_word);
-      if (g2 == ~0u) {
+      if (wait_gen_past(gen, g, ticks, &s_word) == 0) {
         err = 1;
         break;
       }

@@ -30,7 +30,7 @@ SHRINK_SRCS = [os.path.join(PKG, "csrc", f)
                for f in ("lpht_shrink.hip", "lpht_shrink.h", "lpht_device.h", "lpht_internal.h")]
 STR_SRCS = [os.path.join(PKG, "csrc", f) for f in ("lpht_str.hip", "lpht_str.h", "lpht_device.h", "lpht_internal.h")]
 ASYNC_SRCS = [os.path.join(PKG, "csrc", f)
-              for f in ("lpht_async.hip", "lpht_async.h", "lpht_migrate.h", "lpht_device.h", "lpht_internal.h")]
+              for f in ("lpht_async.hip", "lpht_async.h", "lpht_wgwait.h", "lpht_migrate.h", "lpht_device.h", "lpht_internal.h")]
 PART_SRCS = [os.path.join(PKG, "csrc", f) for f in ("lpht_part.hip", "lpht_part.h", "lpht_lane_op.h", "lpht_device.h",
                                                      "lpht_internal.h")]
 
