@@ -2,36 +2,42 @@
 // scratch, kept for reuse after they are freed (the paper's user-space memory
 // pool, Sec. 7).
 //
-// Why not the runtime's stream-ordered pool: a block freed by an object of
-// one pass and asked for by the next went through page mapping again, and the
-// next kernel launch waited for it.  Growing a table from 4096 cells with
-// 2 * 10^7 keys took 57 ms a pass of which the kernels are 3.5, an insertion of
-// 10^7 Zipf keys growing inside the kernel 30 ms of 6; with this cache 3.4 and
-// 6.1 ms.
+// Why not the runtime's stream-ordered pool alone: a block freed by an object
+// of one pass and asked for by the next went through page mapping again, and
+// the next kernel launch waited for it.  Growing a table from 4096 cells with
+// 2 * 10^7 keys took 57 ms a pass of which the kernels were 3.5, an insertion of
+// 10^7 Zipf keys growing inside the kernel 30 ms of 6; with this cache in front
+// of it, and the same kernels, 3.4 and 6.1 ms.
 //
-// Blocks come from hipMalloc in size classes.  A freed block carries an event
-// recorded on the stream it was freed on, since work queued there may still
-// use it (the old table of a migration just enqueued):
+// Blocks come from a pool of the runtime (hipMallocFromPoolAsync) in size
+// classes and go back to it by hipFreeAsync: hipMalloc is refused, and ruins the
+// capture, while any other stream is captured in the global mode, and hipFree
+// waits for every stream of the device, a resident kernel's among them.  A freed
+// block carries an event recorded on the stream it was freed on, since work
+// queued there may still use it (the old table of a migration just enqueued):
 //   - an allocation ordered on the same stream takes it at once, behind a
 //     stream wait on that event (free of charge in stream order, and right
 //     even if the handle has come to name another stream since);
 //   - any other allocation takes it only once the event has completed.
 // What is cached is bounded by a quarter of the device's memory; beyond that,
-// and when an allocation fails, the blocks freed longest ago go back to HIP.
-// All of it goes back in release_pools.
+// and when an allocation fails, the blocks freed longest ago go back (the
+// runtime's pool keeps none of it past the next synchronisation).  Everything
+// goes back in release_pools.
 //
 // While a stream is being captured no block of the cache is handed out, since
 // a replay would use it at any later time: allocations of a capturing stream
-// come from a hipMemPool, and their frees wait for release_pools unless their
-// events can be queried.
+// become nodes of its graph, from a pool of their own, and their frees wait for
+// release_pools.  The events' queries are made in the relaxed capture mode, so
+// that they pass, and harm nothing, while some other thread captures.
 
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
+#include <chrono>
 #include <cstdint>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -56,7 +62,7 @@ constexpr int kMaxDevices = 64;
 
 struct Free {
   void *p;
-  hipEvent_t ev;      // null: never used since hipMalloc
+  hipEvent_t ev;      // null: never used yet
   hipStream_t s;      // the stream it was freed on
   uint64_t seq;       // order of the frees
 };
@@ -72,7 +78,7 @@ struct Device {
   std::unordered_map<uint32_t, std::vector<Free>> free;  // by class, oldest first
   std::vector<void *> slabs;
   uint64_t cached = 0, limit = 0;
-  hipMemPool_t graph_pool = nullptr;
+  hipMemPool_t pool = nullptr, graph_pool = nullptr;
   // blocks whose event cannot be waited on: given back by release_pools
   std::vector<Free> stuck;
 };
@@ -83,7 +89,7 @@ std::unordered_map<void *, Block> g_blocks;  // every block the library holds
 std::vector<hipEvent_t> g_events;            // spare
 uint64_t g_seq = 0;
 // blocks handed out by pool_alloc and not yet given back to pool_free
-std::atomic<long long> g_out{0};
+long long g_out = 0;
 
 // Classes: powers of two up to 64 KiB, above that eight steps per power of
 // two (at most an eighth is lost).  A class is its size's exponent and eighth.
@@ -119,6 +125,16 @@ struct OnDevice {
   }
   ~OnDevice() {
     if (before >= 0) (void)hipSetDevice(before);
+  }
+};
+
+// The calling thread's HIP calls in the relaxed capture mode.
+struct Relaxed {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  bool ok;
+  Relaxed() : ok(hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {}
+  ~Relaxed() {
+    if (ok) (void)hipThreadExchangeStreamCaptureMode(&mode);
   }
 };
 
@@ -161,9 +177,10 @@ void *take(Device &D, uint32_t cls, hipStream_t s, bool in_order) {
   return nullptr;
 }
 
-// Gives cached blocks back to HIP, the one freed longest ago first, until
-// `keep` bytes are left.  `wait`: those still in use are waited for.
-void trim(Device &D, uint64_t keep, bool wait) {
+// Gives cached blocks whose last use has completed back, in stream order on s,
+// the one freed longest ago first, until `keep` bytes are left.  Waits for
+// nothing.  Returns the bytes given back; `busy`: some block is still in use.
+uint64_t give_back(Device &D, uint64_t keep, hipStream_t s, bool *busy = nullptr) {
   struct Ref {
     uint64_t seq;
     uint32_t cls;
@@ -175,32 +192,32 @@ void trim(Device &D, uint64_t keep, bool wait) {
       if (b != g_blocks.end() && !b->second.slab) order.push_back({f.seq, kv.first});
     }
   std::sort(order.begin(), order.end(), [](const Ref &a, const Ref &b) { return a.seq < b.seq; });
+  const uint64_t before = D.cached;
   for (const Ref &r : order) {
     if (D.cached <= keep) break;
     std::vector<Free> &v = D.free[r.cls];
-    for (size_t k = 0; k < v.size(); ++k) {
-      if (v[k].seq != r.seq) continue;
-      const Free f = v[k];
-      if (f.ev) {
-        const hipError_t e = wait ? hipEventSynchronize(f.ev) : hipEventQuery(f.ev);
-        if (e != hipSuccess) {
-          (void)hipGetLastError();
-          break;
-        }
-      }
-      if (hipFree(f.p) != hipSuccess) (void)hipGetLastError();
-      g_blocks.erase(f.p);
-      spare(f.ev);
-      D.cached -= class_bytes(r.cls);
-      v.erase(v.begin() + (long)k);
-      break;
+    const auto at = std::find_if(v.begin(), v.end(), [&](const Free &f) { return f.seq == r.seq; });
+    if (at == v.end()) continue;
+    const hipError_t e = at->ev ? hipEventQuery(at->ev) : hipSuccess;
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      if (busy && e == hipErrorNotReady) *busy = true;
+      continue;
     }
+    if (hipFreeAsync(at->p, s) != hipSuccess) (void)hipGetLastError();
+    g_blocks.erase(at->p);
+    spare(at->ev);
+    D.cached -= class_bytes(r.cls);
+    v.erase(at);
   }
+  return before - D.cached;
 }
 
-hipMemPool_t graph_pool(int dev) {
-  Device &D = g_dev[dev];
-  if (!D.graph_pool) {
+// The runtime's pool behind one of a device's handles, made at first use.
+// keep: it holds freed memory until it is trimmed (a graph's allocations),
+// otherwise until the next synchronisation.
+hipMemPool_t runtime_pool(hipMemPool_t &slot, int dev, bool keep) {
+  if (!slot) {
     hipMemPoolProps props{};
     props.allocType = hipMemAllocationTypePinned;
     props.handleTypes = hipMemHandleTypeNone;
@@ -208,42 +225,69 @@ hipMemPool_t graph_pool(int dev) {
     props.location.id = dev;
     hipMemPool_t pool = nullptr;
     if (hipMemPoolCreate(&pool, &props) != hipSuccess) return nullptr;
-    uint64_t keep = ~0ull;
-    (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
-    D.graph_pool = pool;
+    uint64_t threshold = keep ? ~0ull : 0ull;
+    (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &threshold);
+    slot = pool;
   }
-  return D.graph_pool;
+  return slot;
 }
 
 void *graph_alloc(int device, size_t bytes, hipStream_t s) {
-  std::lock_guard<std::mutex> lk(g_mu);
-  hipMemPool_t pool = graph_pool(device);
+  hipMemPool_t pool = runtime_pool(g_dev[device].graph_pool, device, true);
   void *p = nullptr;
   if (!pool || hipMallocFromPoolAsync(&p, bytes, pool, s) != hipSuccess) return nullptr;
   g_blocks[p] = {kGraphBlock, device, true};
   return p;
 }
 
-// A new block (with the lock held by `lk`, given up around hipMalloc).
-void *fresh(int device, uint32_t cls, std::unique_lock<std::mutex> &lk) {
+// How long an allocation that found no memory waits for cached blocks still in
+// use (a table destroyed just before another one as large is made).
+constexpr auto kRoomWait = std::chrono::milliseconds(200);
+
+// `nb` bytes from the runtime's pool, in stream order on s; with the lock held
+// by `lk`, given up while the runtime maps memory or a wait goes on.
+void *from_runtime(int device, size_t nb, hipStream_t s, bool in_order, std::unique_lock<std::mutex> &lk) {
+  Device &D = g_dev[device];
+  hipMemPool_t pool = runtime_pool(D.pool, device, false);
+  if (!pool) return nullptr;
+  const auto attempt = [&]() -> void * {
+    void *p = nullptr;
+    lk.unlock();
+    const hipError_t e = hipMallocFromPoolAsync(&p, nb, pool, s);
+    if (e != hipSuccess) (void)hipGetLastError();
+    lk.lock();
+    return e == hipSuccess ? p : nullptr;
+  };
+  if (void *p = attempt()) return p;
+  const auto until = std::chrono::steady_clock::now() + kRoomWait;
+  for (bool first = true;; first = false) {
+    bool busy = false;
+    const uint64_t given = give_back(D, 0, s, &busy);
+    if (first || given) {
+      if (hipMemPoolTrimTo(pool, 0) != hipSuccess) (void)hipGetLastError();
+      if (void *p = attempt()) return p;
+    }
+    // (a kernel already running waits for a block that is not in stream order)
+    if (!busy || !in_order || std::chrono::steady_clock::now() > until) return nullptr;
+    lk.unlock();
+    std::this_thread::sleep_for(std::chrono::microseconds(100));
+    lk.lock();
+  }
+}
+
+// A new block (with the lock held by `lk`).
+void *fresh(int device, uint32_t cls, hipStream_t s, bool in_order, std::unique_lock<std::mutex> &lk) {
   Device &D = g_dev[device];
   const size_t cb = class_bytes(cls);
   const bool slab = cb <= ((size_t)1 << kSmallLog2);
   const size_t nb = slab ? kSlabBytes : cb;
-  void *p = nullptr;
-  lk.unlock();
-  hipError_t e = hipMalloc(&p, nb);
-  lk.lock();
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    trim(D, 0, true);
-    if ((e = hipMalloc(&p, nb)) != hipSuccess) return nullptr;
-  }
+  void *p = from_runtime(device, nb, s, in_order, lk);
+  if (!p) return nullptr;
   if (!slab) {
     g_blocks[p] = {cls, device, false};
     return p;
   }
-  // small classes are cut from slabs: one hipMalloc for many status blocks
+  // small classes are cut from slabs: one allocation for many status blocks
   D.slabs.push_back(p);
   for (size_t at = 0; at + cb <= nb; at += cb) {
     void *q = (unsigned char *)p + at;
@@ -256,22 +300,34 @@ void *fresh(int device, uint32_t cls, std::unique_lock<std::mutex> &lk) {
   return p;
 }
 
+void hold_bound(Device &D, int device, hipStream_t s) {
+  if (!D.limit) {
+    size_t total = 0;
+    if (hipDeviceTotalMem(&total, device) != hipSuccess) (void)hipGetLastError();
+    D.limit = std::max<uint64_t>(1ull << 30, total / 4);
+  }
+  if (D.cached > D.limit) (void)give_back(D, D.limit, s);
+}
+
 }  // namespace
 
 void *pool_alloc(int device, size_t bytes, hipStream_t s, bool in_order) try {
   if (device < 0 || device >= kMaxDevices) return nullptr;
   OnDevice on(device);
   if (!on.ok) return nullptr;
+  Relaxed relaxed;
+  const bool captured = capturing(s);
+  std::unique_lock<std::mutex> lk(g_mu);
+  Device &D = g_dev[device];
   void *p = nullptr;
-  if (capturing(s)) {
+  if (captured) {
     p = graph_alloc(device, bytes, s);
   } else {
     const uint32_t cls = class_of(bytes);
-    std::unique_lock<std::mutex> lk(g_mu);
-    p = take(g_dev[device], cls, s, in_order);
-    if (!p) p = fresh(device, cls, lk);
+    p = take(D, cls, s, in_order);
+    if (!p) p = fresh(device, cls, s, in_order, lk);
   }
-  if (p) g_out.fetch_add(1);
+  if (p) ++g_out;
   return p;
 } catch (const std::bad_alloc &) {
   return nullptr;  // host memory for the bookkeeping
@@ -279,60 +335,61 @@ void *pool_alloc(int device, size_t bytes, hipStream_t s, bool in_order) try {
 
 void pool_free(void *p, hipStream_t s) try {
   if (!p) return;
-  std::lock_guard<std::mutex> lk(g_mu);
-  const auto it = g_blocks.find(p);
-  if (it == g_blocks.end()) return;  // not of this pool
-  const Block b = it->second;
-  Device &D = g_dev[b.device];
-  OnDevice on(b.device);
-  g_out.fetch_sub(1);
+  Relaxed relaxed;
+  Block b;
   hipEvent_t ev = nullptr;
-  if (!g_events.empty()) {
-    ev = g_events.back();
-    g_events.pop_back();
-  } else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+  {
+    std::lock_guard<std::mutex> lk(g_mu);
+    const auto it = g_blocks.find(p);
+    if (it == g_blocks.end()) return;  // not of this pool
+    b = it->second;
+    if (!g_events.empty()) {
+      ev = g_events.back();
+      g_events.pop_back();
+    }
+  }
+  OnDevice on(b.device);
+  const bool captured = capturing(s);
+  if (!ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
     (void)hipGetLastError();
     ev = nullptr;
   }
-  const bool captured = capturing(s);
-  if (ev && hipEventRecord(ev, s) != hipSuccess) {
+  if (!captured && ev && hipEventRecord(ev, s) != hipSuccess) {
     (void)hipGetLastError();
     (void)hipEventDestroy(ev);
     ev = nullptr;
   }
-  if (captured || (!ev && hipStreamSynchronize(s) != hipSuccess)) {
-    // freed inside a capture, or nothing to wait for: out of use until the
-    // pools are released after a device synchronisation
+  // freed inside a capture, or outside the capture it was allocated in, or with
+  // nothing to wait for: out of use until the pools are released after a device
+  // synchronisation
+  bool out_of_use = captured || b.cls == kGraphBlock;
+  if (!out_of_use && !ev && hipStreamSynchronize(s) != hipSuccess) {
     (void)hipGetLastError();
-    D.stuck.push_back({p, ev, s, ++g_seq});
-    return;
+    out_of_use = true;
   }
-  if (b.cls == kGraphBlock) {
-    // freed outside the capture it was allocated in
-    D.stuck.push_back({p, ev, s, ++g_seq});
+  std::lock_guard<std::mutex> lk(g_mu);
+  Device &D = g_dev[b.device];
+  --g_out;
+  if (out_of_use) {
+    spare(ev);
+    D.stuck.push_back({p, nullptr, s, ++g_seq});
     return;
   }
   D.free[b.cls].push_back({p, ev, s, ++g_seq});
   D.cached += class_bytes(b.cls);
-  if (!D.limit) {
-    size_t total = 0;
-    if (hipDeviceTotalMem(&total, b.device) != hipSuccess) (void)hipGetLastError();
-    D.limit = std::max<uint64_t>(1ull << 30, total / 4);
-  }
-  if (D.cached > D.limit) trim(D, D.limit, false);
+  hold_bound(D, b.device, s);
 } catch (const std::bad_alloc &) {
   // no host memory for the bookkeeping: the block is lost to the process
 }
 
 int release_pools() try {
+  Relaxed relaxed;
   std::lock_guard<std::mutex> lk(g_mu);
-  if (g_out.load() != 0) return LPHT_ERR_INVALID;
+  if (g_out != 0) return LPHT_ERR_INVALID;
   int rc = LPHT_OK;
   for (int d = 0; d < kMaxDevices; ++d) {
     Device &D = g_dev[d];
-    bool any = D.graph_pool || !D.slabs.empty() || !D.stuck.empty();
-    for (const auto &kv : D.free) any = any || !kv.second.empty();
-    if (!any) continue;
+    if (!D.pool && !D.graph_pool) continue;
     OnDevice on(d);
     if (!on.ok || hipDeviceSynchronize() != hipSuccess) {
       rc = LPHT_ERR_DEVICE;
@@ -342,25 +399,26 @@ int release_pools() try {
     D.stuck.clear();
     for (auto &kv : D.free) all.insert(all.end(), kv.second.begin(), kv.second.end());
     D.free.clear();
+    auto release = [&](void *p, bool graph) {
+      if (hipFreeAsync(p, nullptr) == hipSuccess) return;
+      (void)hipGetLastError();
+      if (!graph) rc = LPHT_ERR_DEVICE;
+    };
     for (const Free &f : all) {
       const Block b = g_blocks[f.p];
-      if (b.cls == kGraphBlock) {
-        if (hipFreeAsync(f.p, nullptr) != hipSuccess) (void)hipGetLastError();
-      } else if (!b.slab && hipFree(f.p) != hipSuccess) {
-        rc = LPHT_ERR_DEVICE;
-      }
+      // (the slabs' parts go with their slabs)
+      if (b.cls == kGraphBlock || !b.slab) release(f.p, b.cls == kGraphBlock);
       g_blocks.erase(f.p);
       if (f.ev && hipEventDestroy(f.ev) != hipSuccess) (void)hipGetLastError();
     }
-    for (void *p : D.slabs)
-      if (hipFree(p) != hipSuccess) rc = LPHT_ERR_DEVICE;
+    for (void *p : D.slabs) release(p, false);
     D.slabs.clear();
     D.cached = 0;
-    if (D.graph_pool) {
-      if (hipDeviceSynchronize() != hipSuccess || hipMemPoolTrimTo(D.graph_pool, 0) != hipSuccess ||
-          hipMemPoolDestroy(D.graph_pool) != hipSuccess)
+    if (hipDeviceSynchronize() != hipSuccess) rc = LPHT_ERR_DEVICE;
+    for (hipMemPool_t *pool : {&D.pool, &D.graph_pool}) {
+      if (*pool && (hipMemPoolTrimTo(*pool, 0) != hipSuccess || hipMemPoolDestroy(*pool) != hipSuccess))
         rc = LPHT_ERR_DEVICE;
-      D.graph_pool = nullptr;
+      *pool = nullptr;
     }
   }
   for (hipEvent_t ev : g_events) (void)hipEventDestroy(ev);

@@ -694,6 +694,9 @@ bool persist_step(lpht_server *S, std::vector<Req *> &admitted) {
 
 void worker_loop(lpht_server *S) {
   (void)hipSetDevice(S->device);
+  // its queries of events must pass while some other thread captures a stream
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
   std::vector<Req *> admitted;
   const bool persistent = S->cfg.mode == LPHT_SERVE_PERSISTENT;
   while (true) {
