@@ -35,7 +35,8 @@
  * - The table's cells and its status block are owned by the library and
  *   allocated through the configured allocator (default: the library's own
  *   stream-ordered cache of blocks on the table's device, which keeps freed
- *   memory for reuse, up to a quarter of the device's).
+ *   memory for reuse, up to a quarter of the device's; a block that was still
+ *   in use when the cache passed that goes back at a later call).
  */
 #ifndef LPHT_H
 #define LPHT_H

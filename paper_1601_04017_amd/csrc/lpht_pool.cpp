@@ -19,10 +19,11 @@
 //     stream wait on that event (free of charge in stream order, and right
 //     even if the handle has come to name another stream since);
 //   - any other allocation takes it only once the event has completed.
-// What is cached is bounded by a quarter of the device's memory; beyond that,
-// and when an allocation fails, the blocks freed longest ago go back (the
-// runtime's pool keeps none of it past the next synchronisation).  Everything
-// goes back in release_pools.
+// What is cached is bounded by a quarter of the device's memory: beyond that the
+// blocks freed longest ago go back, each as soon as a call of the library finds
+// its last use completed (the runtime's pool keeps none of it past the next
+// synchronisation).  When an allocation fails, all that have completed go back.
+// Everything goes back in release_pools.
 //
 // While a stream is being captured no block of the cache is handed out, since
 // a replay would use it at any later time: allocations of a capturing stream
@@ -204,7 +205,10 @@ uint64_t give_back(Device &D, uint64_t keep, hipStream_t s, bool *busy = nullptr
       if (busy && e == hipErrorNotReady) *busy = true;
       continue;
     }
-    if (hipFreeAsync(at->p, s) != hipSuccess) (void)hipGetLastError();
+    if (hipFreeAsync(at->p, s) != hipSuccess) {
+      (void)hipGetLastError();  // the block stays where it is
+      continue;
+    }
     g_blocks.erase(at->p);
     spare(at->ev);
     D.cached -= class_bytes(r.cls);
@@ -326,6 +330,7 @@ void *pool_alloc(int device, size_t bytes, hipStream_t s, bool in_order) try {
     const uint32_t cls = class_of(bytes);
     p = take(D, cls, s, in_order);
     if (!p) p = fresh(device, cls, s, in_order, lk);
+    hold_bound(D, device, s);
   }
   if (p) ++g_out;
   return p;

@@ -198,6 +198,30 @@ int main() {
     show("capture_harmed", invalidated);
     finish(1);
   }
+  // a block that HIP does not take back stays in the books
+  {
+    void *a = pool_alloc(0, 20 * kGiB, handle(1));
+    refuse_free = true;
+    pool_free(a, handle(1));                        // above the bound
+    refuse_free = false;
+    void *b = pool_alloc(0, 20 * kGiB, handle(1));
+    show("kept_block_used_again", a == b);
+    pool_free(b, handle(1));
+  }
+  // the bound: a block still in use when it is freed goes back later
+  {
+    finish(1);
+    void *a = pool_alloc(0, 24 * kGiB, handle(1));
+    work(1);
+    const uint64_t waits = device_waits + event_waits;
+    pool_free(a, handle(1));
+    finish(1);
+    void *b = pool_alloc(0, 2 * kMiB, handle(2));
+    hipMemPoolTrimTo(nullptr, 0);                   // (the runtime's next synchronisation)
+    show("reserved_within_bound", reserved <= 17 * kGiB);
+    show("waits_over_bound", device_waits + event_waits - waits);
+    pool_free(b, handle(2));
+  }
   // no memory left: what has completed goes back, without a wait for the device
   // or for an event
   {

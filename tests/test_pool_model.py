@@ -1,6 +1,6 @@
 """The memory cache (csrc/lpht_pool.cpp) over a model of HIP on the CPU
-(tests/native/pool_model.cpp): another thread's stream capture, and allocations
-that find no memory."""
+(tests/native/pool_model.cpp): another thread's stream capture, a free that HIP
+refuses, the bound on what is cached, and allocations that find no memory."""
 import os
 import subprocess
 
@@ -23,6 +23,14 @@ def seen(tmp_path_factory):
 
 def test_capture_on_another_thread(seen):
     assert seen["capture_allocated"] and not seen["capture_harmed"]
+
+
+def test_refused_free_keeps_the_block(seen):
+    assert seen["kept_block_used_again"]
+
+
+def test_bound_is_held_without_waiting(seen):
+    assert seen["reserved_within_bound"] and seen["waits_over_bound"] == 0
 
 
 def test_room_is_made_without_waiting_for_the_device(seen):
