@@ -84,6 +84,17 @@ constexpr uint32_t kTileB = 4096;   // tile of stage B without skew
 // workgroup of stage B would run that much longer than the others, and the
 // passes that combine equal keys on the way are taken instead.
 constexpr uint32_t kSkewTimes = 4;
+// Within the rule above a bin may still hold keys with many copies, which stage
+// C would have to sort: a block of more than kEMax elements by one workgroup in
+// global memory, smaller ones by many steps (10^7 keys, each 2000 times: 18.6 ms
+// against 0.9 when stage B combines them first).  So stage B combines a bin in
+// which a block exceeds kEMax, or a key drawn from it has more than kRepeats
+// copies in the mean (the variance of its blocks' counts over their mean).
+// Where that line lies, 10^7 elements in 2^25 cells, insert-or-add, every key so
+// many times, combining in both stages / not at all, us: 4 times 1463 / 1077, 16
+// times 1552 / 1568, 100 times 1286 / 2691, 300 times 1054 / 7442.
+constexpr uint32_t kRepeats = 12;
+constexpr uint32_t kDeclined = ~0u;  // count of a bin's first block: the bin is left to k_bm_partition
 constexpr uint32_t kScanTile = 256 * kScanPer;
 
 template <int L>
@@ -551,7 +562,7 @@ __global__ void __launch_bounds__(256) k_bm_scatter(BmK k) {
 // ------------------------------------------------------------- stage B
 
 // Without skew: one workgroup of 1024 threads per first-level bin counts its
-// elements per block and moves them.
+// elements per block and moves them, or leaves the bin to k_bm_partition.
 template <int L>
 __global__ void __launch_bounds__(1024) k_bm_partition_plain(BmK k) {
   __shared__ uint32_t T[8][256];
@@ -560,11 +571,17 @@ __global__ void __launch_bounds__(1024) k_bm_partition_plain(BmK k) {
   __shared__ KT<L> buf[kTileB];
   __shared__ uint16_t obin[kTileB];
   __shared__ uint32_t sw[17];
+  __shared__ unsigned long long s_squares;
+  __shared__ uint32_t s_most;
   if (k.ctl->full || k.ctl->skewed) return;
   crc_tables_build(T);
   const uint32_t s = blockIdx.x;
   const uint32_t nl2 = 1u << k.l2_bits;
   const uint32_t mask2 = nl2 - 1;
+  if (threadIdx.x == 0) {
+    s_squares = 0;
+    s_most = 0;
+  }
   for (uint32_t i = threadIdx.x; i < nl2; i += blockDim.x) hist[i] = 0;
   __syncthreads();
   const u64 out0 = k.l1_off[s];
@@ -592,10 +609,24 @@ __global__ void __launch_bounds__(1024) k_bm_partition_plain(BmK k) {
   {
     const uint32_t per = (nl2 + blockDim.x - 1) / blockDim.x;  // <= 2
     const uint32_t i0 = std::min(nl2, threadIdx.x * per), i1 = std::min(nl2, i0 + per);
-    uint32_t sum = 0;
-    for (uint32_t i = i0; i < i1; ++i) sum += hist[i];
+    uint32_t sum = 0, most = 0;
+    u64 squares = 0;
+    for (uint32_t i = i0; i < i1; ++i) {
+      const uint32_t c = hist[i];
+      sum += c;
+      most = std::max(most, c);
+      squares += (u64)c * c;
+    }
+    squares = (u64)wave_sum((long long)squares);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&s_squares, (unsigned long long)squares);
+    if (most > kEMax) s_most = 1;
     uint32_t tot;
     uint32_t acc = block_excl_scan(sum, &tot, sw);
+    // (sums of squares in float: the counts of a bin may reach 2^32)
+    if (s_most || (float)s_squares * nl2 > (float)total * total + (float)kRepeats * total * nl2) {
+      if (threadIdx.x == 0) k.blk_cnt[(u64)s << k.l2_bits] = kDeclined;
+      return;
+    }
     for (uint32_t i = i0; i < i1; ++i) {
       const uint32_t c = hist[i];
       const u64 at = ((u64)s << k.l2_bits) + i;
@@ -682,16 +713,17 @@ __global__ void __launch_bounds__(1024) k_bm_partition_plain(BmK k) {
   }
 }
 
-// One workgroup of 1024 threads per first-level bin s.
+// One workgroup of 1024 threads per first-level bin s: of a skewed call, or one
+// that k_bm_partition_plain left.
 template <int L>
 __global__ void __launch_bounds__(1024) k_bm_partition(BmK k) {
   __shared__ uint32_t T[8][256];
   __shared__ uint32_t hist[kL2Max];
   __shared__ Combine<L> cb;
   __shared__ uint32_t sw[17];
-  if (k.ctl->full || !k.ctl->skewed) return;
-  crc_tables_build(T);
   const uint32_t s = blockIdx.x;
+  if (k.ctl->full || !(k.ctl->skewed || k.blk_cnt[(u64)s << k.l2_bits] == kDeclined)) return;
+  crc_tables_build(T);
   const uint32_t nl2 = 1u << k.l2_bits;
   const uint32_t mask2 = nl2 - 1;
   for (uint32_t i = threadIdx.x; i < nl2; i += blockDim.x) hist[i] = 0;
@@ -1571,6 +1603,7 @@ hipError_t launch_bulk_merge(const BulkMergeArgs &a, hipStream_t s) {
   hipLaunchKernelGGL(k_bm_scan_bins, dim3(1), dim3(1024), 0, s, k);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // of each pair the one that the bins' sizes ask for runs, the other returns
+  // (the partitions bin by bin)
   LPHT_BM(k_bm_scatter_plain, g.GA, kThreadsP);
   LPHT_BM(k_bm_scatter, g.GA, 256);
   LPHT_BM(k_bm_partition_plain, g.L1, 1024);

@@ -1,0 +1,74 @@
+"""GPU: sort-based builds of batches whose keys repeat, without any bin that is
+skewed as a whole: cell for cell against the oracle where a bin goes one way or
+the other, and in a time of the order of a batch of distinct keys."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1601_04017_amd import inputs
+from tests.gpu_util import cells_host, keys_dtype, make_table, to_dev
+
+pytestmark = pytest.mark.gpu
+
+LAYOUTS = [oracle.PACKED32, oracle.KV64]
+
+
+def _keys(layout, n, seed):
+    return (inputs.distinct_keys_u32 if layout == oracle.PACKED32 else inputs.distinct_keys_u64)(n, seed)
+
+
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("op", [oracle.ASSIGN, oracle.ADD])
+@pytest.mark.parametrize("copies", [10, 12, 14, 60, 1000, "mixed"])
+def test_repeated_keys(layout, op, copies):
+    dt = keys_dtype(layout)
+    rng = np.random.default_rng(7)
+    n = 400_000
+    if copies == "mixed":
+        # some keys a thousand times among distinct ones: bins of both kinds
+        k = _keys(layout, n, 3)
+        k[rng.random(n) < 0.05] = 0
+        hot = np.flatnonzero(k == 0)
+        k[hot] = _keys(layout, n + 20, 3)[n:][rng.integers(0, 20, hot.size)]
+    else:
+        k = _keys(layout, n // copies, 3)[rng.integers(0, n // copies, n)]
+    v = rng.integers(0, 1 << 20, n).astype(dt)
+    t, o = make_table(layout, 20), oracle.OracleTable(layout, 20)
+    t.build(to_dev(k), to_dev(v), op=op)
+    o.build(k, v, op)
+    assert np.array_equal(cells_host(t), o.cells())
+    # half of them again, into what is there
+    t.merge(to_dev(k[::2]), to_dev(v[::2]), op=op)
+    o.merge(k[::2], v[::2], op)
+    assert np.array_equal(cells_host(t), o.cells())
+    assert t.count() == o.counts()
+    t.close()
+
+
+def test_time_of_repeated_keys():
+    # a block of 1024 elements and more was sorted by one workgroup in global
+    # memory, 20 times the whole call's time
+    import torch
+    from paper_1601_04017_amd import lpht
+    n = 4_000_000
+    distinct = to_dev(inputs.distinct_keys_u64(n, 1))
+    pick = torch.randint(0, n // 2000, (n,), device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    one = distinct.clone()
+    one[torch.rand(n, device="cuda", generator=torch.Generator("cuda").manual_seed(2)) < 0.01] = 77
+    t = lpht.Table(log2_capacity=24)
+
+    def best(k):
+        ms = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            t.build(k, None, op=lpht.ADD)
+            b.record()
+            torch.cuda.synchronize()
+            ms.append(a.elapsed_time(b))
+        return min(ms)
+
+    base = best(distinct)
+    for k in (distinct[pick].contiguous(), one):
+        assert best(k) < 5 * base
+    t.close()
