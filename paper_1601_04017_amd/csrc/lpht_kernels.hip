@@ -1721,9 +1721,7 @@ hipError_t launch_migrate(const void *old_cells, uint32_t log2_old, void *new_ce
   }
   const bool lds_path = !old_is_full && g <= 1 && (mb == 256 || mb == 512 || mb == 1024) && cap >= mb &&
                         wpb >= 1;
-  uint32_t sgrid = grid_for(cap, LaunchCfg{256, 1, cfg.blocks_per_cu, cfg.num_cus, mb, 0, 0});
-  // as a fallback it nearly always only reads the flag: a small grid then
-  if (lds_path) sgrid = std::min(2 * cfg.num_cus, sgrid);
+  const uint32_t sgrid = grid_for(cap, LaunchCfg{256, 1, cfg.blocks_per_cu, cfg.num_cus, mb, 0, 0});
   if (lds_path) {
     const size_t lds = wpb * per_wave;
     const u64 nwaves = cap / mb;
@@ -1744,10 +1742,13 @@ hipError_t launch_migrate(const void *old_cells, uint32_t log2_old, void *new_ce
 #undef LPHT_MIG_LAUNCH
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // fallback, a no-op unless a wavefront reported overflow
+    // Fallback, a no-op unless a wavefront reported overflow.  Its grids are the
+    // full ones: from fill 2/3 on (a fill bound above 1/2) clusters longer than
+    // the halo are regular and this is the migration (KV64, 2^26 cells at fill
+    // 0.74: doubled in 5.7 ms, 12.5 with two workgroups per CU).
     const u64 n16 = new_bytes / 16;
-    hipLaunchKernelGGL(k_fill_zero_if, dim3(std::min(2 * cfg.num_cus, grid_for(n16, cfg))), dim3(cfg.block_threads),
-                       0, s, (u64x2 *)new_cells, n16, st);
+    hipLaunchKernelGGL(k_fill_zero_if, dim3(grid_for(n16, cfg)), dim3(cfg.block_threads), 0, s, (u64x2 *)new_cells,
+                       n16, st);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   } else {
