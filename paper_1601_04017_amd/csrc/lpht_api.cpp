@@ -324,8 +324,10 @@ int run_bulk(lpht_table *t, OpKind op, const void *keys, const void *vals, uint6
                  t->known_used + t->pending <= (1ull << t->log2c))
                     ? 1u
                     : 0u;
-  if (a.aggregate && t->tuning.aggregate == 1 && part_applies(n, t->log2c)) {
+  if (a.aggregate && t->tuning.aggregate == 1 && part_applies(n, t->log2c) && !capturing(s)) {
     // large insert-or-add on a large table: partition by table region first
+    // (under capture the scratch would stay with the graph until the pools are
+    // released, and be a node of it that nothing frees between replays)
     const size_t sb = part_scratch_bytes(n, t->log2c, t->cfg.layout, vals != nullptr, flags != nullptr,
                                          t->launch.num_cus);
     void *scratch = dev_alloc(t, sb, s);
