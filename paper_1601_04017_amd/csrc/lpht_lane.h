@@ -14,10 +14,6 @@ namespace lpht {
 // half full.
 hipError_t launch_lane(OpKind op, const BulkArgs &a, uint32_t threads, bool dense, hipStream_t s);
 
-// The same, decided on the device: nothing happens unless *only_if is set when
-// the launch runs.
-hipError_t launch_lane_if(OpKind op, const BulkArgs &a, const uint32_t *only_if, hipStream_t s);
-
 // Descriptors of a multi-table launch that fit its kernel arguments.
 constexpr uint32_t kLaneDescs = 28;
 

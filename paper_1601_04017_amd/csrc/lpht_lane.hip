@@ -87,9 +87,8 @@ constexpr uint32_t kMostThreads = 256;
 
 // One call on one table.
 template <int LAYOUT, int OP, int UP, int W>
-__global__ void __launch_bounds__(kMostThreads) k_lane(BulkArgs A, const uint32_t *only_if) {
+__global__ void __launch_bounds__(kMostThreads) k_lane(BulkArgs A) {
   __shared__ uint32_t s_hits[kMostThreads / 64];
-  if (only_if && *only_if == 0) return;
   uint32_t err = 0, hits = 0;
   const u64 stride = (u64)gridDim.x * blockDim.x;
   for (u64 base = (u64)blockIdx.x * blockDim.x; base < A.n; base += stride) {
@@ -194,11 +193,9 @@ void lane_launch(const BulkArgs &a, uint32_t threads, bool dense, hipStream_t s)
   threads = std::min(threads, kMostThreads);
   const u64 blocks = std::min<u64>((a.n + threads - 1) / threads, kMaxThreads / threads);
   if (dense)
-    hipLaunchKernelGGL((k_lane<LAYOUT, OP, UP, 4>), dim3((uint32_t)blocks), dim3(threads), 0, s, a,
-                       (const uint32_t *)nullptr);
+    hipLaunchKernelGGL((k_lane<LAYOUT, OP, UP, 4>), dim3((uint32_t)blocks), dim3(threads), 0, s, a);
   else
-    hipLaunchKernelGGL((k_lane<LAYOUT, OP, UP, 2>), dim3((uint32_t)blocks), dim3(threads), 0, s, a,
-                       (const uint32_t *)nullptr);
+    hipLaunchKernelGGL((k_lane<LAYOUT, OP, UP, 2>), dim3((uint32_t)blocks), dim3(threads), 0, s, a);
 }
 
 // The host does not know every table's fill here: W = 4, which costs small
@@ -236,27 +233,6 @@ hipError_t launch_lane(OpKind op, const BulkArgs &a, uint32_t threads, bool dens
 #define LPHT_CALL(OP, UP) \
   (a.layout == 0 ? lane_launch<0, OP, UP>(a, threads, dense, s) : lane_launch<1, OP, UP>(a, threads, dense, s))
   LPHT_LANE_OPS(LPHT_CALL, op, a.up)
-#undef LPHT_CALL
-  return hipGetLastError();
-}
-
-hipError_t launch_lane_if(OpKind op, const BulkArgs &a, const uint32_t *only_if, hipStream_t s) {
-  drop_stale_error();
-  // a small grid: nearly always it only reads the flag
-  const uint32_t blocks = (uint32_t)std::min<u64>((a.n + kMostThreads - 1) / kMostThreads, 4096);
-#define LPHT_CALL(OP, UP)                                                                                       \
-  if (a.layout == 0)                                                                                            \
-    hipLaunchKernelGGL((k_lane<0, OP, UP, 4>), dim3(blocks), dim3(kMostThreads), 0, s, a, only_if);             \
-  else                                                                                                          \
-    hipLaunchKernelGGL((k_lane<1, OP, UP, 4>), dim3(blocks), dim3(kMostThreads), 0, s, a, only_if)
-  switch (op) {
-    case OP_INSERT: LPHT_CALL(OP_INSERT, 0); break;
-    case OP_UPSERT:
-      if (a.up) return hipErrorInvalidValue;
-      LPHT_CALL(OP_UPSERT, 0);
-      break;
-    default: return hipErrorInvalidValue;
-  }
 #undef LPHT_CALL
   return hipGetLastError();
 }
