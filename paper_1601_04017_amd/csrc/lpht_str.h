@@ -50,9 +50,8 @@ struct StrMigArgs {
 hipError_t launch_str_init(StrCtl *ctl, hipStream_t s);
 // Finds and erases.
 hipError_t launch_str_op(int kind, const StrArgs &a, uint32_t num_cus, hipStream_t s);
-// Inserting operations, in slices of `slice` (at most kStrSlice): a slice's
-// equal absent keys all write their records, so this bounds what a skewed call
-// leaves in the pool.  `scratch`: 16 bytes for each of `slice` operations.
+// Inserting operations, in slices of `slice` (at most kStrSlice).  `scratch`:
+// 16 bytes for each of `slice` operations.
 constexpr uint64_t kStrSlice = 1ull << 20;
 hipError_t launch_str_insert(int kind, const StrArgs &a, uint64_t slice, void *scratch, uint32_t num_cus, hipStream_t s);
 hipError_t launch_str_migrate(const StrMigArgs &a, uint32_t num_cus, hipStream_t s);

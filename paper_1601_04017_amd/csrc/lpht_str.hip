@@ -11,14 +11,14 @@
 //
 // A pool record is a 32-bit length followed by the bytes, rounded up to 8
 // bytes.  Records are allocated by bumping a device cursor.  An inserting call
-// takes two launches: the first looks every key up and writes the records of
-// the absent ones, the second publishes their references with
-// compare-and-swap.  The boundary between them makes the records visible, so
-// no operation fences (an agent-scope release writes back the XCD's L2).
-// Records of erased keys, and of insertions that lost to an equal key of the
-// same call, stay in the pool until the next migration, which copies only live
-// keys into a new pool (the paper reclaims key space when the array is
-// migrated).
+// takes two launches.  The first inserts every absent key by compare-and-swap as
+// a claim, a reference to the operation, whose key is read from the call's own
+// bytes: equal keys of the call meet it there.  Each claim gets a record, whose
+// reference the second puts in the claim's place.  So no operation fences to make
+// a record visible (an agent-scope release writes back the XCD's L2), and the
+// pool takes one record per inserted key.  Records of erased keys stay in the
+// pool until the next migration, which copies only live keys into a new pool (the
+// paper reclaims key space when the array is migrated).
 //
 // The hash is the pair of CRC-32C register updates over the key's bytes with
 // the two seeds (Sec. 8.3), the same function as for word keys.
@@ -70,17 +70,6 @@ __device__ __forceinline__ u64 str_hash(const uint32_t (*T)[256], const uint8_t 
 
 __device__ __forceinline__ u64 rec_bytes(u64 len) { return (4 + len + 7) & ~7ull; }
 
-__device__ __forceinline__ bool rec_equal(const uint8_t *pool, u64 off, const uint8_t *s, u64 len) {
-  if (*(const uint32_t *)(pool + off) != (uint32_t)len) return false;
-  const uint8_t *r = pool + off + 4;
-  u64 i = 0;
-  for (; i + 8 <= len; i += 8)
-    if (ld8(r + i) != ld8(s + i)) return false;
-  for (; i < len; ++i)
-    if (r[i] != s[i]) return false;
-  return true;
-}
-
 // Writes the record of s[0..len) at pool offset off (8-aligned).
 __device__ __forceinline__ void rec_write(uint8_t *pool, u64 off, const uint8_t *s, u64 len) {
   *(uint32_t *)(pool + off) = (uint32_t)len;
@@ -91,15 +80,34 @@ __device__ __forceinline__ void rec_write(uint8_t *pool, u64 off, const uint8_t 
 }
 
 // A cell: reference and value.  Plain loads: within a launch a cell only goes
-// from empty to a reference (insertions) or from a reference to the tombstone
+// from empty to a claim (insertions) or from a reference to the tombstone
 // (erases), each by compare-and-swap, and a probe that read the cell before
 // learns so from its own compare-and-swap.
 __device__ __forceinline__ u64x2 ld_cell(const void *cells, u64 p) { return ((const u64x2 *)cells)[p]; }
 
+// Marks a claim among the references: the low 47 bits are the operation's index.
+constexpr u64 kClaim = 1ull << 47;
+
+__device__ __forceinline__ bool bytes_equal(const uint8_t *a, const uint8_t *b, u64 len) {
+  u64 i = 0;
+  for (; i + 8 <= len; i += 8)
+    if (ld8(a + i) != ld8(b + i)) return false;
+  for (; i < len; ++i)
+    if (a[i] != b[i]) return false;
+  return true;
+}
+
 // Whether the cell's reference word r names the key s[0..len).  Every record
 // that a reference names was written by an earlier launch.
-__device__ __forceinline__ bool same_key(const uint8_t *pool, u64 r, u64 sig, const uint8_t *s, u64 len) {
-  return r != kTomb && (r >> 48) == sig && rec_equal(pool, r & kOffMask, s, len);
+template <bool CLAIMS>
+__device__ __forceinline__ bool same_key(const StrArgs &a, u64 r, u64 sig, const uint8_t *s, u64 len) {
+  if (r == kTomb || (r >> 48) != sig) return false;
+  if (CLAIMS && (r & kClaim)) {
+    const u64 i = r & (kClaim - 1), o = a.offsets[i];
+    return a.offsets[i + 1] - o == len && bytes_equal(a.bytes + o, s, len);
+  }
+  const uint8_t *rec = a.pool + (r & kOffMask);
+  return *(const uint32_t *)rec == (uint32_t)len && bytes_equal(rec + 4, s, len);
 }
 
 // Exclusive prefix sum of v over the wavefront's 64 lanes (all active);
@@ -115,24 +123,20 @@ __device__ __forceinline__ u64 wave_excl_scan(u64 v, u64 &total) {
   return x - v;
 }
 
-// Looks a key up: the cell that holds it (found) or the empty cell its probe
-// ended at; neither: every cell holds another key.
+// Looks a key up: the cell that holds it, if any.
 struct StrProbe {
-  u64 p, r, v, sig;  // r, v: the cell's words
-  bool found, at_empty;
+  u64 p, r, v;  // r, v: the cell's words
+  bool found;
 };
 __device__ __forceinline__ StrProbe str_probe(const StrArgs &a, const uint32_t (*T)[256], const uint8_t *s, u64 len) {
-  const u64 mask = (1ull << a.log2c) - 1, h = str_hash(T, s, len, a.crc_hi, a.crc_lo);
-  StrProbe q{h >> (64 - a.log2c), kEmpty, 0, h & 0xFFFFull, false, false};
+  const u64 mask = (1ull << a.log2c) - 1, h = str_hash(T, s, len, a.crc_hi, a.crc_lo), sig = h & 0xFFFFull;
+  StrProbe q{h >> (64 - a.log2c), kEmpty, 0, false};
   for (u64 step = 0; step <= mask; ++step, q.p = (q.p + 1) & mask) {
     const u64x2 c = ld_cell(a.cells, q.p);
     q.r = c.x;
     q.v = c.y;
-    if (q.r == kEmpty) {
-      q.at_empty = true;
-      break;
-    }
-    if (same_key(a.pool, q.r, q.sig, s, len)) {
+    if (q.r == kEmpty) break;
+    if (same_key<false>(a, q.r, sig, s, len)) {
       q.found = true;
       break;
     }
@@ -177,45 +181,64 @@ __global__ void __launch_bounds__(256) k_str_op(StrArgs a) {
 }
 
 // What the first launch of an inserting call leaves for the second: the
-// reference of the operation's record (0: the operation is done) and the empty
-// cell its probe ended at.
+// reference of the record (0: nothing was claimed) and the cell claimed for it.
 typedef u64x2 Staged;
 
-// First launch, one lane per operation: present keys are done here, absent
-// ones get a record.  One addition to the pool's cursor per workgroup (of 1024:
-// every addition is 12 ns on the one line, 2 * 10^6 operations by wavefronts
-// would be 375 us).
+// First launch, one lane per operation: absent keys are claimed and their
+// records written, present ones updated.  One addition to the pool's cursor per
+// workgroup (of 1024: every addition is 12 ns on the one line, 2 * 10^6 operations
+// by wavefronts would be 375 us).
 //
-// Bound: random lines (cell, and record for hits) and the latency of each key's
-// chain of loads, which one operation per lane and full occupancy hide: eight
-// operations per lane, one after the other, with one fence per wavefront took
-// 502 us for 2 * 10^6 keys of 8 to 40 bytes in 2^23 cells, the two launches
-// 296 us.
+// Bound: random lines (cell, and record or key for hits) and the latency of each
+// key's chain of loads, which one operation per lane and full occupancy hide:
+// eight operations per lane, one after the other, with one fence per wavefront
+// took 502 us for 2 * 10^6 keys of 8 to 40 bytes in 2^23 cells, the two launches
+// 307 us.
 template <int KIND>
-__global__ void __launch_bounds__(1024, 8) k_str_stage(StrArgs a, Staged *staged) {
+__global__ void __launch_bounds__(1024, 8) k_str_claim(StrArgs a, Staged *staged) {
   __shared__ uint32_t T[8][256];
   __shared__ u64 s_w[16];
   crc_tables_build(T);
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const u64 mask = (1ull << a.log2c) - 1;
+  u64 *cells = (u64 *)a.cells;
   const u64 stride = (u64)gridDim.x * blockDim.x;
   uint32_t err = 0;
   // the bound is uniform over the workgroup, which allocates together
   for (u64 i0 = (u64)blockIdx.x * blockDim.x; i0 < a.n; i0 += stride) {
     const u64 i = i0 + threadIdx.x;
     const uint8_t *s = nullptr;
-    u64 len = 0, need = 0;
-    StrProbe q{};
+    u64 len = 0, need = 0, p = 0, sig = 0;
     uint8_t flag = 0xFF;
     if (i < a.n) {
       const u64 o0 = a.offsets[i];
       len = a.offsets[i + 1] - o0;
       s = a.bytes + o0;
-      q = str_probe(a, T, s, len);
-      if (q.found) {
-        str_update<KIND>(a, q.p, a.vals ? a.vals[i] : 1);
-        flag = 0;
+      const u64 h = str_hash(T, s, len, a.crc_hi, a.crc_lo);
+      sig = h & 0xFFFFull;
+      p = h >> (64 - a.log2c);
+      for (u64 step = 0; step <= mask; ++step, p = (p + 1) & mask) {
+        u64 r = ld_cell(a.cells, p).x;
+        if (r == kEmpty) {
+          r = cas64(cells + 2 * p, kEmpty, (sig << 48) | kClaim | i);
+          if (r == kEmpty) {
+            // the value, 0 until now; concurrent insert-or-adds of the key also add
+            const u64 d = a.vals ? a.vals[i] : 1;
+            if (KIND == kStrInsert || a.up == 0)
+              __hip_atomic_store(cells + 2 * p + 1, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else
+              add64(cells + 2 * p + 1, d);
+            need = rec_bytes(len);
+            flag = 1;
+            break;
+          }
+        }
+        if (same_key<true>(a, r, sig, s, len)) {
+          str_update<KIND>(a, p, a.vals ? a.vals[i] : 1);
+          flag = 0;
+          break;
+        }
       }
-      need = q.at_empty ? rec_bytes(len) : 0;
     }
     u64 total;
     u64 off = wave_excl_scan(need, total);
@@ -235,52 +258,27 @@ __global__ void __launch_bounds__(1024, 8) k_str_stage(StrArgs a, Staged *staged
     off += s_w[wave];
     __syncthreads();  // read before the next round writes it
     if (i >= a.n) continue;
-    Staged out = {0, q.p};
+    Staged out = {0, p};
     if (need && off + need <= a.pool_cap) {
       rec_write(a.pool, off, s, len);
-      out.x = (q.sig << 48) | off;
-    } else if (flag == 0xFF) {
-      err |= kErrFull;  // no cell, or no room in the pool
+      out.x = (sig << 48) | off;
+    } else if (need) {
+      out.x = kTomb;  // no room in the pool: the claim becomes a tombstone
+      flag = 0xFF;
     }
+    if (flag == 0xFF) err |= kErrFull;  // no cell, or no room in the pool
     staged[i] = out;
-    if (!out.x && a.flags) a.flags[i] = flag;
+    if (a.flags) a.flags[i] = flag;
   }
   if (err) atomicOr(&a.ctl->err, err);
 }
 
-// Second launch: the records' references are published from the empty cell
-// on; an equal key of the call that was faster is met on the way.
-template <int KIND>
+// Second launch: the records' references in the claims' place.
 __global__ void __launch_bounds__(256) k_str_publish(StrArgs a, const Staged *staged) {
   const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   const Staged st = staged[i];
-  if (!st.x) return;
-  const u64 mask = (1ull << a.log2c) - 1, sig = st.x >> 48, off = st.x & kOffMask;
-  const u64 d = a.vals ? a.vals[i] : 1;
-  u64 *cells = (u64 *)a.cells;
-  uint8_t flag = 0xFF;
-  u64 p = st.y, r = kEmpty;
-  for (u64 step = 0; step <= mask; ++step, p = (p + 1) & mask, r = cells[2 * p]) {
-    if (r == kEmpty) {
-      r = cas64(cells + 2 * p, kEmpty, st.x);
-      if (r == kEmpty) {
-        if (KIND == kStrInsert || a.up == 0)
-          __hip_atomic_store(cells + 2 * p + 1, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else
-          add64(cells + 2 * p + 1, d);
-        flag = 1;
-        break;
-      }
-    }
-    if (same_key(a.pool, r, sig, a.pool + off + 4, *(const uint32_t *)(a.pool + off))) {
-      str_update<KIND>(a, p, d);
-      flag = 0;
-      break;
-    }
-  }
-  if (flag == 0xFF) atomicOr(&a.ctl->err, kErrFull);
-  if (a.flags) a.flags[i] = flag;
+  if (st.x) ((u64 *)a.cells)[2 * st.y] = st.x;
 }
 
 // Migration: every live key of the old table is copied into the new pool
@@ -382,15 +380,13 @@ hipError_t launch_str_insert(int kind, const StrArgs &all, uint64_t slice, void 
     a.vals = all.vals ? all.vals + lo : nullptr;
     a.flags = all.flags ? all.flags + lo : nullptr;
     const u64 want = (a.n + 1023) / 1024, most = 2ull * (num_cus ? num_cus : 1);
-    const uint32_t gs = (uint32_t)(want < most ? want : most), gp = (uint32_t)((a.n + 255) / 256);
+    const uint32_t grid = (uint32_t)(want < most ? want : most);
     Staged *st = (Staged *)scratch;
-    if (kind == kStrInsert) {
-      hipLaunchKernelGGL(k_str_stage<kStrInsert>, dim3(gs), dim3(1024), 0, s, a, st);
-      hipLaunchKernelGGL(k_str_publish<kStrInsert>, dim3(gp), dim3(256), 0, s, a, (const Staged *)st);
-    } else {
-      hipLaunchKernelGGL(k_str_stage<kStrUpsert>, dim3(gs), dim3(1024), 0, s, a, st);
-      hipLaunchKernelGGL(k_str_publish<kStrUpsert>, dim3(gp), dim3(256), 0, s, a, (const Staged *)st);
-    }
+    if (kind == kStrInsert)
+      hipLaunchKernelGGL(k_str_claim<kStrInsert>, dim3(grid), dim3(1024), 0, s, a, st);
+    else
+      hipLaunchKernelGGL(k_str_claim<kStrUpsert>, dim3(grid), dim3(1024), 0, s, a, st);
+    hipLaunchKernelGGL(k_str_publish, dim3((uint32_t)((a.n + 255) / 256)), dim3(256), 0, s, a, (const Staged *)st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
