@@ -43,8 +43,9 @@ size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // True when the first and the last byte of [p, p + bytes) lie in pinned host
 // memory or in device memory (memory a kernel can address); `at_p`: and the
-// device's address of it is p.
-bool gpu_accessible(const void *p, size_t bytes, bool at_p = false) {
+// address of it on device `at_p` is p, which memory of another device need not
+// be within a kernel's reach of.
+bool gpu_accessible(const void *p, size_t bytes, int at_p = -1) {
   for (const void *x : {p, (const void *)((const char *)p + bytes - 1)}) {
     hipPointerAttribute_t at{};
     if (hipPointerGetAttributes(&at, x) != hipSuccess) {
@@ -52,15 +53,16 @@ bool gpu_accessible(const void *p, size_t bytes, bool at_p = false) {
       return false;
     }
     if (at.type != hipMemoryTypeHost && at.type != hipMemoryTypeDevice) return false;
-    if (at_p && at.devicePointer != x) return false;
+    if (at_p >= 0 && (at.devicePointer != x || (at.type == hipMemoryTypeDevice && at.device != at_p))) return false;
   }
   return true;
 }
 
 // One array of a request, in or out: by the group's copy kernel where the
-// device can address it, else by a copy of its own.
-void stage(std::vector<ServeSeg> &segs, void *dst, const void *src, uint64_t bytes, bool in, hipStream_t s) {
-  if (gpu_accessible(in ? src : dst, bytes, true))
+// server's device can address it, else by a copy of its own.
+void stage(std::vector<ServeSeg> &segs, void *dst, const void *src, uint64_t bytes, bool in, int device,
+           hipStream_t s) {
+  if (gpu_accessible(in ? src : dst, bytes, device))
     segs.push_back({dst, src, bytes, in ? 1u : 0u, 0});
   else
     (void)hipMemcpyAsync(dst, src, bytes, in ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost, s);
@@ -260,8 +262,8 @@ void launch_group(lpht_server *S, std::vector<Req *> &group) {
     lpht_table *t = S->tables[q->r.table];
     g.tables.push_back(q->r.table);
     g.reqs.push_back(q);
-    stage(segs, dkeys, q->r.keys, n * S->kb, true, s);
-    stage(segs, dkinds, q->r.kinds, n, true, s);
+    stage(segs, dkeys, q->r.keys, n * S->kb, true, S->device, s);
+    stage(segs, dkinds, q->r.kinds, n, true, S->device, s);
     const uint32_t kind_op[3] = {LPHT_OP_FIND, LPHT_OP_UPSERT, LPHT_OP_ERASE};
     for (uint32_t k = 0; k < 3; ++k) {
       if (q->count[k] == 0) continue;
@@ -301,8 +303,8 @@ void launch_group(lpht_server *S, std::vector<Req *> &group) {
   for (Req *q : group) {
     const size_t n = q->r.n;
     unsigned char *base = S->arena + q->arena_off;
-    if (q->r.vals_out && q->count[0]) stage(segs, q->r.vals_out, base + round256(n * S->kb), n * S->kb, false, s);
-    if (q->r.flags) stage(segs, q->r.flags, base + 2 * round256(n * S->kb) + round256(n), n, false, s);
+    if (q->r.vals_out && q->count[0]) stage(segs, q->r.vals_out, base + round256(n * S->kb), n * S->kb, false, S->device, s);
+    if (q->r.flags) stage(segs, q->r.flags, base + 2 * round256(n * S->kb) + round256(n), n, false, S->device, s);
   }
   if (launch_serve_copy(segs, counts, s) != hipSuccess)
     for (Req *q : group) q->c.status = LPHT_ERR_DEVICE;
