@@ -59,13 +59,14 @@ bool gpu_accessible(const void *p, size_t bytes, int at_p = -1) {
 }
 
 // One array of a request, in or out: by the group's copy kernel where the
-// server's device can address it, else by a copy of its own.
-void stage(std::vector<ServeSeg> &segs, void *dst, const void *src, uint64_t bytes, bool in, int device,
+// server's device can address it, else by a copy of its own.  False: that failed.
+bool stage(std::vector<ServeSeg> &segs, void *dst, const void *src, uint64_t bytes, bool in, int device,
            hipStream_t s) {
-  if (gpu_accessible(in ? src : dst, bytes, device))
+  if (gpu_accessible(in ? src : dst, bytes, device)) {
     segs.push_back({dst, src, bytes, in ? 1u : 0u, 0});
-  else
-    (void)hipMemcpyAsync(dst, src, bytes, in ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost, s);
+    return true;
+  }
+  return hipMemcpyAsync(dst, src, bytes, in ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost, s) == hipSuccess;
 }
 
 struct Req {
@@ -88,6 +89,7 @@ struct Group {
   std::vector<uint32_t> tables;
   hipEvent_t ev;
   uint32_t stream;
+  bool counted;  // its kernel that writes the tables' counts was launched
 };
 
 }  // namespace
@@ -249,6 +251,7 @@ void launch_group(lpht_server *S, std::vector<Req *> &group) {
   ops.reserve(3 * group.size());
   std::vector<ServeSeg> segs;
   segs.reserve(2 * group.size());
+  bool staged = true;
   const double t_admit = now_us();
   for (Req *q : group) {
     q->c.admit_us = t_admit;
@@ -262,8 +265,8 @@ void launch_group(lpht_server *S, std::vector<Req *> &group) {
     lpht_table *t = S->tables[q->r.table];
     g.tables.push_back(q->r.table);
     g.reqs.push_back(q);
-    stage(segs, dkeys, q->r.keys, n * S->kb, true, S->device, s);
-    stage(segs, dkinds, q->r.kinds, n, true, S->device, s);
+    staged &= stage(segs, dkeys, q->r.keys, n * S->kb, true, S->device, s);
+    staged &= stage(segs, dkinds, q->r.kinds, n, true, S->device, s);
     const uint32_t kind_op[3] = {LPHT_OP_FIND, LPHT_OP_UPSERT, LPHT_OP_ERASE};
     for (uint32_t k = 0; k < 3; ++k) {
       if (q->count[k] == 0) continue;
@@ -282,8 +285,13 @@ void launch_group(lpht_server *S, std::vector<Req *> &group) {
       ops.push_back(o);
     }
   }
-  if (launch_serve_copy(segs, {}, s) != hipSuccess)
+  staged &= launch_serve_copy(segs, {}, s) == hipSuccess;
+  if (!staged) {
+    // what the staging holds is not what was sent: no operation of the group runs
+    (void)hipGetLastError();
     for (Req *q : group) q->c.status = LPHT_ERR_DEVICE;
+    ops.clear();
+  }
   std::vector<uint64_t> before(group.size());
   for (size_t i = 0; i < group.size(); ++i) before[i] = table_bytes_of(S->tables[group[i]->r.table]);
   if (!ops.empty()) {
@@ -300,14 +308,22 @@ void launch_group(lpht_server *S, std::vector<Req *> &group) {
   for (uint32_t ti : g.tables) counts.push_back({S->tables[ti]->status, S->totals + si * area + 4 * ti});
   g.stream = si;
   segs.clear();
+  bool returned = true;
   for (Req *q : group) {
+    if (!staged) break;
     const size_t n = q->r.n;
     unsigned char *base = S->arena + q->arena_off;
-    if (q->r.vals_out && q->count[0]) stage(segs, q->r.vals_out, base + round256(n * S->kb), n * S->kb, false, S->device, s);
-    if (q->r.flags) stage(segs, q->r.flags, base + 2 * round256(n * S->kb) + round256(n), n, false, S->device, s);
+    if (q->r.vals_out && q->count[0])
+      returned &= stage(segs, q->r.vals_out, base + round256(n * S->kb), n * S->kb, false, S->device, s);
+    if (q->r.flags)
+      returned &= stage(segs, q->r.flags, base + 2 * round256(n * S->kb) + round256(n), n, false, S->device, s);
   }
-  if (launch_serve_copy(segs, counts, s) != hipSuccess)
-    for (Req *q : group) q->c.status = LPHT_ERR_DEVICE;
+  g.counted = launch_serve_copy(segs, counts, s) == hipSuccess;
+  if (!returned || !g.counted) {
+    (void)hipGetLastError();
+    for (Req *q : group)
+      if (q->c.status == LPHT_OK) q->c.status = LPHT_ERR_DEVICE;
+  }
   (void)hipEventRecord(g.ev, s);
   if (S->inflight.empty()) S->busy_since = now_us();
   S->inflight_reqs += (uint32_t)group.size();
@@ -321,11 +337,12 @@ void retire_group(lpht_server *S, Group &g) {
   for (uint32_t ti : g.tables) {
     lpht_table *T = S->tables[ti];
     const uint64_t *tot = S->totals + g.stream * 4 * S->tables.size() + 4 * ti;
+    S->busy[ti] = 0;
+    if (!g.counted) continue;  // the bounds stand
     T->known_used = tot[0];
     T->known_live = tot[1];
     T->pending = 0;
     T->mods_since_exact = 0;
-    S->busy[ti] = 0;
   }
   for (Req *q : g.reqs) {
     if (q->r.vals_out && q->count[0] == 0) std::memset(q->r.vals_out, 0, q->r.n * S->kb);

@@ -147,8 +147,12 @@ int main() {
   serve("other_device");
   array_device = 0;
   array_type = hipMemoryTypeHost;
+  fail_kernel = 1;
+  serve("copy_in_refused");
   serve("after_it");
   array_type = hipMemoryTypeUnregistered;
   serve("pageable");
+  fail_copy = 1;
+  serve("pageable_refused");
   lpht_server_destroy(S);
 }

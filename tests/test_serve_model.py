@@ -1,6 +1,6 @@
 """The serving loop's copies (csrc/lpht_server.cpp) over a model of HIP and of
 the tables on the CPU (tests/native/serve_model.cpp): which arrays the copy
-kernel takes."""
+kernel takes, and that no operation runs when the arrays did not arrive."""
 import os
 import subprocess
 
@@ -8,7 +8,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1601_04017_amd", "csrc")
-OK = 0
+OK, ERR_DEVICE = 0, -5
 
 
 @pytest.fixture(scope="module")
@@ -27,3 +27,8 @@ def seen(tmp_path_factory):
 def test_arrays_arrive(seen, name, kernel_arrays, copies):
     assert seen[name + ".status"] == OK and seen[name + ".batches"] == 1
     assert (seen[name + ".kernel_arrays"], seen[name + ".copies"]) == (kernel_arrays, copies)
+
+
+@pytest.mark.parametrize("name", ["copy_in_refused", "pageable_refused"])
+def test_nothing_runs_on_arrays_that_did_not_arrive(seen, name):
+    assert seen[name + ".status"] == ERR_DEVICE and seen[name + ".batches"] == 0
