@@ -353,7 +353,8 @@ int lpht_get_tuning(const lpht_table *t, lpht_tuning *tuning);
  *     narrowest width within 3 % of its fastest, and a quarter keeps the
  *     fill-3/8 choice unless another width is more than 3 % faster;
  *     group_width = the fill-3/8 finds' choice;
- *   - block_threads over {256, 512, 1024} at fill 3/8 with those widths;
+ *   - block_threads over {256, 512, 1024} at fill 3/8 with those widths (256
+ *     where both are 1, whose launches take at most that many);
  *   - migrate_block over {256, 512, 1024, 2048}: doubling a table at fill 7/16
  *     (lpht_grow);
  *   - blocks_per_cu 8 and aggregate 1 as the defaults.

@@ -164,9 +164,15 @@ extern "C" int lpht_autotune(uint32_t layout, uint32_t log2c, uint32_t reps, voi
   choose(rep.insert_ms, best.g_modify);
   best.group_width = best.g_find[1];
 
-  // workgroup size at fill 3/8 with the chosen widths
+  // workgroup size at fill 3/8 with the chosen widths; width 1 takes at most
+  // kBlocks[0] threads of it, so its launches are all the same
+  const bool same = best.g_find[1] == 1 && best.g_modify[1] == 1;
   uint32_t bb = 0;
   for (int bi = 0; bi < 3; ++bi) {
+    if (same && bi > 0) {
+      rep.block_ms[bi] = rep.block_ms[0];
+      continue;
+    }
     lpht_tuning u = best;
     u.block_threads = kBlocks[bi];
     double ins, fnd;
