@@ -90,10 +90,15 @@ constexpr uint32_t kSkewTimes = 4;
 // against 0.9 when stage B combines them first).  So stage B combines a bin in
 // which a block exceeds kEMax, or a key drawn from it has more than kRepeats
 // copies in the mean (the variance of its blocks' counts over their mean).
-// Where that line lies, 10^7 elements in 2^25 cells, insert-or-add, every key so
-// many times, combining in both stages / not at all, us: 4 times 1463 / 1077, 16
-// times 1552 / 1568, 100 times 1286 / 2691, 300 times 1054 / 7442.
-constexpr uint32_t kRepeats = 12;
+// Where that line lies, insert-or-add, every key so many times, combining in both
+// stages / not at all, us: 10^7 elements in 2^25 cells, 4 times 1463 / 1077, 16
+// times 1552 / 1568, 100 times 1286 / 2691, 300 times 1054 / 7442; 4 * 10^6 in
+// 2^23 cells, 8 times 577 / 685 (a cell is crowded sooner there).
+// A bin of few elements is combined as soon as a block exceeds what a wavefront
+// sorts: a workgroup's sort takes its 40 us whatever the batch, a chunk of stage
+// B seven (10^6 Zipf(0.9) keys in 2^21 cells 394 -> 329 us).
+constexpr uint32_t kRepeats = 6;
+constexpr uint32_t kFewElements = 8192;
 constexpr uint32_t kDeclined = ~0u;  // count of a bin's first block: the bin is left to k_bm_partition
 constexpr uint32_t kScanTile = 256 * kScanPer;
 
@@ -619,7 +624,7 @@ __global__ void __launch_bounds__(1024) k_bm_partition_plain(BmK k) {
     }
     squares = (u64)wave_sum((long long)squares);
     if ((threadIdx.x & 63) == 0) atomicAdd(&s_squares, (unsigned long long)squares);
-    if (most > kEMax) s_most = 1;
+    if (most > (total <= kFewElements ? kEW : kEMax)) s_most = 1;
     uint32_t tot;
     uint32_t acc = block_excl_scan(sum, &tot, sw);
     // (sums of squares in float: the counts of a bin may reach 2^32)
