@@ -143,7 +143,8 @@ typedef struct lpht_tuning {
                            * occurrence of a key is combined and each distinct key costs one
                            * upsert (scratch: about twice (key width [+ value width] [+ 4 with
                            * flags]) bytes per operation and 32 MiB at most beside, from the
-                           * table's allocator; without it 2 is done); 2: LDS combining
+                           * table's allocator; without it, and under stream capture, 2 is
+                           * done); 2: LDS combining
                            * of 2048-operation chunks only; 0: no combining */
   /* Group width by fill quarter, used / capacity in [0, 1/4], (1/4, 1/2],
    * (1/2, 3/4], (3/4, 1] (the host's bound on `used` after the operations):
@@ -197,8 +198,9 @@ int lpht_destroy(lpht_table *t, void *stream);
  * that used + n <= alpha * c (bulk pre-growth, Sec. 5.5).  Calls of 2^20
  * operations and more on a nearly empty table are partitioned by table region
  * first (scratch: about twice (key width + value width [+ 4 with flags]) bytes
- * per operation from the table's allocator; without it the operations go to
- * the table one by one). */
+ * per operation from the table's allocator); without it, under stream capture,
+ * and where a sample of the batch shows that keys repeat, the operations go to
+ * the table one by one. */
 int lpht_insert(lpht_table *t, const void *keys, const void *vals, uint64_t n, uint8_t *flags,
                 void *stream);
 

@@ -326,7 +326,7 @@ __device__ bool migrate(const AsyncArgs &a, const uint32_t (*T)[256], uint32_t e
 // ends its run.  All wavefronts' updates of one key go through one line, which
 // takes 83 M a second, and a small table's chunks of 64 operations would send
 // it one each.  10^7 Zipf(1.0) insert-or-adds from 4096 cells: 5.9 ms without
-// list and kept keys, 5.5 with the list, 2.3 with both.
+// list and kept keys, 5.5 with the list, 2.3 with both (the kernel, then).
 // (Slots freed before a kept key's can let it be claimed a second time; both
 // are applied, one of them inserts.)
 constexpr uint32_t kChunkSlots = 512;

@@ -19,11 +19,11 @@ def _keys(layout, n, seed):
 
 @pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("op", [oracle.ASSIGN, oracle.ADD])
-@pytest.mark.parametrize("copies", [10, 12, 14, 60, 1000, "mixed"])
-def test_repeated_keys(layout, op, copies):
+@pytest.mark.parametrize("copies", [3, 5, 7, 12, 60, 1000, "mixed"])
+@pytest.mark.parametrize("n,log2c", [(400_000, 20), (2_400_000, 23)])  # bins of few and of more elements
+def test_repeated_keys(layout, op, copies, n, log2c):
     dt = keys_dtype(layout)
     rng = np.random.default_rng(7)
-    n = 400_000
     if copies == "mixed":
         # some keys a thousand times among distinct ones: bins of both kinds
         k = _keys(layout, n, 3)
@@ -33,7 +33,7 @@ def test_repeated_keys(layout, op, copies):
     else:
         k = _keys(layout, n // copies, 3)[rng.integers(0, n // copies, n)]
     v = rng.integers(0, 1 << 20, n).astype(dt)
-    t, o = make_table(layout, 20), oracle.OracleTable(layout, 20)
+    t, o = make_table(layout, log2c), oracle.OracleTable(layout, log2c)
     t.build(to_dev(k), to_dev(v), op=op)
     o.build(k, v, op)
     assert np.array_equal(cells_host(t), o.cells())
