@@ -89,7 +89,8 @@ Device g_dev[kMaxDevices];
 std::unordered_map<void *, Block> g_blocks;  // every block the library holds
 std::vector<hipEvent_t> g_events;            // spare
 uint64_t g_seq = 0;
-// blocks handed out by pool_alloc and not yet given back to pool_free
+// blocks handed out by pool_alloc, or being made by it, and not yet given back
+// to pool_free
 long long g_out = 0;
 
 // Classes: powers of two up to 64 KiB, above that eight steps per power of
@@ -323,6 +324,15 @@ void *pool_alloc(int device, size_t bytes, hipStream_t s, bool in_order) try {
   const bool captured = capturing(s);
   std::unique_lock<std::mutex> lk(g_mu);
   Device &D = g_dev[device];
+  // counted from here on: the lock is given up on the way, and the pools must
+  // not be released meanwhile
+  struct Counted {
+    bool kept = false;
+    Counted() { ++g_out; }
+    ~Counted() {
+      if (!kept) --g_out;
+    }
+  } counted;
   void *p = nullptr;
   if (captured) {
     p = graph_alloc(device, bytes, s);
@@ -332,7 +342,7 @@ void *pool_alloc(int device, size_t bytes, hipStream_t s, bool in_order) try {
     if (!p) p = fresh(device, cls, s, in_order, lk);
     hold_bound(D, device, s);
   }
-  if (p) ++g_out;
+  counted.kept = p != nullptr;
   return p;
 } catch (const std::bad_alloc &) {
   return nullptr;  // host memory for the bookkeeping

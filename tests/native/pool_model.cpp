@@ -33,6 +33,7 @@ struct Event {
   uint64_t at = 0;
 };
 std::set<Event *> events;
+void (*during_alloc)() = nullptr;  // runs while the runtime makes a block
 bool capture_elsewhere = false, invalidated = false, refuse_free = false;
 uint64_t device_waits = 0, event_waits = 0;
 thread_local hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
@@ -106,6 +107,7 @@ hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t) {
   return hipSuccess;
 }
 hipError_t hipMallocFromPoolAsync(void **p, size_t n, hipMemPool_t, hipStream_t) {
+  if (during_alloc) during_alloc();
   LOCK;
   return give(p, n, true);
 }
@@ -217,7 +219,7 @@ int main() {
     pool_free(a, handle(1));
     finish(1);
     void *b = pool_alloc(0, 2 * kMiB, handle(2));
-    hipMemPoolTrimTo(nullptr, 0);                   // (the runtime's next synchronisation)
+    (void)hipMemPoolTrimTo(nullptr, 0);                 // (the runtime's next synchronisation)
     show("reserved_within_bound", reserved <= 17 * kGiB);
     show("waits_over_bound", device_waits + event_waits - waits);
     pool_free(b, handle(2));
@@ -253,6 +255,15 @@ int main() {
     show("waits_at_last", device_waits + event_waits - waits);
     finish(1);
     pool_free(c, handle(2));
+  }
+  // a release while a block is being made
+  {
+    static int rc = LPHT_OK;
+    during_alloc = [] { std::thread([] { rc = release_pools(); }).join(); };
+    void *a = pool_alloc(0, 7 * kMiB, handle(1));
+    during_alloc = nullptr;
+    show("release_refused", a && rc == LPHT_ERR_INVALID);
+    pool_free(a, handle(1));
   }
   show("released", release_pools() == LPHT_OK);
   show("left", live.size());

@@ -39,5 +39,9 @@ def test_room_is_made_without_waiting_for_the_device(seen):
     assert seen["waits_at_last"] == 0
 
 
+def test_no_release_while_a_block_is_made(seen):
+    assert seen["release_refused"]
+
+
 def test_everything_is_released(seen):
     assert seen["released"] and seen["left"] == 0 and seen["events_left"] == 0
